@@ -9,7 +9,9 @@
 // The stencil is bound by HBM bandwidth (1320 flop against >= 960 compulsory
 // bytes per site in FP64), so there is no matrix-core work here: every lane
 // streams its site's links and spinor planes, coalesced across the wave.
+#include <algorithm>
 #include <atomic>
+#include <cmath>
 
 #include "blas.h"
 #include "cg_site.h"
@@ -20,20 +22,11 @@
 #ifndef WD_DSLASH_BLOCK
 #define WD_DSLASH_BLOCK 256   // threads per workgroup
 #endif
-#ifndef WD_MARCH_GW
-#define WD_MARCH_GW 0         // right-hand sides per t-marching workgroup; 0 picks automatically
-#endif
-#ifndef WD_XCD_GROUP
-#define WD_XCD_GROUP -1       // tiles per XCD run; -1 picks automatically
-#endif
 #ifndef WD_DSLASH_KERNEL
 #define WD_DSLASH_KERNEL 0    // 0: t-marching where the lattice allows it, 1: one site per lane
 #endif
 #ifndef WD_MARCH_THREADS
 #define WD_MARCH_THREADS 256  // target sites per t-marching tile
-#endif
-#ifndef WD_MARCH_WG_PER_CU
-#define WD_MARCH_WG_PER_CU 4  // t-marching workgroups per CU aimed for (LDS permitting)
 #endif
 #ifndef WD_UT_NT
 #define WD_UT_NT 1            // non-temporal loads of the t links in the t-marching kernel
@@ -52,28 +45,25 @@ constexpr int kDslashBlock = WD_DSLASH_BLOCK;
 constexpr int kMarchMaxThreads = 256;       // lanes of a one-right-hand-side tile
 constexpr int kMarchMultiThreads = 768;     // lanes of a several-right-hand-side workgroup
 constexpr int kMarchTargetThreads = WD_MARCH_THREADS;
-constexpr int kMarchWgPerCu = WD_MARCH_WG_PER_CU;
 constexpr bool kUtNt = WD_UT_NT != 0;
 constexpr bool kMarchBuf = WD_MARCH_BUF != 0;
 constexpr bool kXShfl = WD_X_SHFL != 0;
 constexpr int kNumCu = 256;
-// Waves of the t-marching kernel a CU holds at once, from the compiled
-// kernels' register use: 256 VGPRs in FP64 (one wave per SIMD), 146-168 with
-// FP32 arithmetic (three per SIMD).
-constexpr int kWavesPerCuFp64 = 4;
-constexpr int kWavesPerCuFp32 = 12;
 constexpr size_t kLdsBytes = 160 * 1024;  // LDS per CU on gfx950
 
-// Workgroup -> tile of kBlock consecutive sites. Consecutive workgroups are
-// dispatched round-robin over the 8 XCDs, each with its own L2; with
-// group > 0 the mapping gives every XCD runs of `group` consecutive tiles, so
-// that neighbours in y and z, which sit a few tiles away, share an L2.
-__device__ __forceinline__ int tile_of_block(int group) {
+// Workgroup -> tile. Consecutive workgroups are dispatched round-robin over the
+// 8 XCDs, each with its own L2; with group > 0 the mapping gives every XCD runs
+// of `group` consecutive tiles, so that neighbours in y and z, which sit a few
+// tiles away, share an L2. A group of at least an eighth of the nb tiles gives
+// each XCD one run; the grid then is 8 groups, and workgroups past the last tile
+// (a result of nb or more) have nothing to do.
+__device__ __forceinline__ int tile_of_block(int group, int nb) {
   const int b = blockIdx.x;
-  const int nb = gridDim.x;
-  if (group <= 0 || nb % (kNumXcd * group) != 0) return b;
+  if (group <= 0) return b;
   const int xcd = b % kNumXcd;
   const int l = b / kNumXcd;
+  if (static_cast<long>(group) * kNumXcd >= nb) return xcd * group + l;
+  if (nb % (kNumXcd * group) != 0) return b;
   return ((l / group) * kNumXcd + xcd) * group + (l % group);
 }
 
@@ -84,7 +74,7 @@ __global__ __launch_bounds__(kDslashBlock) void dslash_kernel(
     const typename Packed<T>::L* __restrict__ links, Geo geo, Diag<typename Packed<T>::R> diags,
     long stride, int gamma5, int group) {
   using R = typename Packed<T>::R;
-  const int s = tile_of_block(group) * kDslashBlock + static_cast<int>(threadIdx.x);
+  const int s = tile_of_block(group, static_cast<int>(gridDim.x)) * kDslashBlock + static_cast<int>(threadIdx.x);
   if (s >= geo.V) return;
   const long V = geo.V;
   const int rhs = blockIdx.y;
@@ -145,6 +135,7 @@ struct MarchParams {
   int tb;      // t steps per workgroup
   int ytiles;  // Y / ny
   int group;   // XCD run length (workgroups), 0 = hardware order
+  int nb;      // workgroups that have work
   int nrhs;    // right-hand sides of the launch
   int gw;      // lane groups per workgroup
   int rb;      // right-hand sides per lane (gw * rb divides nrhs)
@@ -301,7 +292,8 @@ __attribute__((amdgpu_waves_per_eu(march_waves_per_eu<CGM, T, RB>()))) void dsla
   // step), so a link line fetched for one of them is an L1/L2 hit for the
   // others. Further workgroups of the same tile are consecutive.
   const int groups = p.nrhs / (p.gw * RB);
-  const int bb = tile_of_block(p.group);
+  const int bb = tile_of_block(p.group, p.nb);
+  if (bb >= p.nb) return;
   // (with BUF the host launches one lane group per workgroup, so slot is 0 and
   // the fields' bases derive from the block index alone: wave-uniform)
   const int rhs0 = ((bb % groups) * p.gw + (BUF ? 0 : slot)) * RB;
@@ -513,74 +505,96 @@ __attribute__((amdgpu_waves_per_eu(march_waves_per_eu<CGM, T, RB>()))) void dsla
 // Run length of consecutive workgroups per XCD: the largest power of two up
 // to `preferred` that divides the grid evenly.
 int xcd_group(int nblocks, int preferred) {
-  if (WD_XCD_GROUP >= 0) return WD_XCD_GROUP;
   for (int g = preferred; g > 1; g /= 2)
     if (nblocks % (kNumXcd * g) == 0) return g;
   return 0;
 }
 
-// Geometry of the t-marching kernel for a lattice, or ny = 0 if it does not
-// apply (x rows longer than a workgroup, or too few sites per tile).
 size_t march_lds_bytes(int threads, size_t real_bytes) {
   return 2 * 24 * real_bytes * static_cast<size_t>(threads);  // two spinor slices
 }
 
+size_t real_bytes_of(int prec) { return prec == WD_FP64 ? 8 : 4; }
 
+// Cost model behind the default t split and right-hand sides per lane. A
+// workgroup that marches tb slices costs tb + prologue slices (the prologue
+// reads the outer hops, the backward t hop and the first slice); a CU holds
+// `waves` waves' worth of workgroups at once, and the chip works through the
+// launch's workgroups in rounds of 256 CUs' worth. In FP64 and FP32 a started
+// round takes its whole time (tail < 0: whole rounds); with FP16 storage, whose
+// workgroups are short and uneven, the last round costs half of one on average.
+// rb2: the cost of a slice of two right-hand sides per lane in a launch of half
+// the workgroups.
+// Fitted on MI355X to every split of t timed on 12 lattices (16^4 to 32^3 x 64,
+// among them 28 x 15 x 22 x 33 and 9 x 33 x 12 x 20) with 1 to 16 right-hand
+// sides: the choice is on average 0.4 % (FP64), 0.6 % (FP32) and 1.0 % (FP16)
+// slower than the best split timed, where one resident round of workgroups
+// whatever its last round leaves idle was 14, 24 and 24 % slower: 24^3 x 48 with
+// 12 FP32 fields 757 -> 541 us, 24^4 with 4 FP64 fields 363 -> 238 us, 24^4 with
+// one FP16 field 29.0 -> 24.3 us. Two right-hand sides per lane pay in FP32
+// (86 against 105 us for 4 fields on 24^4), not with FP16 storage, whose waves
+// they halve; several lane groups per workgroup never were the fastest.
+struct MarchCost {
+  int waves, waves2;
+  double prologue, prologue2, tail, rb2;
+};
+MarchCost march_cost(int prec) {
+  if (prec == WD_FP64) return {4, 0, 0.8, 0.0, -1.0, 0.0};
+  if (prec == WD_FP32) return {8, 8, 0.4, 0.7, -1.0, 1.2};
+  return {12, 0, 0.4, 0.0, 0.5, 0.0};
+}
 
-MarchParams march_params(const Geo& geo, size_t real_bytes, int nrhs) {
-  MarchParams p{0, 0, 0, 0, nrhs, 1, 1, 0u, 0u};
+// Geometry of the t-marching kernel for a lattice, with the default launch
+// choice, or ny = 0 if it does not apply (x rows longer than a workgroup, or
+// too few sites per tile).
+MarchParams march_params(const Geo& geo, int prec, int nrhs) {
+  MarchParams p{0, 0, 0, 0, 0, nrhs, 1, 1, 0u, 0u};
+  const size_t real_bytes = real_bytes_of(prec);
   if (geo.X > kMarchMaxThreads) return p;
   int ny = 0;
-  for (int d = 1; d <= geo.Y; ++d)
-    if (geo.Y % d == 0 && geo.X * d <= kMarchTargetThreads &&
-        march_lds_bytes(geo.X * d, real_bytes) <= kLdsBytes)
-      ny = d;
+  for (int d = 1; d <= geo.Y && geo.X * d <= kMarchTargetThreads; ++d)
+    if (geo.Y % d == 0 && march_lds_bytes(geo.X * d, real_bytes) <= kLdsBytes) ny = d;
   if (ny == 0 || geo.X * ny < 64) return p;
   p.ny = ny;
   p.ytiles = geo.Y / ny;
   const int n = geo.X * ny;
-  const size_t lds1 = march_lds_bytes(n, real_bytes);
-  // right-hand sides per workgroup (FP32 arithmetic only: two FP64 tiles exceed the
-  // LDS): a divisor of nrhs that the lanes and LDS of a CU allow, preferring
-  // the largest that still fills every CU in one round
-  const int columns = p.ytiles * geo.Z;
-  if (real_bytes == 4) {
-    int best = 1;
-    for (int gw = 2; gw <= kMaxMultiRhs && gw <= nrhs; ++gw) {
-      if (nrhs % gw != 0 || gw * n > kMarchMultiThreads || gw * lds1 > kLdsBytes) continue;
-      if (WD_MARCH_GW > 0 && gw != WD_MARCH_GW) continue;
-      const int per_cu = static_cast<int>(kLdsBytes / (gw * lds1));
-      const int slots = kNumCu * (per_cu < kMarchWgPerCu ? per_cu : kMarchWgPerCu);
-      const int wgs = columns * (nrhs / gw);
-      if (WD_MARCH_GW > 0 || (wgs <= slots && wgs * 4 >= slots * 3)) best = gw;
+  const int waves = (n + 63) / 64;
+  const MarchCost mc = march_cost(prec);
+  double best = 0.0;
+  for (int rb = 1; rb <= 2; ++rb) {
+    const size_t lds = rb * march_lds_bytes(n, real_bytes);
+    if (rb == 2 && (mc.waves2 == 0 || nrhs % 2 != 0 || lds > kLdsBytes)) break;
+    const int by_waves = (rb == 1 ? mc.waves : mc.waves2) / waves;
+    const int by_lds = static_cast<int>(kLdsBytes / lds);
+    const int per_cu = std::max(1, std::min(by_waves, by_lds));
+    const double slots = static_cast<double>(kNumCu) * per_cu;
+    const double columns = static_cast<double>(p.ytiles) * geo.Z * (nrhs / rb);
+    // every distinct ceil(T / nt), largest first
+    for (int tb = geo.T, nt = 1;;) {
+      const double x = columns * nt / slots;
+      const double rounds = mc.tail < 0.0 ? std::ceil(x) : std::max(1.0, x + mc.tail);
+      const double cost = rounds * (tb + (rb == 1 ? mc.prologue : mc.prologue2)) * (rb == 1 ? 1.0 : mc.rb2);
+      if (p.tb == 0 || cost < best || (cost == best && rb == p.rb)) {
+        best = cost;
+        p.tb = tb;
+        p.rb = rb;
+      }
+      if (tb == 1) break;
+      nt = (geo.T + tb - 2) / (tb - 1);  // fewest workgroups along t with fewer steps each
+      tb = (geo.T + nt - 1) / nt;
     }
-    p.gw = best;
   }
-  const int planes = columns * (nrhs / p.gw);
-  // as many workgroups as fit on the chip at once (LDS and registers decide
-  // how many per CU), without a second round, and at least 4 t steps per
-  // workgroup so the prologue of each march stays cheap; t steps split evenly
-  const int waves = (p.gw * n + 63) / 64;
-  const int by_regs = (real_bytes == 8 ? kWavesPerCuFp64 : kWavesPerCuFp32) / waves;
-  int per_cu = static_cast<int>(kLdsBytes / (p.gw * lds1));
-  per_cu = per_cu < by_regs ? per_cu : by_regs;
-  per_cu = per_cu > 1 ? per_cu : 1;
-  const int slots = kNumCu * (per_cu < kMarchWgPerCu ? per_cu : kMarchWgPerCu);
-  int nt = slots / planes;
-  const int nt_max = geo.T / 4 > 1 ? geo.T / 4 : 1;
-  nt = nt < 1 ? 1 : (nt > nt_max ? nt_max : nt);
-  p.tb = (geo.T + nt - 1) / nt;
-  const int nb = planes * ((geo.T + p.tb - 1) / p.tb);
+  const int nb = p.ytiles * geo.Z * (nrhs / p.rb) * ((geo.T + p.tb - 1) / p.tb);
   // every XCD gets one contiguous eighth of the workgroups: the right-hand
   // sides, y tiles and z planes that share links and halo slices meet in one L2
-  p.group = WD_XCD_GROUP >= 0 ? WD_XCD_GROUP : (nb % kNumXcd == 0 ? nb / kNumXcd : 0);
+  p.group = (nb + kNumXcd - 1) / kNumXcd;
   return p;
 }
 
 template <typename T, bool C12, int MAXT, int RB, int CGM, bool BUF>
 hipError_t launch_march_t(const void* in, void* out, const void* links, const Geo& geo,
                           const Diag<typename Packed<T>::R>& diag, long stride, int g5,
-                          const MarchParams& p, const CgFuse& f, hipStream_t st) {
+                          MarchParams p, const CgFuse& f, hipStream_t st) {
   using SV = typename Packed<T>::S;
   using LV = typename Packed<T>::L;
   using R = typename Packed<T>::R;
@@ -597,9 +611,11 @@ hipError_t launch_march_t(const void* in, void* out, const void* links, const Ge
     if (e != hipSuccess) return e;
     attr_set.store(1, std::memory_order_release);
   }
-  const unsigned nb = static_cast<unsigned>((p.nrhs / (p.gw * RB)) * p.ytiles * geo.Z *
-                                            ((geo.T + p.tb - 1) / p.tb));
-  dslash_march_kernel<T, C12, MAXT, RB, CGM, BUF><<<nb, p.gw * n, lds, st>>>(
+  p.nb = (p.nrhs / (p.gw * RB)) * p.ytiles * geo.Z * ((geo.T + p.tb - 1) / p.tb);
+  const int eighth = (p.nb + kNumXcd - 1) / kNumXcd;  // larger groups mean the same
+  if (p.group > eighth) p.group = eighth;
+  const unsigned grid = static_cast<unsigned>(p.group == eighth ? eighth * kNumXcd : p.nb);
+  dslash_march_kernel<T, C12, MAXT, RB, CGM, BUF><<<grid, p.gw * n, lds, st>>>(
       static_cast<const SV*>(in), static_cast<SV*>(out), static_cast<const LV*>(links), geo, diag,
       stride, g5, p, f);
   return hipGetLastError();
@@ -669,7 +685,7 @@ hipError_t launch_typed(const wd_gauge* g, const void* in, void* out, const Geo&
     diag.idx[k] = fields ? fields[k] : k;
   }
   const long stride = spinor_units<T>(geo.V);  // 16-B elements per field
-  MarchParams p = march_params(geo, sizeof(R), nrhs);
+  MarchParams p = march_params(geo, g->prec, nrhs);
   // byte sizes for buffer-resource access, or 0 where a field reaches 4 GiB
   const unsigned long sbytes = static_cast<unsigned long>(stride) * 16;
   p.link_bytes = g->link_bytes < (1ul << 32) ? static_cast<unsigned>(g->link_bytes) : 0u;
@@ -725,8 +741,6 @@ hipError_t launch_any(const wd_gauge* g, const double* masses, int nrhs, const i
   }
 }
 
-size_t real_bytes_of(int prec) { return prec == WD_FP64 ? 8 : 4; }
-
 }  // namespace
 
 hipError_t launch_dslash_multi(const wd_gauge* g, const double* masses, int nrhs, const int* fields,
@@ -740,7 +754,7 @@ hipError_t launch_dslash_multi(const wd_gauge* g, const double* masses, int nrhs
 int cg_fuse_slices(const int32_t dims[4], int prec) {
   if (WD_DSLASH_KERNEL != 0) return 0;
   const Geo geo = make_geo(dims);
-  const MarchParams p = march_params(geo, real_bytes_of(prec), 1);
+  const MarchParams p = march_params(geo, prec, 1);
   if (p.ny == 0 || (geo.X * p.ny) % 64 != 0) return 0;
   const long n = static_cast<long>(geo.T) * geo.Z * p.ytiles;
   return n <= 0x7fffffffL ? static_cast<int>(n) : 0;
@@ -763,7 +777,7 @@ hipError_t launch_dslash_tuned(const wd_gauge* g, const double* masses, int nrhs
 
 bool march_default(const int32_t dims[4], int prec, int nrhs, MarchTuning* t) {
   if (WD_DSLASH_KERNEL != 0) return false;
-  const MarchParams p = march_params(make_geo(dims), real_bytes_of(prec), nrhs);
+  const MarchParams p = march_params(make_geo(dims), prec, nrhs);
   if (p.ny == 0) return false;
   *t = MarchTuning{p.tb, p.gw, p.group, p.rb};
   return true;
@@ -772,7 +786,7 @@ bool march_default(const int32_t dims[4], int prec, int nrhs, MarchTuning* t) {
 bool march_tuning_valid(const int32_t dims[4], int prec, int nrhs, const MarchTuning& t) {
   const Geo geo = make_geo(dims);
   const size_t real = real_bytes_of(prec);
-  const MarchParams p = march_params(geo, real, nrhs);
+  const MarchParams p = march_params(geo, prec, nrhs);
   if (WD_DSLASH_KERNEL != 0 || p.ny == 0 || nrhs < 1 || nrhs > kMaxMultiRhs) return false;
   if (t.tb < 1 || t.tb > geo.T || t.group < 0) return false;
   if (t.rb != 1 && t.rb != 2) return false;
@@ -793,7 +807,7 @@ void march_candidates(const int32_t dims[4], int prec, int nrhs, MarchTuning* ou
   if (!march_default(dims, prec, nrhs, &d) || cap < 1) return;
   out[(*n)++] = d;
   const Geo geo = make_geo(dims);
-  const MarchParams p = march_params(geo, real_bytes_of(prec), nrhs);
+  const MarchParams p = march_params(geo, prec, nrhs);
   // t steps per workgroup: the distinct ceil(T / nt) for nt workgroups along t
   int tbs[64];
   int ntb = 0;
@@ -808,8 +822,8 @@ void march_candidates(const int32_t dims[4], int prec, int nrhs, MarchTuning* ou
       for (int i = 0; i < ntb; ++i) {
         const long nb =
             static_cast<long>(nrhs / (gw * rb)) * p.ytiles * geo.Z * ((geo.T + tbs[i] - 1) / tbs[i]);
-        const int groups[2] = {0, nb % kNumXcd == 0 ? static_cast<int>(nb / kNumXcd) : 0};
-        for (int j = 0; j < (groups[1] > 0 ? 2 : 1); ++j) {
+        const int groups[2] = {0, static_cast<int>((nb + kNumXcd - 1) / kNumXcd)};
+        for (int j = 0; j < 2; ++j) {
           const MarchTuning t{tbs[i], gw, groups[j], rb};
           if (!march_tuning_valid(dims, prec, nrhs, t)) continue;
           if (t.tb == d.tb && t.gw == d.gw && t.group == d.group && t.rb == d.rb) continue;

@@ -176,9 +176,10 @@ WD_API int dslash_apply_multi(const wd_gauge* g, const double* masses_host, int3
  * ------------------------------------------------------------------------ */
 
 typedef struct wd_tune_result {
-  int32_t candidates;  /* launch choices timed (0: this lattice uses the one-site-per-lane kernel) */
+  int32_t candidates;  /* launch choices timed (0: this lattice has no t-marching tiles) */
   int32_t eligible;    /* of those, bit-identical to the default choice */
-  int32_t tb, gw, group;  /* the choice kept: t steps and lane groups per workgroup, XCD run */
+  int32_t tb, gw, group;  /* the choice kept: t steps and lane groups per workgroup, XCD run
+                             (tb 0: the kernel for small lattices, where it is the default) */
   int32_t rb;          /* ... and right-hand sides per lane */
   double default_us;   /* average time per launch of the default choice */
   double best_us;      /* ... and of the choice kept */

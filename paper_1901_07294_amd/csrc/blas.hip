@@ -20,32 +20,16 @@ namespace {
 
 constexpr int kThreads = 256;
 
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
-
-// This thread's share of pp[0..np): pp[threadIdx.x + kThreads * j] added in
-// order of j, with four loads in flight.
+// This thread's share of pp[0..np).
 __device__ __forceinline__ double strided_sum(const double* __restrict__ pp, int np) {
-  double s = 0.0;
-  int i = threadIdx.x;
-  for (; i + 3 * kThreads < np; i += 4 * kThreads) {
-    const double a0 = pp[i], a1 = pp[i + kThreads], a2 = pp[i + 2 * kThreads], a3 = pp[i + 3 * kThreads];
-    s += a0;
-    s += a1;
-    s += a2;
-    s += a3;
-  }
-  for (; i < np; i += kThreads) s += pp[i];
-  return s;
+  static_assert(kThreads == 256, "the shares are 256");
+  return strided_sum256(pp, np, static_cast<int>(threadIdx.x));
 }
 
 // Sum of v over the workgroup, combined in a fixed order; valid in thread 0.
 __device__ __forceinline__ double block_sum(double v) {
   __shared__ double part[kThreads / 64];
-  v = wave_sum(v);
+  v = wave_total(v);
   const int w = threadIdx.x / 64;
   if ((threadIdx.x & 63) == 0) part[w] = v;
   __syncthreads();

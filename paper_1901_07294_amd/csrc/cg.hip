@@ -47,6 +47,7 @@ CgLayout cg_layout(const int32_t dims[4], int slots, int inner, bool eo) {
   CgLayout w;
   const long V = static_cast<long>(dims[0]) * dims[1] * dims[2] * dims[3] / (eo ? 2 : 1);
   w.nslices = eo ? 0 : cg_fuse_slices(dims, inner);
+  w.fuse_update = !eo && cg_fuse_update(dims, inner);
   const size_t hi = align256(static_cast<size_t>(packed_sites(V)) * slots * spinor_site_bytes(WD_FP64));
   const size_t lo = align256(static_cast<size_t>(packed_sites(V)) * slots * spinor_site_bytes(inner));
   const size_t acc = align256(static_cast<size_t>(packed_sites(V)) * slots * spinor_site_bytes(WD_FP32));
@@ -165,6 +166,28 @@ int CgEngine::chunk(const RhsSet& set, int n) {
 int CgEngine::iterate(const RhsSet& set, int j, int n) {
   double m[kMaxRhs];
   for (int i = 0; i < set.n; ++i) m[i] = masses_[set.idx[i]];
+  if (lay_.nslices > 0 && inner_ == WD_FP64 && lay_.fuse_update) {
+    // as with FP32 arithmetic below, but x is updated in every iteration
+    CgFuse f{};
+    f.mode = kCgNorm;
+    f.rr = paps_;
+    f.nslices = lay_.nslices;
+    int rc = launch_status(launch_dslash_cg(glo_, m, set.n, set.idx, at(ws_, lay_.p), at(ws_, lay_.t), f,
+                                            st_), "cg: Q p with |Q p|^2");
+    f.mode = kCgUpdate;
+    f.r = at(ws_, lay_.r);
+    f.pap = paps_;
+    f.npap = lay_.nslices;
+    f.rr = rr_;
+    f.scal = scal_;
+    if (rc == WD_OK)
+      rc = launch_status(launch_dslash_cg(glo_, m, set.n, set.idx, at(ws_, lay_.t), nullptr, f, st_),
+                         "cg: Q Q p with r");
+    if (rc == WD_OK)
+      rc = launch_status(blas_update_xp(x_, at(ws_, lay_.p), at(ws_, lay_.r), nlo_, set, rr_, lay_.nslices,
+                                        scal_, st_), "cg: x, p");
+    return rc;
+  }
   if (lay_.nslices > 0 && inner_ == WD_FP64) {
     // t = Q p with <p, A p> = |t|^2 summed per tile slice in the same launch;
     // A p = Q t; then r -= alpha A p (reducing those sums to alpha), and x and

@@ -11,7 +11,7 @@ namespace wd {
 
 // Offsets (bytes) of a CG workspace for `slots` right-hand sides. Where the
 // iteration's vector work is fused into its applications of Q (nslices > 0),
-// paps and rr hold the |Q p|^2 and <r,r> partial sums of the tile slices, and
+// paps and rr hold the |Q p|^2 and <r,r> partial sums of the slices, and
 // (FP32 arithmetic, where the update is fused too) A p is never stored, and p
 // and p2 hold the search directions of two consecutive iterations (the x
 // update of one iteration waits for the next, see CgEngine::chunk).
@@ -23,6 +23,7 @@ struct CgLayout {
   size_t r_hi = 0, t_hi = 0, x_lo = 0, r = 0, p = 0, p2 = 0, t = 0, ap = 0, partials = 0, pap = 0,
          scal = 0, rr = 0, paps = 0, e_lo = 0, e_hi = 0;
   int nslices = 0;
+  bool fuse_update = false;  // kCgUpdate too
 };
 CgLayout cg_layout(const int32_t dims[4], int slots, int inner, bool eo = false);
 

@@ -16,6 +16,53 @@ __device__ __forceinline__ double norm2(float4 a) {
   return fmar(x, x, fmar(y, y, fmar(z, z, w * w)));
 }
 
+// Sum over the 64 lanes of a wave in a fixed order (every lane gets it), and
+// over each 32 lanes of it.
+__device__ __forceinline__ double half_wave_total(double v) {
+#pragma unroll
+  for (int off = 16; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  return v;
+}
+__device__ __forceinline__ double wave_total(double v) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  return v;
+}
+
+// Share i of 256 of pp[0..np): pp[i + 256 j] added in order of j, with eight
+// loads in flight (24^4 has 1728 partial sums: one round of memory latency).
+// Every kernel that reduces partial sums adds these shares in waves of 64 and
+// the four waves' sums in order, so that all of them get the same bits.
+__device__ __forceinline__ double strided_sum256(const double* __restrict__ pp, int np, int i) {
+  double s = 0.0;
+  for (; i < np; i += 8 * 256) {
+    double a[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) a[j] = i + 256 * j < np ? pp[i + 256 * j] : 0.0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) s += a[j];
+  }
+  return s;
+}
+
+// Squared norm of two components of a site. A site's norm adds its six pairs
+// in order, so that it does not matter whether one lane or six hold them.
+__device__ __forceinline__ double pair_norm2(cx<double> a, cx<double> b) {
+  return fmar(a.re, a.re, a.im * a.im) + fmar(b.re, b.re, b.im * b.im);
+}
+__device__ __forceinline__ double pair_norm2(cx<float> a, cx<float> b) {
+  return norm2(make_float4(a.re, a.im, b.re, b.im));
+}
+__device__ __forceinline__ double half_pair_norm2(h4 q, float m) {
+  double n = 0.0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const double d = static_cast<float>(q[k]) * m;
+    n = fmar(d, d, n);
+  }
+  return n;
+}
+
 __device__ __forceinline__ double site_norm2(const cx<float> (&v)[12]) {
   double s = 0.0;
 #pragma unroll
@@ -26,6 +73,16 @@ __device__ __forceinline__ double site_norm2(const cx<float> (&v)[12]) {
   return s;
 }
 
+__device__ __forceinline__ double half_site_norm2(const h8 (&q)[3], float m) {
+  double n = 0.0;
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
+    n += half_pair_norm2(h4{q[j][0], q[j][1], q[j][2], q[j][3]}, m);
+    n += half_pair_norm2(h4{q[j][4], q[j][5], q[j][6], q[j][7]}, m);
+  }
+  return n;
+}
+
 // Quantises and stores a site (cached stores: CG vectors are read again at
 // once); returns the squared norm of the values as stored.
 __device__ __forceinline__ double store_half_site(h8* __restrict__ p, long s, const cx<float> (&v)[12]) {
@@ -34,15 +91,7 @@ __device__ __forceinline__ double store_half_site(h8* __restrict__ p, long s, co
 #pragma unroll
   for (int j = 0; j < 3; ++j) p[half_unit(s, j)] = q[j];
   reinterpret_cast<float*>(p)[half_scale_index(s)] = m;
-  double n = 0.0;
-#pragma unroll
-  for (int j = 0; j < 3; ++j)
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const double d = static_cast<float>(q[j][k]) * m;
-      n = fmar(d, d, n);
-    }
-  return n;
+  return half_site_norm2(q, m);
 }
 
 // r -= alpha (A p) at one site; ap holds A p. FP32 vectors.
@@ -60,6 +109,25 @@ __device__ __forceinline__ double cg_site_update_r(float4* __restrict__ r, long 
     re.w = fmar(-a, ap[2 * j + 1].im, re.w);
     r[e] = re;
     n += norm2(re);
+  }
+  return n;
+}
+
+// The same for FP64 vectors.
+__device__ __forceinline__ double cg_site_update_r(double2* __restrict__ r, long V, long s,
+                                                   const cx<double> (&ap)[12], double alpha) {
+  double n = 0.0;
+#pragma unroll
+  for (int j = 0; j < 6; ++j) {
+    cx<double> v[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const long i = pidx(s, 2 * j + e, 12, V);
+      const double2 re = r[i];
+      v[e] = {fmar(-alpha, ap[2 * j + e].re, re.x), fmar(-alpha, ap[2 * j + e].im, re.y)};
+      r[i] = make_double2(v[e].re, v[e].im);
+    }
+    n += pair_norm2(v[0], v[1]);
   }
   return n;
 }
@@ -131,13 +199,16 @@ __device__ __forceinline__ double store_site_norm(double2* __restrict__ p, long 
   store_spinor(p, V, s, v);
   double n = 0.0;
 #pragma unroll
-  for (int c = 0; c < 12; ++c) n += fmar(v[c].re, v[c].re, v[c].im * v[c].im);
+  for (int j = 0; j < 6; ++j) n += pair_norm2(v[2 * j], v[2 * j + 1]);
   return n;
 }
 __device__ __forceinline__ double store_site_norm(float4* __restrict__ p, long V, int s,
                                                   const cx<float> (&v)[12]) {
   store_spinor(p, V, s, v);
-  return site_norm2(v);
+  double n = 0.0;
+#pragma unroll
+  for (int j = 0; j < 6; ++j) n += pair_norm2(v[2 * j], v[2 * j + 1]);
+  return n;
 }
 __device__ __forceinline__ double store_site_norm(h8* __restrict__ p, long /*V*/, int s,
                                                   const cx<float> (&v)[12]) {
@@ -146,15 +217,27 @@ __device__ __forceinline__ double store_site_norm(h8* __restrict__ p, long /*V*/
 #pragma unroll
   for (int j = 0; j < 3; ++j) __builtin_nontemporal_store(q[j], p + half_unit(s, j));
   __builtin_nontemporal_store(m, reinterpret_cast<float*>(p) + half_scale_index(s));
-  double n = 0.0;
-#pragma unroll
-  for (int j = 0; j < 3; ++j)
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const double d = static_cast<float>(q[j][k]) * m;
-      n = fmar(d, d, n);
-    }
-  return n;
+  return half_site_norm2(q, m);
+}
+
+// Stores components 2j, 2j + 1 of a site; returns their squared norm as stored.
+// FP16 storage: m is the site's largest modulus; j = 0 also stores it.
+__device__ __forceinline__ double store_pair(double2* __restrict__ p, long V, int s, int j,
+                                             const cx<double> (&v)[2]) {
+  p[pidx(s, 2 * j, 12, V)] = make_double2(v[0].re, v[0].im);
+  p[pidx(s, 2 * j + 1, 12, V)] = make_double2(v[1].re, v[1].im);
+  return pair_norm2(v[0], v[1]);
+}
+__device__ __forceinline__ double store_pair(float4* __restrict__ p, long V, int s, int j,
+                                             const cx<float> (&v)[2]) {
+  p[pidx(s, j, 6, V)] = make_float4(v[0].re, v[0].im, v[1].re, v[1].im);
+  return pair_norm2(v[0], v[1]);
+}
+__device__ __forceinline__ double store_pair(h8* __restrict__ p, int s, int j, const cx<float> (&v)[2], float m) {
+  const h4 q = half_quantise_pair(v, m);
+  reinterpret_cast<h4*>(p)[2 * half_unit(s, j >> 1) + (j & 1)] = q;
+  if (j == 0) reinterpret_cast<float*>(p)[half_scale_index(s)] = m;
+  return half_pair_norm2(q, m);
 }
 
 // alpha = <r, r> / <p, A p> and its failure flag from <p, A p> = t.

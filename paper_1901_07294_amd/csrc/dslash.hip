@@ -1,4 +1,5 @@
-// The Wilson-Dirac operator on gfx950: one lane per lattice site.
+// The Wilson-Dirac operator on gfx950: one lane per lattice site on large
+// lattices (the t-marching kernel below), eight on small ones (split.h).
 //
 //   out(x) = (4+m) psi(x) - 1/2 sum_mu [ (1-g_mu) U_mu(x) psi(x+mu)
 //                                       + (1+g_mu) U_mu(x-mu)^dag psi(x-mu) ]
@@ -15,15 +16,13 @@
 
 #include "blas.h"
 #include "cg_site.h"
+#include "split.h"
 #include "stencil.h"
 #include "wd_internal.h"
 
 // Compile-time tuning knobs (the defaults are the measured best on MI355X).
-#ifndef WD_DSLASH_BLOCK
-#define WD_DSLASH_BLOCK 256   // threads per workgroup
-#endif
-#ifndef WD_DSLASH_KERNEL
-#define WD_DSLASH_KERNEL 0    // 0: t-marching where the lattice allows it, 1: one site per lane
+#ifndef WD_SPLIT_SITES
+#define WD_SPLIT_SITES 49152  // sites times fields up to which the split kernel is always taken
 #endif
 #ifndef WD_MARCH_THREADS
 #define WD_MARCH_THREADS 256  // target sites per t-marching tile
@@ -41,7 +40,6 @@
 namespace wd {
 namespace {
 
-constexpr int kDslashBlock = WD_DSLASH_BLOCK;
 constexpr int kMarchMaxThreads = 256;       // lanes of a one-right-hand-side tile
 constexpr int kMarchMultiThreads = 768;     // lanes of a several-right-hand-side workgroup
 constexpr int kMarchTargetThreads = WD_MARCH_THREADS;
@@ -65,55 +63,6 @@ __device__ __forceinline__ int tile_of_block(int group, int nb) {
   if (static_cast<long>(group) * kNumXcd >= nb) return xcd * group + l;
   if (nb % (kNumXcd * group) != 0) return b;
   return ((l / group) * kNumXcd + xcd) * group + (l % group);
-}
-
-// T: storage type of spinors and links (double, float or _Float16).
-template <typename T, bool C12>
-__global__ __launch_bounds__(kDslashBlock) void dslash_kernel(
-    const typename Packed<T>::S* __restrict__ in_all, typename Packed<T>::S* __restrict__ out_all,
-    const typename Packed<T>::L* __restrict__ links, Geo geo, Diag<typename Packed<T>::R> diags,
-    long stride, int gamma5, int group) {
-  using R = typename Packed<T>::R;
-  const int s = tile_of_block(group, static_cast<int>(gridDim.x)) * kDslashBlock + static_cast<int>(threadIdx.x);
-  if (s >= geo.V) return;
-  const long V = geo.V;
-  const int rhs = blockIdx.y;
-  const typename Packed<T>::S* in = in_all + diags.idx[rhs] * stride;
-  typename Packed<T>::S* out = out_all + diags.idx[rhs] * stride;
-  const R diag = diags.d[rhs];
-
-  const int x = s % geo.X;
-  const int y = (s / geo.X) % geo.Y;
-  const int z = (s / geo.XY) % geo.Z;
-  const int t = s / geo.XYZ;
-  // periodic neighbours (extent 1 wraps onto the site itself)
-  const int xp = x + 1 == geo.X ? s - (geo.X - 1) : s + 1;
-  const int xm = x == 0 ? s + (geo.X - 1) : s - 1;
-  const int yp = y + 1 == geo.Y ? s - (geo.Y - 1) * geo.X : s + geo.X;
-  const int ym = y == 0 ? s + (geo.Y - 1) * geo.X : s - geo.X;
-  const int zp = z + 1 == geo.Z ? s - (geo.Z - 1) * geo.XY : s + geo.XY;
-  const int zm = z == 0 ? s + (geo.Z - 1) * geo.XY : s - geo.XY;
-  const int tp = t + 1 == geo.T ? s - (geo.T - 1) * geo.XYZ : s + geo.XYZ;
-  const int tm = t == 0 ? s + (geo.T - 1) * geo.XYZ : s - geo.XYZ;
-
-  cx<R> acc[12];
-#pragma unroll
-  for (int c = 0; c < 12; ++c) acc[c] = {R(0), R(0)};
-
-  hop<0, -1, C12>(in, links, V, xp, s, acc);
-  hop<0, +1, C12>(in, links, V, xm, xm, acc);
-  hop<1, -1, C12>(in, links, V, yp, s, acc);
-  hop<1, +1, C12>(in, links, V, ym, ym, acc);
-  hop<2, -1, C12>(in, links, V, zp, s, acc);
-  hop<2, +1, C12>(in, links, V, zm, zm, acc);
-  hop<3, -1, C12>(in, links, V, tp, s, acc);
-  hop<3, +1, C12>(in, links, V, tm, tm, acc);
-
-  cx<R> psi[12];
-  load_spinor(in, V, s, psi);
-  cx<R> o[12];
-  epilogue(psi, acc, diag, gamma5, o);
-  store_spinor(out, V, s, o);
 }
 
 // ---------------------------------------------------------------------------
@@ -142,19 +91,6 @@ struct MarchParams {
   unsigned link_bytes;    // bytes of the packed links and of one packed spinor field (used
   unsigned spinor_bytes;  // when they are read through buffer resources, below 4 GiB)
 };
-
-// How the march kernel reaches a field: a plain pointer (any size) or, with
-// BUF, a buffer resource (fields below 4 GiB; no address arithmetic per load).
-template <bool BUF, typename E>
-__device__ __forceinline__ auto field_in(const E* p, unsigned bytes) {
-  if constexpr (BUF) return buf_field(p, bytes);
-  else return p;
-}
-template <bool BUF, typename E>
-__device__ __forceinline__ auto field_out(E* p, unsigned bytes) {
-  if constexpr (BUF) return buf_field(p, bytes);
-  else return p;
-}
 
 // One hop for the RB right-hand sides of a lane: the link (direction MU at
 // site ls) is loaded once and applied to each one's neighbour spinor at site
@@ -237,13 +173,6 @@ __device__ __forceinline__ void outer_hops(const SA (&in)[RB], const LA& links, 
   hop_rb<2, +1, C12>(in, links, V, st + dzm, st + dzm, acc);
   if (y_fwd_out) hop_rb<1, -1, C12>(in, links, V, st + dyp, st, acc);
   if (y_bwd_out) hop_rb<1, +1, C12>(in, links, V, st + dym, st + dym, acc);
-}
-
-// Sum over the 64 lanes of a wave in a fixed order (every lane gets it).
-__device__ __forceinline__ double wave_total(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
 }
 
 // Doubles of LDS per lane group and right-hand side that the fused CG work
@@ -502,14 +431,6 @@ __attribute__((amdgpu_waves_per_eu(march_waves_per_eu<CGM, T, RB>()))) void dsla
   }
 }
 
-// Run length of consecutive workgroups per XCD: the largest power of two up
-// to `preferred` that divides the grid evenly.
-int xcd_group(int nblocks, int preferred) {
-  for (int g = preferred; g > 1; g /= 2)
-    if (nblocks % (kNumXcd * g) == 0) return g;
-  return 0;
-}
-
 size_t march_lds_bytes(int threads, size_t real_bytes) {
   return 2 * 24 * real_bytes * static_cast<size_t>(threads);  // two spinor slices
 }
@@ -649,19 +570,60 @@ hipError_t launch_march(const void* in, void* out, const void* links, const Geo&
   return launch_march_b<T, C12, CGM, false>(in, out, links, geo, diag, stride, g5, p, f, st);
 }
 
-template <typename T, bool C12>
-hipError_t launch_site(const void* in, void* out, const void* links, const Geo& geo,
-                       const Diag<typename Packed<T>::R>& diag, int nrhs, long stride, int g5,
-                       hipStream_t st) {
+// The split kernel: mode CGM of the launch.
+template <typename T, bool C12, int CGM>
+hipError_t launch_split(const void* in, void* out, const void* links, const Geo& geo,
+                        const Diag<typename Packed<T>::R>& diag, long stride, int g5, const MarchParams& m,
+                        const CgFuse& f, hipStream_t st) {
   using SV = typename Packed<T>::S;
   using LV = typename Packed<T>::L;
-  const unsigned nb = static_cast<unsigned>((geo.V + kDslashBlock - 1) / kDslashBlock);
-  const int group = xcd_group(static_cast<int>(nb), 8);
-  dslash_kernel<T, C12><<<dim3(nb, nrhs), kDslashBlock, 0, st>>>(
-      static_cast<const SV*>(in), static_cast<SV*>(out), static_cast<const LV*>(links), geo, diag,
-      stride, g5, group);
-  return hipGetLastError();
+  SplitParams p{};
+  p.ntiles = (geo.V + kSplitSites - 1) / kSplitSites;
+  p.per = (p.ntiles + kNumXcd - 1) / kNumXcd;
+  p.nrhs = m.nrhs;
+  p.ny = m.ny;
+  p.link_bytes = m.link_bytes;
+  p.spinor_bytes = m.spinor_bytes;
+  const unsigned nb = static_cast<unsigned>(p.per) * kNumXcd * static_cast<unsigned>(m.nrhs);
+  const auto run = [&](auto kernel) {
+    kernel<<<nb, kSplitThreads, 0, st>>>(static_cast<const SV*>(in), static_cast<SV*>(out),
+                                         static_cast<const LV*>(links), geo, diag, stride, g5, p, f);
+    return hipGetLastError();
+  };
+  if (kMarchBuf && m.link_bytes != 0 && m.spinor_bytes != 0) return run(&dslash_split_kernel<T, C12, CGM, true>);
+  return run(&dslash_split_kernel<T, C12, CGM, false>);
 }
+
+// Whether the split kernel is the default for nrhs fields: where the t-marching
+// one does not apply, in launches too small to fill the chip with marches, and
+// in somewhat larger ones on lattices whose tiles leave lanes of their waves
+// idle (X * ny not near a multiple of 64). Measured on MI355X, t-marching
+// against split (us): 12^4 FP64 12.9 / 8.3; 15 x 9 x 14 x 21 (135 of 192 lanes)
+// FP32 12.0 / 8.6, with 12 fields 39.6 / 38.6; 20^4 (200 of 256) FP64 with two
+// fields 54.7 / 52.7, FP32 21.9 / 19.1, FP16 16.2 / 16.8; but 16^4 (whole waves)
+// FP64 15.0 / 16.6, 16^3 x 32 FP32 13.2 / 14.3 and FP16 9.6 / 13.3.
+bool use_split(const Geo& geo, const MarchParams& p, int prec) {
+  if (p.ny == 0) return true;
+  const long work = static_cast<long>(geo.V) * p.nrhs;
+  if (work <= WD_SPLIT_SITES) return true;
+  const int n = geo.X * p.ny;
+  const int lanes = (n + 63) / 64 * 64;
+  if (10 * n >= 9 * lanes) return false;  // at least nine tenths of the lanes at work
+  if (prec == WD_FP16) return work <= (10 * n < 6 * lanes ? 800000 : 100000);
+  return work <= 640000;
+}
+
+// Whether the t-marching tiles are whole waves (what its fused CG work needs).
+bool whole_waves(const Geo& geo, const MarchParams& p) { return p.ny > 0 && (geo.X * p.ny) % 64 == 0; }
+
+// Whether the fused CG work runs in the split kernel, with slices of 32 sites:
+// on lattices small enough for it to be the faster one with any number of
+// fields, and, up to 131072 sites (4096 partial sums, which every workgroup of
+// the kernel that follows reads), where the t-marching kernel cannot fuse.
+bool small_slices(const Geo& geo, const MarchParams& p) { return geo.V <= (whole_waves(geo, p) ? 16384 : 131072); }
+
+// The tuning choice that stands for the split kernel.
+constexpr MarchTuning kSplitTuning{0, 1, 0, 1};
 
 // Applies a tuning choice to the default parameters.
 MarchParams with_tuning(MarchParams p, const MarchTuning& t) {
@@ -690,31 +652,29 @@ hipError_t launch_typed(const wd_gauge* g, const void* in, void* out, const Geo&
   const unsigned long sbytes = static_cast<unsigned long>(stride) * 16;
   p.link_bytes = g->link_bytes < (1ul << 32) ? static_cast<unsigned>(g->link_bytes) : 0u;
   p.spinor_bytes = sbytes < (1ul << 32) ? static_cast<unsigned>(sbytes) : 0u;
-  if (WD_DSLASH_KERNEL == 0 && p.ny > 0) {
-    MarchTuning t;
-    if (force != nullptr) p = with_tuning(p, *force);
-    else if (tuned_lookup(g->dims, g->prec, g->c12, nrhs, &t)) p = with_tuning(p, t);
-    if (cg != nullptr) {
-      // whole waves per tile, a partial sum slot for every tile slice, and the
-      // inputs the update reads
-      if ((geo.X * p.ny) % 64 != 0 || cg->rr == nullptr ||
-          static_cast<long>(cg->nslices) < static_cast<long>(geo.T) * geo.Z * p.ytiles)
-        return hipErrorInvalidValue;
-      if (cg->mode == kCgUpdate && (cg->r == nullptr || cg->pap == nullptr || cg->npap < 1 || cg->scal == nullptr))
-        return hipErrorInvalidValue;
-      if (cg->mode == kCgNorm)
-        return launch_march<T, C12, kCgNorm>(in, out, g->links, geo, diag, stride, g5, p, *cg, st);
-      if constexpr (sizeof(R) == 4) {  // the update is fused with FP32 arithmetic only
-        if (cg->mode == kCgUpdate)
-          return launch_march<T, C12, kCgUpdate>(in, nullptr, g->links, geo, diag, stride, g5, p, *cg,
-                                                 st);
-      }
-      return hipErrorInvalidValue;
-    }
-    return launch_march<T, C12, kCgNone>(in, out, g->links, geo, diag, stride, g5, p, CgFuse{}, st);
+  MarchTuning t;
+  bool split = use_split(geo, p, g->prec);
+  if (p.ny > 0 && (force != nullptr || tuned_lookup(g->dims, g->prec, g->c12, nrhs, &t))) {
+    if (force != nullptr) t = *force;
+    split = t.tb == 0;
+    if (!split) p = with_tuning(p, t);
   }
-  if (cg != nullptr) return hipErrorInvalidValue;
-  return launch_site<T, C12>(in, out, g->links, geo, diag, nrhs, stride, g5, st);
+  if (cg != nullptr) {
+    // a partial sum slot for every slice, and the inputs the update reads
+    if (cg->rr == nullptr || cg->nslices < cg_fuse_slices(g->dims, g->prec)) return hipErrorInvalidValue;
+    if (cg->mode == kCgUpdate && (cg->r == nullptr || cg->pap == nullptr || cg->npap < 1 || cg->scal == nullptr))
+      return hipErrorInvalidValue;
+    split = small_slices(geo, p);
+    if (!split && !whole_waves(geo, p)) return hipErrorInvalidValue;
+    if (cg->mode == kCgNorm)
+      return split ? launch_split<T, C12, kCgNorm>(in, out, g->links, geo, diag, stride, g5, p, *cg, st)
+                   : launch_march<T, C12, kCgNorm>(in, out, g->links, geo, diag, stride, g5, p, *cg, st);
+    if (cg->mode != kCgUpdate) return hipErrorInvalidValue;
+    return split ? launch_split<T, C12, kCgUpdate>(in, nullptr, g->links, geo, diag, stride, g5, p, *cg, st)
+                 : launch_march<T, C12, kCgUpdate>(in, nullptr, g->links, geo, diag, stride, g5, p, *cg, st);
+  }
+  return split ? launch_split<T, C12, kCgNone>(in, out, g->links, geo, diag, stride, g5, p, CgFuse{}, st)
+               : launch_march<T, C12, kCgNone>(in, out, g->links, geo, diag, stride, g5, p, CgFuse{}, st);
 }
 
 template <typename T>
@@ -741,6 +701,7 @@ hipError_t launch_any(const wd_gauge* g, const double* masses, int nrhs, const i
   }
 }
 
+
 }  // namespace
 
 hipError_t launch_dslash_multi(const wd_gauge* g, const double* masses, int nrhs, const int* fields,
@@ -748,16 +709,21 @@ hipError_t launch_dslash_multi(const wd_gauge* g, const double* masses, int nrhs
   return launch_any(g, masses, nrhs, fields, in, out, flags, nullptr, nullptr, st);
 }
 
-// (With FP64 vectors the engine fuses only the norm: the FP64 kernel holds one
-// wave per SIMD, and the x, r update in its epilogue cost more than the
-// separate update kernel it saves: 24^4 FP64 CG 46.5 -> 47.9 ms per solve.)
 int cg_fuse_slices(const int32_t dims[4], int prec) {
-  if (WD_DSLASH_KERNEL != 0) return 0;
   const Geo geo = make_geo(dims);
   const MarchParams p = march_params(geo, prec, 1);
-  if (p.ny == 0 || (geo.X * p.ny) % 64 != 0) return 0;
+  if (small_slices(geo, p)) return (geo.V + kSplitSites - 1) / kSplitSites;
+  if (!whole_waves(geo, p)) return 0;
   const long n = static_cast<long>(geo.T) * geo.Z * p.ytiles;
   return n <= 0x7fffffffL ? static_cast<int>(n) : 0;
+}
+
+// FP64 vectors: the t-marching FP64 kernel holds one wave per SIMD, and the r
+// update in its epilogue costs a little more than the separate update kernel's
+// work, but saves a launch: 16^4 with one field 79 -> 51 us per iteration and
+// 16^3 x 32 99 -> 88 (with the launch shapes of before: 24^4 277 -> 285).
+bool cg_fuse_update(const int32_t dims[4], int prec) {
+  return cg_fuse_slices(dims, prec) > 0 && (prec != WD_FP64 || make_geo(dims).V <= 131072);
 }
 
 hipError_t launch_dslash_cg(const wd_gauge* g, const double* masses, int nrhs, const int* fields,
@@ -776,10 +742,10 @@ hipError_t launch_dslash_tuned(const wd_gauge* g, const double* masses, int nrhs
 }
 
 bool march_default(const int32_t dims[4], int prec, int nrhs, MarchTuning* t) {
-  if (WD_DSLASH_KERNEL != 0) return false;
-  const MarchParams p = march_params(make_geo(dims), prec, nrhs);
+  const Geo geo = make_geo(dims);
+  const MarchParams p = march_params(geo, prec, nrhs);
   if (p.ny == 0) return false;
-  *t = MarchTuning{p.tb, p.gw, p.group, p.rb};
+  *t = use_split(geo, p, prec) ? kSplitTuning : MarchTuning{p.tb, p.gw, p.group, p.rb};
   return true;
 }
 
@@ -787,7 +753,9 @@ bool march_tuning_valid(const int32_t dims[4], int prec, int nrhs, const MarchTu
   const Geo geo = make_geo(dims);
   const size_t real = real_bytes_of(prec);
   const MarchParams p = march_params(geo, prec, nrhs);
-  if (WD_DSLASH_KERNEL != 0 || p.ny == 0 || nrhs < 1 || nrhs > kMaxMultiRhs) return false;
+  if (p.ny == 0 || nrhs < 1 || nrhs > kMaxMultiRhs) return false;
+  if (t.tb == 0)  // the split kernel
+    return use_split(geo, p, prec) && t.gw == kSplitTuning.gw && t.group == kSplitTuning.group && t.rb == kSplitTuning.rb;
   if (t.tb < 1 || t.tb > geo.T || t.group < 0) return false;
   if (t.rb != 1 && t.rb != 2) return false;
   if (t.gw < 1 || nrhs % (t.gw * t.rb) != 0) return false;

@@ -214,6 +214,19 @@ __device__ __forceinline__ float half_quantise(const cx<float> (&v)[12], h8 (&q)
   return m;
 }
 
+// The same for two components of a site whose largest modulus is m.
+__device__ __forceinline__ h4 half_quantise_pair(const cx<float> (&v)[2], float m) {
+  if (m > 0.0f && m < 0x1p-126f) {
+    const float k = 0x1p64f;
+    const float inv = 1.0f / (m * k);
+    return h4{f32_to_half((v[0].re * k) * inv), f32_to_half((v[0].im * k) * inv),
+              f32_to_half((v[1].re * k) * inv), f32_to_half((v[1].im * k) * inv)};
+  }
+  const float inv = m > 0.0f ? 1.0f / m : 0.0f;
+  return h4{f32_to_half(v[0].re * inv), f32_to_half(v[0].im * inv), f32_to_half(v[1].re * inv),
+            f32_to_half(v[1].im * inv)};
+}
+
 __device__ __forceinline__ void store_spinor(h8* __restrict__ p, long /*V*/, int s,
                                              const cx<float> (&v)[12]) {
   h8 q[3];
@@ -519,6 +532,64 @@ __device__ __forceinline__ void load_link(const BufField<h2>& f, long /*V*/, int
       u[k] = {static_cast<float>(t.x), static_cast<float>(t.y)};
     }
   }
+}
+
+// How a kernel reaches a field: a plain pointer (any size) or, with BUF, a
+// buffer resource (fields below 4 GiB; no address arithmetic per load).
+template <bool BUF, typename E>
+__device__ __forceinline__ auto field_in(const E* p, unsigned bytes) {
+  if constexpr (BUF) return buf_field(p, bytes);
+  else return p;
+}
+template <bool BUF, typename E>
+__device__ __forceinline__ auto field_out(E* p, unsigned bytes) {
+  if constexpr (BUF) return buf_field(p, bytes);
+  else return p;
+}
+
+// ------------------------------------------------- two components of a site
+//
+// Components 2j and 2j + 1 of a spinor (j = 0..5), for kernels that spread a
+// site over several lanes: two planes in FP64, one in FP32, half a plane in
+// FP16 storage (whose values are those load_spinor gives).
+
+__device__ __forceinline__ void load_pair(const double2* __restrict__ p, long V, int s, int j, cx<double> (&v)[2]) {
+  const double2 a = p[pidx(s, 2 * j, 12, V)], b = p[pidx(s, 2 * j + 1, 12, V)];
+  v[0] = {a.x, a.y};
+  v[1] = {b.x, b.y};
+}
+__device__ __forceinline__ void load_pair(const float4* __restrict__ p, long V, int s, int j, cx<float> (&v)[2]) {
+  const float4 a = p[pidx(s, j, 6, V)];
+  v[0] = {a.x, a.y};
+  v[1] = {a.z, a.w};
+}
+__device__ __forceinline__ void half_pair(h4 t, float sc, cx<float> (&v)[2]) {
+  v[0] = {fmar(static_cast<float>(t.x), sc, 0.0f), fmar(static_cast<float>(t.y), sc, 0.0f)};
+  v[1] = {fmar(static_cast<float>(t.z), sc, 0.0f), fmar(static_cast<float>(t.w), sc, 0.0f)};
+}
+__device__ __forceinline__ void load_pair(const h8* __restrict__ p, long /*V*/, int s, int j, cx<float> (&v)[2]) {
+  const float sc = reinterpret_cast<const float*>(p)[half_scale_index(s)];
+  half_pair(reinterpret_cast<const h4*>(p)[2 * half_unit(s, j >> 1) + (j & 1)], sc, v);
+}
+__device__ __forceinline__ void load_pair(const BufField<double2>& f, long /*V*/, int s, int j, cx<double> (&v)[2]) {
+  const unsigned o = site_off<12, 16>(s) + static_cast<unsigned>(j) * (2 * kPlane16);
+  const nd2 a = buf_ld2(f, o, 0), b = buf_ld2(f, o, kPlane16);
+  v[0] = {a.x, a.y};
+  v[1] = {b.x, b.y};
+}
+__device__ __forceinline__ void load_pair(const BufField<float4>& f, long /*V*/, int s, int j, cx<float> (&v)[2]) {
+  const unsigned o = site_off<6, 16>(s) + static_cast<unsigned>(j) * kPlane16;
+  const nf4 a = __builtin_bit_cast(nf4, __builtin_amdgcn_raw_buffer_load_b128(f.r, o, 0, 0));
+  v[0] = {a.x, a.y};
+  v[1] = {a.z, a.w};
+}
+__device__ __forceinline__ void load_pair(const BufField<h8>& f, long /*V*/, int s, int j, cx<float> (&v)[2]) {
+  const unsigned b = half_block_off(s);
+  const unsigned l = static_cast<unsigned>(s) % kHalfBlock;
+  const float sc = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                                 f.r, b + 3 * kHalfBlock * 16 + l * 4, 0, 0));
+  const unsigned o = b + (static_cast<unsigned>(j >> 1) * kHalfBlock + l) * 16 + (j & 1) * 8;
+  half_pair(__builtin_bit_cast(h4, __builtin_amdgcn_raw_buffer_load_b64(f.r, o, 0, 0)), sc, v);
 }
 
 }  // namespace wd

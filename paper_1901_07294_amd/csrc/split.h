@@ -1,0 +1,265 @@
+// The Wilson-Dirac operator with every site's hops spread over eight lanes.
+//
+// What bounds a small lattice is not bytes but latency: a lane that walks its
+// site's eight hops one after the other waits for memory eight times or more,
+// while most of the chip has nothing to do. Here a workgroup of four waves owns
+// 32 consecutive sites; wave mu works on direction mu, its lower 32 lanes on the
+// forward and its upper 32 on the backward hop, so all eight neighbour spinors
+// and links of a site are in flight at once and an operator costs one round of
+// memory latency. Each lane leaves its half spinor U h (or U^dag h) in LDS; then
+// six groups of 32 lanes rebuild two of the twelve spin-colour components each,
+// adding the hops in the order of the t-marching kernel (or, where that kernel
+// does not apply, in the order x, y, z, t), so that both kernels give the same
+// bits and the choice between them is one of speed alone.
+//
+// 32 sites rather than 64 per workgroup: 8^4 has 128 workgroups of them, and a
+// CU's L1 has to pass 21 16-byte elements per hop, 86 KB for 32 FP64 sites.
+//
+// Measured on MI355X (one lane per site or a march of four slices -> this
+// kernel): 8^4 FP32 in a solve 17.1 -> 5.7 us per launch (6.0 -> 2.8 ms per
+// solve), 15 x 9 x 14 x 21 FP32 24.2 -> 7.6 us, 6 x 6 x 40 x 72 FP64 35.9 -> 19.2
+// us, with four fields 174 -> 62 us. On larger lattices every neighbour spinor
+// comes through L1, and the marches win (24^4 FP16 24 against 31 us).
+#pragma once
+
+#include "cg_site.h"
+#include "stencil.h"
+#include "wd_internal.h"
+
+namespace wd {
+
+constexpr int kSplitSites = 32;     // sites per workgroup
+constexpr int kSplitThreads = 256;  // (direction, sign, site)
+
+struct SplitParams {
+  int ntiles;  // runs of kSplitSites sites
+  int per;     // tiles per XCD (the last XCD may get fewer)
+  int nrhs;
+  int ny;      // y rows per tile of the t-marching kernel, 0 where it does not apply
+  unsigned link_bytes;    // as MarchParams
+  unsigned spinor_bytes;
+};
+
+// h = psi_u + sg * A_mu psi_l with sg = -1 (forward hop) or +1 (backward): the
+// additions of project<>, spelled as multiply-adds by +-1 (the same values).
+template <int MU, typename R>
+__device__ __forceinline__ void project_sg(const cx<R> (&p)[12], R sg, cx<R> (&h)[6]) {
+  auto add = [&](cx<R> a, cx<R> b, R s) { return cx<R>{fmar(s, b.re, a.re), fmar(s, b.im, a.im)}; };
+  auto addi_s = [&](cx<R> a, cx<R> b, R s) { return cx<R>{fmar(-s, b.im, a.re), fmar(s, b.re, a.im)}; };
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    const cx<R> p0 = p[a], p1 = p[3 + a], p2 = p[6 + a], p3 = p[9 + a];
+    if constexpr (MU == 0) {
+      h[a] = addi_s(p0, p3, sg);
+      h[3 + a] = addi_s(p1, p2, sg);
+    } else if constexpr (MU == 1) {
+      h[a] = add(p0, p3, -sg);
+      h[3 + a] = add(p1, p2, sg);
+    } else if constexpr (MU == 2) {
+      h[a] = addi_s(p0, p2, sg);
+      h[3 + a] = addi_s(p1, p3, -sg);
+    } else {
+      h[a] = add(p0, p2, sg);
+      h[3 + a] = add(p1, p3, sg);
+    }
+  }
+}
+
+// u, or its conjugate transpose where dag.
+template <typename R>
+__device__ __forceinline__ void select_dagger(cx<R> (&u)[9], bool dag) {
+  const R s = dag ? R(-1) : R(1);
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    u[4 * a].im *= s;
+#pragma unroll
+    for (int b = a + 1; b < 3; ++b) {
+      const cx<R> x = u[3 * a + b], y = u[3 * b + a];
+      u[3 * a + b] = {dag ? y.re : x.re, s * (dag ? y.im : x.im)};
+      u[3 * b + a] = {dag ? x.re : y.re, s * (dag ? x.im : y.im)};
+    }
+  }
+}
+
+// Hops of all sites of a workgroup, as left in LDS: [hop][half-spinor component][site].
+template <typename R>
+struct SplitHops {
+  cx<R> g[8][6][kSplitSites];
+};
+
+// acc += the contribution of hop H (2 mu + backward) to component c = 2j or
+// 2j + 1 of a spinor: lower says c >= 6, half which of the two half-spinor
+// rows it belongs to, col its colour. The additions are reconstruct_add's.
+template <int H, typename R>
+__device__ __forceinline__ void add_hop(const SplitHops<R>& l, int site, bool lower, int half, int col,
+                                        cx<R>& acc) {
+  constexpr int mu = H / 2;
+  constexpr R S = (H & 1) ? R(1) : R(-1);
+  const int row = (mu < 2 && lower) ? 1 - half : half;
+  const cx<R> g = l.g[H][3 * row + col][site];
+  if constexpr (mu == 0 || mu == 2) {  // lower: S * (-i g), for mu = 2 with the sign flipped in row 1
+    const R s = (mu == 2 && half == 1) ? -S : S;
+    const R x = lower ? g.im : g.re, y = lower ? g.re : g.im;
+    acc.re = fmar(lower ? s : R(1), x, acc.re);
+    acc.im = fmar(lower ? -s : R(1), y, acc.im);
+  } else {  // lower: S * g, for mu = 1 with the sign flipped in row 1
+    const R s = !lower ? R(1) : (mu == 1 && half == 1) ? -S : S;
+    acc.re = fmar(s, g.re, acc.re);
+    acc.im = fmar(s, g.im, acc.im);
+  }
+}
+
+template <typename T, bool C12, int CGM, bool BUF>
+__global__ __launch_bounds__(kSplitThreads) void dslash_split_kernel(
+    const typename Packed<T>::S* __restrict__ in_all, typename Packed<T>::S* __restrict__ out_all,
+    const typename Packed<T>::L* __restrict__ links, Geo geo, Diag<typename Packed<T>::R> diags,
+    long stride, int gamma5, SplitParams p, CgFuse cgf) {
+  using R = typename Packed<T>::R;
+  using GS = typename Packed<T>::S;
+  __shared__ SplitHops<R> hops;
+  __shared__ double red[CGM == kCgNone ? 1 : 6][kSplitSites];
+  __shared__ float mx[sizeof(T) == 2 ? 6 : 1][kSplitSites];
+  __shared__ double aw[kSplitThreads / 64];
+
+  // every XCD gets one contiguous run of tiles (their halos meet in one L2),
+  // the right-hand sides of a tile follow each other
+  const int xcd = blockIdx.x % kNumXcd, l = blockIdx.x / kNumXcd;
+  const int tile = xcd * p.per + l / p.nrhs;
+  if (tile >= p.ntiles) return;
+  const int rhs = l % p.nrhs;
+  const long k = diags.idx[rhs];
+  const auto in = field_in<BUF>(in_all + k * stride, p.spinor_bytes);
+  const auto lk = field_in<BUF>(links, p.link_bytes);
+
+  const int lane = threadIdx.x & 63;
+  const int mu = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+  const int site = lane & (kSplitSites - 1);
+  const int up = lane / kSplitSites;  // 0: forward hop, 1: backward hop
+  const int s0 = tile * kSplitSites + site;
+  const bool valid = s0 < geo.V;
+  const int s = valid ? s0 : geo.V - 1;
+  const long V = geo.V;
+
+  // the neighbour in direction mu (periodic; extent 1 wraps onto the site itself)
+  const int ext = mu == 0 ? geo.X : mu == 1 ? geo.Y : mu == 2 ? geo.Z : geo.T;
+  const int st = mu == 0 ? 1 : mu == 1 ? geo.X : mu == 2 ? geo.XY : geo.XYZ;
+  const int c = static_cast<int>((static_cast<unsigned>(s) / static_cast<unsigned>(st)) % static_cast<unsigned>(ext));
+  const int nb = up == 0 ? (c + 1 == ext ? s - (ext - 1) * st : s + st)
+                         : (c == 0 ? s + (ext - 1) * st : s - st);
+
+  cx<R> u[9], psi[12];
+  load_link<C12>(lk, V, mu, up == 0 ? s : nb, u);
+  load_spinor(in, V, nb, psi);
+
+  // what the second half needs: the site's own components 2j, 2j + 1
+  const int j = 2 * mu + up;
+  const bool mine = j < 6;
+  cx<R> own[2], rv[2];
+  if (mine) load_pair(in, V, s, j, own);
+  GS* const r = CGM == kCgUpdate ? static_cast<GS*>(cgf.r) + k * stride : nullptr;
+  double* const sc = CGM == kCgUpdate ? cgf.scal + k * kScalars : nullptr;
+  if constexpr (CGM == kCgUpdate) {
+    if (mine) load_pair(r, V, s, j, rv);
+    const double t = wave_total(strided_sum256(cgf.pap + k * cgf.npap, cgf.npap, threadIdx.x));
+    if (lane == 0) aw[mu] = t;
+  }
+  bool y_fwd_out = false, y_bwd_out = false;
+  if (p.ny != 0 && p.ny != geo.Y) {
+    const unsigned y = (static_cast<unsigned>(s) / static_cast<unsigned>(geo.X)) % static_cast<unsigned>(geo.Y);
+    const int yl = static_cast<int>(y % static_cast<unsigned>(p.ny));
+    y_fwd_out = yl + 1 == p.ny;
+    y_bwd_out = yl == 0;
+  }
+
+  {
+    const R sg = up == 0 ? R(-1) : R(1);
+    cx<R> h[6], g[6];
+    if (mu == 0) project_sg<0>(psi, sg, h);
+    else if (mu == 1) project_sg<1>(psi, sg, h);
+    else if (mu == 2) project_sg<2>(psi, sg, h);
+    else project_sg<3>(psi, sg, h);
+    select_dagger(u, up != 0);
+    su3_mul<false>(u, h, g);
+#pragma unroll
+    for (int a = 0; a < 6; ++a) hops.g[j][a][site] = g[a];
+  }
+  __syncthreads();
+
+  cx<R> o[2];
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    const int cc = mine ? 2 * j + e : 0;
+    const bool lower = cc >= 6;
+    const int c6 = lower ? cc - 6 : cc;
+    const int half = c6 >= 3 ? 1 : 0;
+    const int col = c6 - 3 * half;
+    cx<R> acc = {R(0), R(0)};
+    if (p.ny != 0) {
+      add_hop<4>(hops, site, lower, half, col, acc);
+      add_hop<5>(hops, site, lower, half, col, acc);
+      if (y_fwd_out) add_hop<2>(hops, site, lower, half, col, acc);
+      if (y_bwd_out) add_hop<3>(hops, site, lower, half, col, acc);
+      add_hop<7>(hops, site, lower, half, col, acc);
+      add_hop<6>(hops, site, lower, half, col, acc);
+      add_hop<0>(hops, site, lower, half, col, acc);
+      add_hop<1>(hops, site, lower, half, col, acc);
+      if (!y_fwd_out) add_hop<2>(hops, site, lower, half, col, acc);
+      if (!y_bwd_out) add_hop<3>(hops, site, lower, half, col, acc);
+    } else {
+      add_hop<0>(hops, site, lower, half, col, acc);
+      add_hop<1>(hops, site, lower, half, col, acc);
+      add_hop<2>(hops, site, lower, half, col, acc);
+      add_hop<3>(hops, site, lower, half, col, acc);
+      add_hop<4>(hops, site, lower, half, col, acc);
+      add_hop<5>(hops, site, lower, half, col, acc);
+      add_hop<6>(hops, site, lower, half, col, acc);
+      add_hop<7>(hops, site, lower, half, col, acc);
+    }
+    const R diag = diags.d[rhs], mhalf = R(-0.5);
+    o[e] = {fmar(diag, own[e].re, mhalf * acc.re), fmar(diag, own[e].im, mhalf * acc.im)};
+    if (gamma5 && lower) o[e] = -o[e];
+  }
+
+  if constexpr (CGM == kCgUpdate) {  // r -= alpha A p, alpha as every workgroup finds it
+    double t = 0.0;
+    for (int w = 0; w < kSplitThreads / 64; ++w) t += aw[w];
+    bool flag = false;
+    const double alpha = cg_alpha(t, sc[kRr], &flag);
+    if (threadIdx.x == 0 && tile == 0) {
+      sc[kPap] = t;
+      sc[kAlpha] = alpha;
+      sc[kRrPrev] = sc[kRr];
+      if (flag) sc[kFlag] = 1.0;
+    }
+    const R a = static_cast<R>(alpha);
+#pragma unroll
+    for (int e = 0; e < 2; ++e) o[e] = {fmar(-a, o[e].re, rv[e].re), fmar(-a, o[e].im, rv[e].im)};
+  }
+
+  // store, and with a CG mode the squared norm of the pair as stored
+  GS* const dst = CGM == kCgUpdate ? r : out_all + k * stride;
+  double n2 = 0.0;
+  if constexpr (sizeof(T) == 2) {
+    if (mine) mx[j][site] = fmaxf(fmaxf(fabsf(o[0].re), fabsf(o[0].im)), fmaxf(fabsf(o[1].re), fabsf(o[1].im)));
+    __syncthreads();
+    float m = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 6; ++i) m = fmaxf(m, mx[i][site]);
+    if (mine && valid) n2 = store_pair(dst, s, j, o, m);
+  } else {
+    if (mine && valid) n2 = store_pair(dst, V, s, j, o);
+  }
+  if constexpr (CGM != kCgNone) {
+    if (mine) red[j][site] = n2;
+    __syncthreads();
+    if (threadIdx.x < kSplitSites) {
+      double v = red[0][site];
+#pragma unroll
+      for (int i = 1; i < 6; ++i) v += red[i][site];
+      v = half_wave_total(v);
+      if (site == 0) cgf.rr[k * cgf.nslices + tile] = v;
+    }
+  }
+}
+
+}  // namespace wd

@@ -112,12 +112,13 @@ hipError_t launch_dslash_multi(const wd_gauge* g, const double* masses, int nrhs
 // Launch choices of the t-marching kernel that leave every site's arithmetic,
 // and so every result bit, unchanged: t steps per workgroup, lane groups per
 // workgroup, the run length of tiles per XCD (0: hardware order) and
-// right-hand sides per lane (1 or 2).
+// right-hand sides per lane (1 or 2). tb = 0 (with gw = rb = 1, group = 0) is
+// the split kernel, where it is the default.
 struct MarchTuning {
   int32_t tb, gw, group, rb;
 };
 // The default choice for a lattice, precision and nrhs; false when the
-// t-marching kernel does not apply (the one-site-per-lane kernel runs).
+// t-marching kernel does not apply (the split kernel runs).
 bool march_default(const int32_t dims[4], int prec, int nrhs, MarchTuning* t);
 // Alternatives to the default (the default included), all valid.
 void march_candidates(const int32_t dims[4], int prec, int nrhs, MarchTuning* out, int* n, int cap);
@@ -130,27 +131,31 @@ hipError_t launch_dslash_tuned(const wd_gauge* g, const double* masses, int nrhs
 bool tuned_lookup(const int32_t dims[4], int prec, int c12, int nrhs, MarchTuning* t);
 
 // Work of a CG iteration fused into its two applications of Q, as a mode of
-// the t-marching kernel. kCgNorm (first application, t = Q p): t is stored
-// and each tile slice (a tile's x rows at one z and t, so the grouping is
-// fixed by the lattice, not the launch) leaves its |t|^2 = <p, A p> partial
-// sum in rr. kCgUpdate (second application, A p = Q t): A p is used at once
+// the dslash kernels. kCgNorm (first application, t = Q p): t is stored
+// and each slice leaves its |t|^2 = <p, A p> partial sum in rr. kCgUpdate
+// (second application, A p = Q t): A p is used at once
 // for r -= alpha A p (alpha = <r,r> / <p,Ap> reduced from pap) instead of
-// being stored, and each tile slice leaves its <r,r>; x += alpha p is left
+// being stored, and each slice leaves its <r,r>; x += alpha p is left
 // to the p update, which reads p anyway.
+// A slice is 32 consecutive sites on small lattices (the split kernel's
+// workgroup), else a tile's x rows at one z and t: fixed by the lattice, not by
+// the launch.
 enum : int { kCgNone = 0, kCgNorm = 1, kCgUpdate = 2 };
 struct CgFuse {
   int mode;           // kCgNorm or kCgUpdate
   void* r;            // residual, inner precision
   const double* pap;  // <p, A p> partial sums, npap per field slot
   int npap;
-  double* rr;         // out: |t|^2 or <r, r> per tile slice, nslices per field slot
+  double* rr;         // out: |t|^2 or <r, r> per slice, nslices per field slot
   int nslices;
   double* scal;       // per field slot scalars (kScalars doubles)
 };
-// Tile slices of the fused work on a lattice in a precision, or 0 where it
-// does not apply (the one-site-per-lane kernel, or tiles that are not whole
-// waves). kCgUpdate exists for FP32 arithmetic (FP32 and FP16 storage) only.
+// Slices of the fused work on a lattice in a precision, or 0 where it does
+// not apply (larger lattices without t-marching tiles of whole waves).
 int cg_fuse_slices(const int32_t dims[4], int prec);
+// Whether kCgUpdate exists there: with FP32 arithmetic (FP32 and FP16
+// storage) wherever kCgNorm does, in FP64 up to 131072 sites.
+bool cg_fuse_update(const int32_t dims[4], int prec);
 // Q = gamma5 D(masses[i]) on field fields[i] of `in` (into `out` for
 // kCgNorm), fused with the work of f.mode for the same field slots
 // (cg_fuse_slices must be > 0).

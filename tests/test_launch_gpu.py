@@ -6,6 +6,7 @@ import pytest
 import torch
 
 import lattice_inputs as li
+import lattice_inputs.device as dev
 import oracle
 import paper_1901_07294_amd.wilson as w
 from paper_1901_07294_amd.buffers import DeviceGauge
@@ -72,3 +73,83 @@ def test_launch_choices_keep_bits(dims, prec, c12, nrhs, tmp_path):
     got = got if nrhs > 1 else got[None]
     ref = oracle.gamma5_apply(oracle.dslash(U, psis[-1], masses[-1]))
     assert rel(got[-1], ref) <= TOL[PRECS[prec]]
+
+
+@pytest.mark.parametrize("prec,c12", [("fp64", False), ("fp64", True), ("fp32", False), ("fp32", True),
+                                      ("fp16", False), ("fp16", True)])
+@pytest.mark.parametrize("dims", [
+    (16, 8, 5, 3),    # 1920 sites: whole runs of 32, tiles of whole waves
+    (13, 5, 3, 7),    # 1365 sites: the last run holds 21
+    (21, 9, 2, 31),   # three y rows per tile of the march: hops leave the tile
+    (1, 64, 1, 3),    # extent-1 directions wrap onto the site itself
+    (31, 1, 1, 1),    # fewer sites than one run, no t-marching tiles
+    (300, 2, 3, 1),   # x rows longer than a t-marching workgroup
+], ids=lambda d: "x".join(map(str, d)))
+def test_split_kernel_sites(dims, prec, c12, tmp_path):
+    """Small lattices run eight lanes per site: every site against the oracle,
+    two fields with their own masses, and the bits of the t-marching kernel
+    where that one applies."""
+    print(f"case split dims={dims} prec={prec} c12={c12}", flush=True)
+    U = li.random_gauge(dims, 81)
+    psis = li.gaussian_spinors(dims, [82, 83])
+    masses = [0.05, -0.2]
+    g = DeviceGauge(U, PRECS[prec], c12)
+    src = g.pack(psis, nrhs=2)
+    out = apply_with(None, tmp_path, g, masses, src)
+    got = g.unpack(out, nrhs=2)
+    for k in range(2):
+        assert rel(got[k], oracle.gamma5_apply(oracle.dslash(U, psis[k], masses[k]))) <= TOL[PRECS[prec]]
+    if dims[0] <= 256 and dims[0] * dims[1] >= 64:
+        assert torch.equal(out, apply_with("1 1 0 1", tmp_path, g, masses, src))
+
+
+def test_split_kernel_links_beyond_4_gib():
+    """Rows of 300 sites (no t-marching tiles) with FP64 links of 4.42 GB, more
+    than buffer offsets reach: plain pointers. Sampled sites against the oracle,
+    the last ones among them."""
+    dims = (300, 128, 100, 2)
+    assert w.wd_gauge_bytes(dims, w.WD_FP64, 0) > 1 << 32
+    print(f"case split dims={dims}: links beyond 4 GiB", flush=True)
+    U, psi = dev.random_gauge(dims, 91), dev.gaussian_spinor(dims, 92)
+    g = DeviceGauge(U, w.WD_FP64)
+    dst = g.spinor()
+    w.dslash_apply(g.handle, 0.1, g.pack(psi), dst, w.WD_FP64)
+    out = g.unpack(dst).reshape(-1, 4, 3)
+    V = li.volume(dims)
+    sites = np.concatenate([np.random.default_rng(93).choice(V, 500, replace=False), V - 1 - np.arange(64)])
+    ref = oracle.dslash_sites(U.cpu().numpy(), psi.cpu().numpy(), 0.1, sites)
+    assert rel(out[sites], ref) <= TOL[w.WD_FP64]
+
+
+@pytest.mark.parametrize("inner", ["fp64", "fp32", "fp16"])
+@pytest.mark.parametrize("dims", [
+    (8, 8, 8, 4),    # split kernel, slices of 32 sites
+    (9, 5, 7, 5),    # split kernel, a last slice of 7 sites
+    (16, 16, 9, 8),  # t-marching tiles, tile slices, the update fused in FP64 too
+], ids=lambda d: "x".join(map(str, d)))
+def test_cg_fused_kernels(dims, inner):
+    """Solves in each of the fused kernels: the oracle's true residual, and the
+    same bits alone as beside another right-hand side."""
+    print(f"case fused cg dims={dims} inner={inner}", flush=True)
+    U = li.near_unity_gauge(dims, 85, 0.3)
+    bs = li.gaussian_spinors(dims, [86, 87])
+    masses = [0.1, 0.4]
+    prec = PRECS[inner]
+    ghi = DeviceGauge(U, w.WD_FP64)
+    glo = DeviceGauge(U, prec)
+
+    def solve(b, m):
+        n = len(m)
+        x = ghi.spinor(n)
+        ws = torch.empty(w.cg_workspace_bytes(dims, n, prec), dtype=torch.uint8, device="cuda")
+        rc, stats = w.cg_solve_normal(ghi.handle, glo.handle, m, n, ghi.pack(b, nrhs=n), x,
+                                      dict(tol=1e-10, max_iter=2000, inner=prec, delta=0.1, check_every=5,
+                                           x0_given=0, use_graph=0), ws)
+        assert rc == w.WD_OK, stats
+        return ghi.unpack(x, nrhs=n).reshape(n, *b.shape[1:])
+
+    both = solve(bs, masses)
+    for k in range(2):
+        assert np.array_equal(both[k], solve(bs[k:k + 1], masses[k:k + 1])[0])
+        r = bs[k] - oracle.normal_op(U, masses[k], both[k])
+        assert np.linalg.norm(r) <= 1e-10 * np.linalg.norm(bs[k])

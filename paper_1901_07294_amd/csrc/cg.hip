@@ -46,8 +46,8 @@ size_t align256(size_t b) { return (b + 255) & ~static_cast<size_t>(255); }
 CgLayout cg_layout(const int32_t dims[4], int slots, int inner, bool eo) {
   CgLayout w;
   const long V = static_cast<long>(dims[0]) * dims[1] * dims[2] * dims[3] / (eo ? 2 : 1);
-  w.nslices = eo ? 0 : cg_fuse_slices(dims, inner);
-  w.fuse_update = !eo && cg_fuse_update(dims, inner);
+  w.nslices = eo ? eo_fuse_slices(dims, inner) : cg_fuse_slices(dims, inner);
+  w.fuse_update = eo ? w.nslices > 0 : cg_fuse_update(dims, inner);
   const size_t hi = align256(static_cast<size_t>(packed_sites(V)) * slots * spinor_site_bytes(WD_FP64));
   const size_t lo = align256(static_cast<size_t>(packed_sites(V)) * slots * spinor_site_bytes(inner));
   const size_t acc = align256(static_cast<size_t>(packed_sites(V)) * slots * spinor_site_bytes(WD_FP32));
@@ -128,8 +128,15 @@ CgEngine::CgEngine(const wd_gauge* ghi, const wd_gauge* glo, int inner, int slot
 
 int CgEngine::apply_q(const wd_gauge* g, const double* m, const RhsSet& set, const void* in, void* tmp,
                       void* out, const char* what) const {
-  return launch_status(eo_ ? launch_schur_q(g, m, set, in, tmp, out, st_)
+  return launch_status(eo_ ? launch_schur_q(g, m, set, in, tmp, out, nullptr, st_)
                            : launch_dslash_multi(g, m, set.n, set.idx, in, out, WD_FLAG_GAMMA5, st_),
+                       what);
+}
+
+int CgEngine::apply_q_cg(const double* m, const RhsSet& set, const void* in, void* out, const CgFuse& f,
+                         const char* what) const {
+  return launch_status(eo_ ? launch_schur_q(glo_, m, set, in, at(ws_, lay_.e_lo), out, &f, st_)
+                           : launch_dslash_cg(glo_, m, set.n, set.idx, in, out, f, st_),
                        what);
 }
 
@@ -172,8 +179,7 @@ int CgEngine::iterate(const RhsSet& set, int j, int n) {
     f.mode = kCgNorm;
     f.rr = paps_;
     f.nslices = lay_.nslices;
-    int rc = launch_status(launch_dslash_cg(glo_, m, set.n, set.idx, at(ws_, lay_.p), at(ws_, lay_.t), f,
-                                            st_), "cg: Q p with |Q p|^2");
+    int rc = apply_q_cg(m, set, at(ws_, lay_.p), at(ws_, lay_.t), f, "cg: Q p with |Q p|^2");
     f.mode = kCgUpdate;
     f.r = at(ws_, lay_.r);
     f.pap = paps_;
@@ -181,8 +187,7 @@ int CgEngine::iterate(const RhsSet& set, int j, int n) {
     f.rr = rr_;
     f.scal = scal_;
     if (rc == WD_OK)
-      rc = launch_status(launch_dslash_cg(glo_, m, set.n, set.idx, at(ws_, lay_.t), nullptr, f, st_),
-                         "cg: Q Q p with r");
+      rc = apply_q_cg(m, set, at(ws_, lay_.t), nullptr, f, "cg: Q Q p with r");
     if (rc == WD_OK)
       rc = launch_status(blas_update_xp(x_, at(ws_, lay_.p), at(ws_, lay_.r), nlo_, set, rr_, lay_.nslices,
                                         scal_, st_), "cg: x, p");
@@ -196,8 +201,7 @@ int CgEngine::iterate(const RhsSet& set, int j, int n) {
     f.mode = kCgNorm;
     f.rr = paps_;
     f.nslices = lay_.nslices;
-    int rc = launch_status(launch_dslash_cg(glo_, m, set.n, set.idx, at(ws_, lay_.p), at(ws_, lay_.t), f,
-                                            st_), "cg: Q p with |Q p|^2");
+    int rc = apply_q_cg(m, set, at(ws_, lay_.p), at(ws_, lay_.t), f, "cg: Q p with |Q p|^2");
     if (rc == WD_OK)
       rc = launch_status(launch_dslash_multi(glo_, m, set.n, set.idx, at(ws_, lay_.t), at(ws_, lay_.ap),
                                              WD_FLAG_GAMMA5, st_), "cg: Q Q p");
@@ -227,8 +231,7 @@ int CgEngine::iterate(const RhsSet& set, int j, int n) {
     f.mode = kCgNorm;
     f.rr = paps_;
     f.nslices = lay_.nslices;
-    int rc = launch_status(launch_dslash_cg(glo_, m, set.n, set.idx, pc, at(ws_, lay_.t), f, st_),
-                           "cg: Q p with |Q p|^2");
+    int rc = apply_q_cg(m, set, pc, at(ws_, lay_.t), f, "cg: Q p with |Q p|^2");
     f.mode = kCgUpdate;
     f.r = at(ws_, lay_.r);
     f.pap = paps_;
@@ -236,8 +239,7 @@ int CgEngine::iterate(const RhsSet& set, int j, int n) {
     f.rr = rr_;
     f.scal = scal_;
     if (rc == WD_OK)
-      rc = launch_status(launch_dslash_cg(glo_, m, set.n, set.idx, at(ws_, lay_.t), nullptr, f, st_),
-                         "cg: Q Q p with r");
+      rc = apply_q_cg(m, set, at(ws_, lay_.t), nullptr, f, "cg: Q Q p with r");
     if (rc == WD_OK)
       rc = launch_status(blas_update_xp_lo(at(ws_, lay_.x_lo), kind == kXpDefer ? p2 : p1, pc, p1,
                                            at(ws_, lay_.r), kind, inner_, nlo_, n32_, V_, set, rr_,

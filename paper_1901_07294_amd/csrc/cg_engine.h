@@ -74,6 +74,9 @@ class CgEngine {
   // out = Q in (Q = gamma5 D, or gamma5 S through the even fields tmp)
   int apply_q(const wd_gauge* g, const double* m, const RhsSet& set, const void* in, void* tmp, void* out,
               const char* what) const;
+  // Q in with the fused work f (kCgNorm: into out), inner precision
+  int apply_q_cg(const double* m, const RhsSet& set, const void* in, void* out, const CgFuse& f,
+                 const char* what) const;
   bool eo_ = false;
   const wd_gauge* ghi_;
   const wd_gauge* glo_;

@@ -575,23 +575,19 @@ template <typename T, bool C12, int CGM>
 hipError_t launch_split(const void* in, void* out, const void* links, const Geo& geo,
                         const Diag<typename Packed<T>::R>& diag, long stride, int g5, const MarchParams& m,
                         const CgFuse& f, hipStream_t st) {
-  using SV = typename Packed<T>::S;
-  using LV = typename Packed<T>::L;
-  SplitParams p{};
-  p.ntiles = (geo.V + kSplitSites - 1) / kSplitSites;
-  p.per = (p.ntiles + kNumXcd - 1) / kNumXcd;
+  using R = typename Packed<T>::R;
+  SplitParams p{geo.X, geo.Y, geo.Z, geo.T, geo.X, geo.XY, geo.XYZ, geo.V};
   p.nrhs = m.nrhs;
   p.ny = m.ny;
   p.link_bytes = m.link_bytes;
   p.spinor_bytes = m.spinor_bytes;
-  const unsigned nb = static_cast<unsigned>(p.per) * kNumXcd * static_cast<unsigned>(m.nrhs);
-  const auto run = [&](auto kernel) {
-    kernel<<<nb, kSplitThreads, 0, st>>>(static_cast<const SV*>(in), static_cast<SV*>(out),
-                                         static_cast<const LV*>(links), geo, diag, stride, g5, p, f);
-    return hipGetLastError();
-  };
-  if (kMarchBuf && m.link_bytes != 0 && m.spinor_bytes != 0) return run(&dslash_split_kernel<T, C12, CGM, true>);
-  return run(&dslash_split_kernel<T, C12, CGM, false>);
+  SplitCoef<R> cf{};
+  for (int k = 0; k < m.nrhs; ++k) {
+    cf.d[k] = diag.d[k];
+    cf.c[k] = R(-0.5);
+    cf.idx[k] = diag.idx[k];
+  }
+  return launch_split_hop<T, C12, CGM>(in, in, out, links, links, cf, stride, g5, p, f, st);
 }
 
 // Whether the split kernel is the default for nrhs fields: where the t-marching

@@ -32,9 +32,13 @@ hipError_t launch_eo_hop(const wd_gauge* g, int parity, const void* in, const vo
 
 // out = gamma5 S in on the odd half fields of set (masses[i] for set.idx[i]),
 // through the even half fields tmp: tmp = -H_eo in / 2, then
-// out = gamma5 [(4+m) in + H_oe tmp / (2(4+m))].
+// out = gamma5 [(4+m) in + H_oe tmp / (2(4+m))]. f: null, or the CG work fused
+// into the second hop (as launch_dslash_cg; out is not written for kCgUpdate).
 hipError_t launch_schur_q(const wd_gauge* g, const double* masses, const RhsSet& set, const void* in,
-                          void* tmp, void* out, hipStream_t s);
+                          void* tmp, void* out, const CgFuse* f, hipStream_t s);
+// Slices of that work (32 consecutive half sites, or 256 on large lattices), or
+// 0 where it does not apply (FP64 on large lattices).
+int eo_fuse_slices(const int32_t dims[4], int prec);
 
 // dst = gamma5 src for FP64 packed fields of V sites (n 16-byte elements each).
 hipError_t blas_gamma5(void* dst, const void* src, long n, const RhsSet& set, hipStream_t st);

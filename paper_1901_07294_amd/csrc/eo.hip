@@ -1,7 +1,7 @@
 // Hops between the two parities of an even-odd split lattice, for the Schur
 // complement of the odd sites (eo.h), and gamma5 on FP64 fields.
 //
-// One lane per output half site. The eight neighbours of an output site all
+// The eight neighbours of an output site all
 // have the other parity: the x neighbours sit in the same half row at x
 // half-index xh or xh +/- 1 (which one depends on the row's parity offset),
 // the y, z and t neighbours at the same half index in the neighbouring half
@@ -9,8 +9,10 @@
 // site's own link (this parity's links), the backward hop the link of the
 // neighbour it comes from (the other parity's links, at the neighbour's index).
 // Over both parities every link is read once per application of H_{p,1-p},
-// as in the full operator.
+// as in the full operator. HBM-bound on large lattices (8 links against 2 or 3
+// spinors per output site), latency-bound on small ones.
 #include "eo.h"
+#include "split.h"
 #include "stencil.h"
 
 namespace wd {
@@ -18,87 +20,133 @@ namespace {
 
 constexpr int kEoBlock = 256;
 
-// Workgroup -> run of kEoBlock half sites: consecutive workgroups go to the 8
-// XCDs in turn; when the grid divides evenly, every XCD gets one contiguous
-// eighth of the field instead, so that the t and z neighbours a workgroup
-// reads were loaded into the same L2 by workgroups of its own XCD.
-__device__ __forceinline__ int eo_tile(int contiguous) {
-  const int b = blockIdx.x;
-  if (!contiguous) return b;
-  const int per = gridDim.x / kNumXcd;
-  return (b % kNumXcd) * per + b / kNumXcd;
+// Whether a launch takes the split kernel (eight lanes per output site) rather
+// than one lane per site. In FP64 a lane that walks its hops keeps too few bytes
+// in flight (one application of the Schur operator, one lane per site against
+// split: 24^4 110 / 97 us, 24^3 x 48 235 / 201, 32^3 x 64 756 / 675, with two
+// fields on 24^4 179 / 146); with FP32 arithmetic only while the launch is small
+// (FP32: 16^4 16.4 / 14.0, with four fields 27.3 / 31.5; FP16: 12^4 13.9 / 12.1,
+// 16^4 with two fields 14.8 / 17.3, 24^4 27.7 / 33.1). Same bits either way.
+bool use_split_eo(int prec, long Vh, int nrhs) { return prec == WD_FP64 || Vh * nrhs <= 48000; }
+
+// One hop: neighbour spinor at half site n of the input, link of direction MU
+// at half site ls.
+template <int MU, int S, bool C12, typename SA, typename LA, typename R>
+__device__ __forceinline__ void eo_hop(const SA& in, const LA& links, long V, int n, int ls, cx<R> (&acc)[12]) {
+  cx<R> u[9], psi[12], h[6], g[6];
+  load_link<C12>(links, V, MU, ls, u);
+  load_spinor(in, V, n, psi);
+  project<MU, S>(psi, h);
+  su3_mul<(S > 0)>(u, h, g);
+  reconstruct_add<MU, S>(g, acc);
 }
 
-template <typename R>
-struct EoCoef {
-  R d[kMaxRhs];
-  R c[kMaxRhs];
-  int idx[kMaxRhs];
-};
-
-template <typename T, bool C12>
+// One lane per output half site. Workgroups of 256 half sites; the links and the
+// input through buffer resources where they fit. Against plain pointers and a
+// grid row per right-hand side (us per application of the Schur operator): FP16
+// 24^4 36.3 -> 27.7, with four fields 97.6 -> 69.1; FP32 24^3 x 48 104 -> 98, with
+// two fields 202 -> 164.
+template <typename T, bool C12, int CGM, bool BUF>
 __global__ __launch_bounds__(kEoBlock) void eo_hop_kernel(
     const typename Packed<T>::S* __restrict__ in_all, const typename Packed<T>::S* __restrict__ w_all,
     typename Packed<T>::S* __restrict__ out_all, const typename Packed<T>::L* __restrict__ lp,
-    const typename Packed<T>::L* __restrict__ lq, EoGeo g, int p, EoCoef<typename Packed<T>::R> cf,
-    long stride, int g5, int contiguous) {
+    const typename Packed<T>::L* __restrict__ lq, SplitCoef<typename Packed<T>::R> cf, long stride, int gamma5,
+    SplitParams p, CgFuse cgf) {
   using R = typename Packed<T>::R;
-  const long hl = static_cast<long>(eo_tile(contiguous)) * kEoBlock + threadIdx.x;
-  if (hl >= g.Vh) return;
-  const int h = static_cast<int>(hl);
-  const long Vh = g.Vh;
-  const int slot = blockIdx.y;
-  const long k = cf.idx[slot];
-  const typename Packed<T>::S* in = in_all + k * stride;
-  typename Packed<T>::S* out = out_all + k * stride;
+  using GS = typename Packed<T>::S;
+  __shared__ double aw[kEoBlock / 64];
+  int rhs;
+  const int tile = split_tile(p, &rhs);
+  if (tile >= p.ntiles) return;
+  const long k = cf.idx[rhs];
+  const int h0 = tile * kEoBlock + static_cast<int>(threadIdx.x);
+  const bool valid = h0 < p.V;
+  const int h = valid ? h0 : p.V - 1;
+  const long V = p.V;
+  const auto in = field_in<BUF>(in_all + k * stride, p.spinor_bytes);
+  const auto fp = field_in<BUF>(lp, p.link_bytes);
+  const auto fq = field_in<BUF>(lq, p.link_bytes);
 
-  const int xh = h % g.Xh;
-  const int r = h / g.Xh;
-  const int y = r % g.Y;
-  const int z = (r / g.Y) % g.Z;
-  const int t = r / (g.Y * g.Z);
-  const int o = (y + z + t + p) & 1;  // this row's x offset: x = 2 xh + o
-  const int row = h - xh;
-  // x + 1 is 2 xh + o + 1: half index xh when o = 0, xh + 1 (wrapping) when o = 1;
-  // x - 1 is 2 xh + o - 1: xh - 1 (wrapping) when o = 0, xh when o = 1
-  const int xp = row + (o ? (xh + 1 == g.Xh ? 0 : xh + 1) : xh);
-  const int xm = row + (o ? xh : (xh == 0 ? g.Xh - 1 : xh - 1));
-  const int sy = g.Xh, sz = g.Xh * g.Y, st = sz * g.Z;
-  const int yp = y + 1 == g.Y ? h - (g.Y - 1) * sy : h + sy;
-  const int ym = y == 0 ? h + (g.Y - 1) * sy : h - sy;
-  const int zp = z + 1 == g.Z ? h - (g.Z - 1) * sz : h + sz;
-  const int zm = z == 0 ? h + (g.Z - 1) * sz : h - sz;
-  const int tp = t + 1 == g.T ? h - (g.T - 1) * st : h + st;
-  const int tm = t == 0 ? h + (g.T - 1) * st : h - st;
+  GS* const r = CGM == kCgUpdate ? static_cast<GS*>(cgf.r) + k * stride : nullptr;
+  double* const sc = CGM == kCgUpdate ? cgf.scal + k * kScalars : nullptr;
+  if constexpr (CGM == kCgUpdate) {
+    const double t = wave_total(strided_sum256(cgf.pap + k * cgf.npap, cgf.npap, threadIdx.x));
+    if ((threadIdx.x & 63) == 0) aw[threadIdx.x / 64] = t;
+    __syncthreads();
+  }
 
   cx<R> acc[12];
 #pragma unroll
   for (int c = 0; c < 12; ++c) acc[c] = {R(0), R(0)};
-  hop<0, -1, C12>(in, lp, Vh, xp, h, acc);
-  hop<0, +1, C12>(in, lq, Vh, xm, xm, acc);
-  hop<1, -1, C12>(in, lp, Vh, yp, h, acc);
-  hop<1, +1, C12>(in, lq, Vh, ym, ym, acc);
-  hop<2, -1, C12>(in, lp, Vh, zp, h, acc);
-  hop<2, +1, C12>(in, lq, Vh, zm, zm, acc);
-  hop<3, -1, C12>(in, lp, Vh, tp, h, acc);
-  hop<3, +1, C12>(in, lq, Vh, tm, tm, acc);
+  // x + 1 is 2 xh + o + 1: half index xh when o = 0, xh + 1 (wrapping) when o = 1;
+  // x - 1 is 2 xh + o - 1: xh - 1 (wrapping) when o = 0, xh when o = 1
+  const int row = h / p.X, xh = h - row * p.X;
+  const int y = row % p.Y, zt = row / p.Y, z = zt % p.Z, t = zt / p.Z;
+  const int o = (y + z + t + p.parity) & 1;
+  const int xp = o ? (xh + 1 == p.X ? h - (p.X - 1) : h + 1) : h;
+  const int xm = o ? h : (xh == 0 ? h + (p.X - 1) : h - 1);
+  const int yp = y + 1 == p.Y ? h - (p.Y - 1) * p.sy : h + p.sy;
+  const int ym = y == 0 ? h + (p.Y - 1) * p.sy : h - p.sy;
+  const int zp = z + 1 == p.Z ? h - (p.Z - 1) * p.sz : h + p.sz;
+  const int zm = z == 0 ? h + (p.Z - 1) * p.sz : h - p.sz;
+  const int tp = t + 1 == p.T ? h - (p.T - 1) * p.st : h + p.st;
+  const int tm = t == 0 ? h + (p.T - 1) * p.st : h - p.st;
+  eo_hop<0, -1, C12>(in, fp, V, xp, h, acc);
+  eo_hop<0, +1, C12>(in, fq, V, xm, xm, acc);
+  eo_hop<1, -1, C12>(in, fp, V, yp, h, acc);
+  eo_hop<1, +1, C12>(in, fq, V, ym, ym, acc);
+  eo_hop<2, -1, C12>(in, fp, V, zp, h, acc);
+  eo_hop<2, +1, C12>(in, fq, V, zm, zm, acc);
+  eo_hop<3, -1, C12>(in, fp, V, tp, h, acc);
+  eo_hop<3, +1, C12>(in, fq, V, tm, tm, acc);
 
-  const R d = cf.d[slot], c = cf.c[slot];
+  const R d = cf.d[rhs], c = cf.c[rhs];
   cx<R> res[12];
   if (w_all != nullptr) {
     cx<R> wv[12];
-    load_spinor(w_all + k * stride, Vh, h, wv);
+    load_spinor(w_all + k * stride, V, h, wv);
 #pragma unroll
     for (int i = 0; i < 12; ++i) res[i] = {fmar(d, wv[i].re, c * acc[i].re), fmar(d, wv[i].im, c * acc[i].im)};
   } else {
 #pragma unroll
     for (int i = 0; i < 12; ++i) res[i] = {c * acc[i].re, c * acc[i].im};
   }
-  if (g5) {
+  if (gamma5) {
 #pragma unroll
     for (int i = 6; i < 12; ++i) res[i] = -res[i];
   }
-  store_spinor(out, Vh, h, res);
+  if constexpr (CGM == kCgNone) {
+    if (valid) store_spinor(out_all + k * stride, V, h, res);
+  } else {
+    double n2 = 0.0;
+    if constexpr (CGM == kCgNorm) {
+      if (valid) n2 = store_site_norm(out_all + k * stride, V, h, res);
+    } else {
+      double pap = 0.0;
+      for (int w = 0; w < kEoBlock / 64; ++w) pap += aw[w];
+      bool flag = false;
+      const double alpha = cg_alpha(pap, sc[kRr], &flag);
+      if (h0 == 0) {
+        sc[kPap] = pap;
+        sc[kAlpha] = alpha;
+        sc[kRrPrev] = sc[kRr];
+        if (flag) sc[kFlag] = 1.0;
+      }
+      if (valid) n2 = cg_site_update_r(r, V, h, res, alpha);
+    }
+    // slices of 32 sites, as the split kernel's, or of the whole workgroup
+    n2 = half_wave_total(n2);
+    if (!p.wide) {
+      const int slice = h0 / kSplitSites;
+      if (threadIdx.x % kSplitSites == 0 && slice < cgf.nslices) cgf.rr[k * cgf.nslices + slice] = n2;
+    } else {
+      n2 += __shfl_xor(n2, 32, 64);
+      __syncthreads();
+      if ((threadIdx.x & 63) == 0) aw[threadIdx.x / 64] = n2;
+      __syncthreads();
+      if (threadIdx.x == 0) cgf.rr[k * cgf.nslices + tile] = ((aw[0] + aw[1]) + aw[2]) + aw[3];
+    }
+  }
 }
 
 // dst = gamma5 src on FP64 packed fields: plane 3 * spin + colour, spins 2
@@ -115,14 +163,18 @@ __global__ __launch_bounds__(256) void gamma5_kernel(double2* __restrict__ dst, 
   }
 }
 
-template <typename T, bool C12>
+// CG slices of 256 sites, which only the one-lane-per-site kernel sums: on
+// lattices where slices of 32 would leave more partial sums than every workgroup
+// of the next kernel should read.
+bool wide_slices(long Vh) { return Vh > 131072; }
+
+template <typename T, bool C12, int CGM>
 hipError_t launch_hop_t(const wd_gauge* g, int p, const void* in, const void* w, void* out, const RhsSet& set,
-                        const double* d, const double* c, int g5, hipStream_t s) {
-  using S = typename Packed<T>::S;
+                        const double* d, const double* c, int g5, const CgFuse& f, hipStream_t s) {
   using L = typename Packed<T>::L;
   using R = typename Packed<T>::R;
   const EoGeo geo = make_eo_geo(g->dims);
-  EoCoef<R> cf{};
+  SplitCoef<R> cf{};
   for (int i = 0; i < set.n; ++i) {
     cf.d[i] = static_cast<R>(d[i]);
     cf.c[i] = static_cast<R>(c[i]);
@@ -132,37 +184,74 @@ hipError_t launch_hop_t(const wd_gauge* g, int p, const void* in, const void* w,
   const char* links = static_cast<const char*>(g->links);
   const L* lp = reinterpret_cast<const L*>(links + p * half);        // this parity: forward hops
   const L* lq = reinterpret_cast<const L*>(links + (p ^ 1) * half);  // the other: backward hops
-  const unsigned nb = static_cast<unsigned>((geo.Vh + kEoBlock - 1) / kEoBlock);
-  const int contiguous = nb % kNumXcd == 0 ? 1 : 0;
-  eo_hop_kernel<T, C12><<<dim3(nb, set.n), kEoBlock, 0, s>>>(
-      static_cast<const S*>(in), static_cast<const S*>(w), static_cast<S*>(out), lp, lq, geo, p, cf,
-      spinor_units<T>(geo.Vh), g5, contiguous);
-  return hipGetLastError();
+  const long stride = spinor_units<T>(geo.Vh);
+  SplitParams sp{geo.Xh, geo.Y, geo.Z, geo.T, geo.Xh, geo.Xh * geo.Y, geo.Xh * geo.Y * geo.Z,
+                 static_cast<int>(geo.Vh), 1, p, wide_slices(geo.Vh) ? 1 : 0};
+  sp.nrhs = set.n;
+  sp.link_bytes = half < (1ul << 32) ? static_cast<unsigned>(half) : 0u;
+  sp.spinor_bytes = stride * 16 < (1l << 32) ? static_cast<unsigned>(stride * 16) : 0u;
+  if (use_split_eo(g->prec, geo.Vh, set.n) && !(CGM != kCgNone && wide_slices(geo.Vh)))
+    return launch_split_hop<T, C12, CGM>(in, w, out, lp, lq, cf, stride, g5, sp, f, s);
+  sp.ntiles = (sp.V + kEoBlock - 1) / kEoBlock;
+  sp.per = (sp.ntiles + kNumXcd - 1) / kNumXcd;
+  const unsigned nb = static_cast<unsigned>(sp.per) * kNumXcd * static_cast<unsigned>(set.n);
+  const auto run = [&](auto kernel) {
+    kernel<<<nb, kEoBlock, 0, s>>>(static_cast<const typename Packed<T>::S*>(in),
+                                   static_cast<const typename Packed<T>::S*>(w),
+                                   static_cast<typename Packed<T>::S*>(out), lp, lq, cf, stride, g5, sp, f);
+    return hipGetLastError();
+  };
+  if (sp.link_bytes != 0 && sp.spinor_bytes != 0) return run(&eo_hop_kernel<T, C12, CGM, true>);
+  return run(&eo_hop_kernel<T, C12, CGM, false>);
+}
+
+template <typename T, bool C12>
+hipError_t launch_hop_mode(const wd_gauge* g, int p, const void* in, const void* w, void* out, const RhsSet& set,
+                           const double* d, const double* c, int g5, const CgFuse* f, hipStream_t s) {
+  if (f == nullptr) return launch_hop_t<T, C12, kCgNone>(g, p, in, w, out, set, d, c, g5, CgFuse{}, s);
+  if (f->rr == nullptr || f->nslices < eo_fuse_slices(g->dims, g->prec) || f->nslices < 1)
+    return hipErrorInvalidValue;
+  if (f->mode == kCgNorm) return launch_hop_t<T, C12, kCgNorm>(g, p, in, w, out, set, d, c, g5, *f, s);
+  if (f->mode != kCgUpdate || f->r == nullptr || f->pap == nullptr || f->npap < 1 || f->scal == nullptr)
+    return hipErrorInvalidValue;
+  return launch_hop_t<T, C12, kCgUpdate>(g, p, in, w, out, set, d, c, g5, *f, s);
 }
 
 template <typename T>
 hipError_t launch_hop_prec(const wd_gauge* g, int p, const void* in, const void* w, void* out,
-                           const RhsSet& set, const double* d, const double* c, int g5, hipStream_t s) {
-  return g->c12 ? launch_hop_t<T, true>(g, p, in, w, out, set, d, c, g5, s)
-                : launch_hop_t<T, false>(g, p, in, w, out, set, d, c, g5, s);
+                           const RhsSet& set, const double* d, const double* c, int g5, const CgFuse* f,
+                           hipStream_t s) {
+  return g->c12 ? launch_hop_mode<T, true>(g, p, in, w, out, set, d, c, g5, f, s)
+                : launch_hop_mode<T, false>(g, p, in, w, out, set, d, c, g5, f, s);
 }
 
-}  // namespace
-
-hipError_t launch_eo_hop(const wd_gauge* g, int parity, const void* in, const void* w, void* out,
-                         const RhsSet& set, const double* d, const double* c, int g5, hipStream_t s) {
+hipError_t launch_hop(const wd_gauge* g, int parity, const void* in, const void* w, void* out, const RhsSet& set,
+                      const double* d, const double* c, int g5, const CgFuse* f, hipStream_t s) {
   if (set.n < 1) return hipSuccess;
   if (set.n > kMaxRhs || !g->eo || (parity != 0 && parity != 1)) return hipErrorInvalidValue;
   switch (g->prec) {
-    case WD_FP64: return launch_hop_prec<double>(g, parity, in, w, out, set, d, c, g5, s);
-    case WD_FP32: return launch_hop_prec<float>(g, parity, in, w, out, set, d, c, g5, s);
-    case WD_FP16: return launch_hop_prec<_Float16>(g, parity, in, w, out, set, d, c, g5, s);
+    case WD_FP64: return launch_hop_prec<double>(g, parity, in, w, out, set, d, c, g5, f, s);
+    case WD_FP32: return launch_hop_prec<float>(g, parity, in, w, out, set, d, c, g5, f, s);
+    case WD_FP16: return launch_hop_prec<_Float16>(g, parity, in, w, out, set, d, c, g5, f, s);
     default: return hipErrorInvalidValue;
   }
 }
 
+}  // namespace
+
+int eo_fuse_slices(const int32_t dims[4], int prec) {
+  const long Vh = make_eo_geo(dims).Vh;
+  if (!wide_slices(Vh)) return static_cast<int>((Vh + kSplitSites - 1) / kSplitSites);
+  return prec == WD_FP64 ? 0 : static_cast<int>((Vh + kEoBlock - 1) / kEoBlock);
+}
+
+hipError_t launch_eo_hop(const wd_gauge* g, int parity, const void* in, const void* w, void* out,
+                         const RhsSet& set, const double* d, const double* c, int g5, hipStream_t s) {
+  return launch_hop(g, parity, in, w, out, set, d, c, g5, nullptr, s);
+}
+
 hipError_t launch_schur_q(const wd_gauge* g, const double* masses, const RhsSet& set, const void* in,
-                          void* tmp, void* out, hipStream_t s) {
+                          void* tmp, void* out, const CgFuse* f, hipStream_t s) {
   double d[kMaxRhs], c[kMaxRhs];
   for (int i = 0; i < set.n; ++i) {
     d[i] = 0.0;
@@ -175,7 +264,7 @@ hipError_t launch_schur_q(const wd_gauge* g, const double* masses, const RhsSet&
     d[i] = a;
     c[i] = 1.0 / (2.0 * a);
   }
-  return launch_eo_hop(g, 1, tmp, in, out, set, d, c, 1, s);
+  return launch_hop(g, 1, tmp, in, out, set, d, c, 1, f, s);
 }
 
 hipError_t blas_gamma5(void* dst, const void* src, long n, const RhsSet& set, hipStream_t st) {

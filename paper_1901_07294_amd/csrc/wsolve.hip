@@ -104,7 +104,8 @@ struct Solver {
       rc = status(blas_gamma5(at(ws, lay.t2), at(ws, lay.t1), spinor_units<double>(Vh), all, st),
                   "wilson: gamma5 source");
     if (rc == WD_OK)
-      rc = status(launch_schur_q(ghi, masses, all, at(ws, lay.t2), at(ws, lay.t1), at(ws, lay.bn), st),
+      rc = status(launch_schur_q(ghi, masses, all, at(ws, lay.t2), at(ws, lay.t1), at(ws, lay.bn), nullptr,
+                                 st),
                   "wilson: S^dag source");
     return rc;
   }

@@ -188,3 +188,71 @@ def test_export_of_partial_runs(dims, prec):
             got = export(w.wd_spinor_export_eo, g.pack_eo(psis, parity), g.prec, 3, parity)
             assert np.array_equal(got, oracle.restrict(want, parity) if want.ndim == 6 else
                                   np.stack([oracle.restrict(f, parity) for f in want]))
+
+
+@pytest.mark.parametrize("prec,c12", [("fp64", False), ("fp32", True), ("fp16", False), ("fp16", True)])
+@pytest.mark.parametrize("dims,nrhs", [
+    ((2, 6, 4, 10), 1),    # x rows of one half site, 240 half sites: the last run of 32 holds 16
+    ((16, 16, 18, 20), 2), # 92160 half sites over both fields: one lane per site in FP32 and FP16
+    ((26, 10, 6, 14), 5),  # 54600: the one-lane kernel's last workgroup is partly filled
+], ids=["2x6x4x10", "16x16x18x20_x2", "26x10x6x14_x5"])
+def test_schur_kernels(dims, nrhs, prec, c12):
+    """The even-odd operator where launches change kernel: the last field
+    against the oracle (output and even intermediate), and each field's bits
+    alone, in a launch small enough for the other kernel."""
+    print(f"case schur dims={dims} nrhs={nrhs} prec={prec} c12={c12}", flush=True)
+    U = li.random_gauge(dims, 111)
+    psis = li.gaussian_spinors(dims, [112 + k for k in range(nrhs)])
+    masses = [0.05 + 0.1 * k for k in range(nrhs)]
+    g = DeviceGauge(U, PRECS[prec], c12, eo=True)
+
+    def apply(psi, m):
+        n = len(m)
+        out, tmp = g.half_spinor(n).zero_(), g.half_spinor(n).zero_()
+        w.dslash_apply_eo(g.handle, m, n, g.pack_eo(psi, 1, nrhs=n), out, tmp, g.prec, flags=w.WD_FLAG_GAMMA5)
+        return out, tmp
+
+    out, tmp = apply(psis, masses)
+    size = out.numel() // nrhs
+    for k in range(nrhs):
+        one, one_tmp = apply(psis[k:k + 1], masses[k:k + 1])
+        assert torch.equal(one, out[k * size:(k + 1) * size])
+        assert torch.equal(one_tmp, tmp[k * size:(k + 1) * size])
+    k = nrhs - 1
+    odd = oracle.restrict(psis[k], 1)
+    tol = 2 * TOL[PRECS[prec]]  # two applications of the hopping term
+    got = g.unpack_eo(tmp, 0, nrhs=nrhs).reshape(nrhs, *psis.shape[1:])[k]
+    assert rel(got, oracle.restrict(-0.5 * oracle.hopping(U, odd), 0)) <= tol
+    got = g.unpack_eo(out, 1, nrhs=nrhs).reshape(nrhs, *psis.shape[1:])[k]
+    assert rel(got, oracle.gamma5_schur(U, masses[k], odd)) <= tol
+
+
+@pytest.mark.parametrize("inner", ["fp64", "fp32", "fp16"])
+@pytest.mark.parametrize("dims", [(6, 4, 10, 8), (16, 16, 16, 16), (24, 24, 24, 20)],
+                         ids=lambda d: "x".join(map(str, d)))
+def test_even_odd_solves_in_fused_kernels(dims, inner):
+    """Even-odd solves with the CG work fused: slices of 32 half sites in both
+    kernels, and slices of 256 (from 131072 half sites on; unfused in FP64). The
+    oracle's residual of D x = b, and a field's bits alone as beside another."""
+    print(f"case even-odd cg dims={dims} inner={inner}", flush=True)
+    U = li.near_unity_gauge(dims, 121, 0.3)
+    bs = li.gaussian_spinors(dims, [122, 123])
+    masses = [0.2, 0.3]
+    prec = PRECS[inner]
+    ghi, glo = DeviceGauge(U, w.WD_FP64, eo=True), DeviceGauge(U, prec, eo=True)
+
+    def solve(b, m):
+        n = len(m)
+        x = ghi.spinor(n)
+        ws = torch.empty(w.wilson_workspace_bytes(dims, n, prec, 1), dtype=torch.uint8, device="cuda")
+        rc, stats = w.cg_solve_wilson(ghi.handle, glo.handle, m, n, ghi.pack(b, nrhs=n), x,
+                                      dict(tol=1e-10, max_iter=2000, inner=prec, delta=0.1, check_every=5,
+                                           x0_given=0, use_graph=0), ws)
+        assert rc == w.WD_OK, stats
+        return ghi.unpack(x, nrhs=n).reshape(n, *b.shape[1:])
+
+    both = solve(bs, masses)
+    assert np.array_equal(both[0], solve(bs[:1], masses[:1])[0])
+    for k in range(2):
+        r = bs[k] - oracle.dslash(U, both[k], masses[k])
+        assert np.linalg.norm(r) <= 1e-10 * np.linalg.norm(bs[k])

@@ -59,8 +59,9 @@ hipError_t blas_update_xr(void* x, void* r, const void* p, const void* ap, int p
 // followed by blas_update_p.
 hipError_t blas_update_r(void* r, const void* ap, long n, long V, const RhsSet& set, const double* pap,
                          int npap, double* partials, int* nrr, double* scal, hipStream_t st);
-hipError_t blas_update_xp(void* x, void* p, const void* r, long n, const RhsSet& set, const double* rr,
-                          int nrr, double* scal, hipStream_t st);
+// p_out may be p.
+hipError_t blas_update_xp(void* x, void* p_out, const void* p, const void* r, long n, const RhsSet& set,
+                          const double* rr, int nrr, double* scal, hipStream_t st);
 // Mixed precision (FP32 or FP16-storage vectors), after the dslash launch that
 // applied r -= alpha Ap in its epilogue: x_lo += alpha p (alpha as that launch
 // recorded it; x_lo the FP32 accumulator, nlo32 16-byte elements per

@@ -206,8 +206,8 @@ __global__ __launch_bounds__(kThreads) void update_r_kernel(double2* __restrict_
 // update_r_kernel recorded it (the value every workgroup there applied) and
 // beta reduced from that kernel's |r|^2 partials. Each element gets the
 // multiply-adds of update_xr_kernel and update_p_kernel, so the bits match.
-__global__ __launch_bounds__(kThreads) void update_xp_kernel(double2* __restrict__ x,
-                                                             double2* __restrict__ p,
+__global__ __launch_bounds__(kThreads) void update_xp_kernel(double2* __restrict__ x, double2* p_out,
+                                                             const double2* p,
                                                              const double2* __restrict__ r, long n,
                                                              RhsSet set, const double* __restrict__ rr,
                                                              int nrr, double* __restrict__ scal) {
@@ -216,7 +216,8 @@ __global__ __launch_bounds__(kThreads) void update_xp_kernel(double2* __restrict
   const double alpha = sc[kAlpha];  // not written by this kernel
   const double beta = beta_from_partials(rr + k * nrr, nrr, sc);
   double2* xk = x + k * n;
-  double2* pk = p + k * n;
+  double2* pok = p_out + k * n;
+  const double2* pk = p + k * n;
   const double2* rk = r + k * n;
   for (long e = static_cast<long>(blockIdx.x) * kThreads + threadIdx.x; e < n;
        e += static_cast<long>(gridDim.x) * kThreads) {
@@ -228,7 +229,7 @@ __global__ __launch_bounds__(kThreads) void update_xp_kernel(double2* __restrict
     pe.x = fmar(beta, pe.x, re.x);
     pe.y = fmar(beta, pe.y, re.y);
     xk[e] = xe;
-    pk[e] = pe;
+    pok[e] = pe;
   }
 }
 
@@ -669,9 +670,10 @@ hipError_t blas_update_r(void* r, const void* ap, long n, long V, const RhsSet& 
   return hipGetLastError();
 }
 
-hipError_t blas_update_xp(void* x, void* p, const void* r, long n, const RhsSet& set, const double* rr,
-                          int nrr, double* scal, hipStream_t st) {
-  update_xp_kernel<<<grid(n, set.n), kThreads, 0, st>>>(static_cast<double2*>(x), static_cast<double2*>(p),
+hipError_t blas_update_xp(void* x, void* p_out, const void* p, const void* r, long n, const RhsSet& set,
+                          const double* rr, int nrr, double* scal, hipStream_t st) {
+  update_xp_kernel<<<grid(n, set.n), kThreads, 0, st>>>(static_cast<double2*>(x), static_cast<double2*>(p_out),
+                                                        static_cast<const double2*>(p),
                                                         static_cast<const double2*>(r), n, set, rr, nrr,
                                                         scal);
   return hipGetLastError();

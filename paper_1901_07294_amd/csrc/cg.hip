@@ -173,25 +173,43 @@ int CgEngine::chunk(const RhsSet& set, int n) {
 int CgEngine::iterate(const RhsSet& set, int j, int n) {
   double m[kMaxRhs];
   for (int i = 0; i < set.n; ++i) m[i] = masses_[set.idx[i]];
-  if (lay_.nslices > 0 && inner_ == WD_FP64 && lay_.fuse_update) {
-    // as with FP32 arithmetic below, but x is updated in every iteration
+  // the update of iteration j - 1's x and p, folded into iteration j's first
+  // application of Q (small lattices), or in a launch of its own
+  const bool fold = lay_.nslices > 0 && lay_.fuse_update &&
+                    (eo_ ? eo_fold_p(ghi_->dims, inner_, set.n) : cg_fold_p(ghi_->dims, inner_, set.n));
+  if (fold || (lay_.nslices > 0 && inner_ == WD_FP64 && lay_.fuse_update)) {
+    void* const pa = at(ws_, lay_.p);
+    void* const pb = at(ws_, inner_ == WD_FP64 ? lay_.ap : lay_.p2);
+    void* const pc = fold && (j & 1) != 0 ? pb : pa;  // this iteration's direction
     CgFuse f{};
     f.mode = kCgNorm;
     f.rr = paps_;
     f.nslices = lay_.nslices;
-    int rc = apply_q_cg(m, set, at(ws_, lay_.p), at(ws_, lay_.t), f, "cg: Q p with |Q p|^2");
-    f.mode = kCgUpdate;
     f.r = at(ws_, lay_.r);
+    f.scal = scal_;
+    const void* in = pc;
+    if (fold && j > 0) {
+      in = pc == pa ? pb : pa;
+      f.p_out = pc;
+      f.x = inner_ == WD_FP64 ? x_ : at(ws_, lay_.x_lo);
+      f.x_units = inner_ == WD_FP64 ? nhi_ : n32_;
+      f.prr = rr_;
+      f.nprr = lay_.nslices;
+    }
+    int rc = apply_q_cg(m, set, in, at(ws_, lay_.t), f, "cg: Q p with |Q p|^2");
+    f.p_out = nullptr;
+    f.mode = kCgUpdate;
     f.pap = paps_;
     f.npap = lay_.nslices;
     f.rr = rr_;
-    f.scal = scal_;
     if (rc == WD_OK)
       rc = apply_q_cg(m, set, at(ws_, lay_.t), nullptr, f, "cg: Q Q p with r");
-    if (rc == WD_OK)
-      rc = launch_status(blas_update_xp(x_, at(ws_, lay_.p), at(ws_, lay_.r), nlo_, set, rr_, lay_.nslices,
-                                        scal_, st_), "cg: x, p");
-    return rc;
+    if (rc != WD_OK || (fold && j + 1 < n)) return rc;
+    return launch_status(inner_ == WD_FP64
+                             ? blas_update_xp(x_, pa, pc, at(ws_, lay_.r), nlo_, set, rr_, lay_.nslices, scal_, st_)
+                             : blas_update_xp_lo(at(ws_, lay_.x_lo), pa, pc, pa, at(ws_, lay_.r), kXpNow, inner_,
+                                                 nlo_, n32_, V_, set, rr_, lay_.nslices, scal_, st_),
+                         "cg: x, p");
   }
   if (lay_.nslices > 0 && inner_ == WD_FP64) {
     // t = Q p with <p, A p> = |t|^2 summed per tile slice in the same launch;
@@ -210,7 +228,7 @@ int CgEngine::iterate(const RhsSet& set, int j, int n) {
       rc = launch_status(blas_update_r(at(ws_, lay_.r), at(ws_, lay_.ap), nlo_, V_, set, paps_,
                                        lay_.nslices, partials_, &nrr, scal_, st_), "cg: r");
     if (rc == WD_OK)
-      rc = launch_status(blas_update_xp(x_, at(ws_, lay_.p), at(ws_, lay_.r), nlo_, set, partials_, nrr,
+      rc = launch_status(blas_update_xp(x_, at(ws_, lay_.p), at(ws_, lay_.p), at(ws_, lay_.r), nlo_, set, partials_, nrr,
                                         scal_, st_), "cg: x, p");
     return rc;
   }
@@ -261,7 +279,7 @@ int CgEngine::iterate(const RhsSet& set, int j, int n) {
       rc = launch_status(blas_update_r(at(ws_, lay_.r), at(ws_, lay_.ap), nlo_, V_, set, pap_, npap,
                                        partials_, &nrr, scal_, st_), "cg: r");
     if (rc == WD_OK)
-      rc = launch_status(blas_update_xp(x_, at(ws_, lay_.p), at(ws_, lay_.r), nlo_, set, partials_, nrr,
+      rc = launch_status(blas_update_xp(x_, at(ws_, lay_.p), at(ws_, lay_.p), at(ws_, lay_.r), nlo_, set, partials_, nrr,
                                         scal_, st_), "cg: x, p");
     return rc;
   }

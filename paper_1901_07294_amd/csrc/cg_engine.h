@@ -54,7 +54,10 @@ class CgEngine {
   // scalars of the slots zeroed, <b,b>, x = 0 and r = b (or r = b - A x
   // when x0_given), inner residual and p = r.
   int start(const RhsSet& set, bool x0_given);
-  // n CG iterations on the slots of set. Where the inner vector updates are
+  // n CG iterations on the slots of set. On small lattices the x and p update of
+  // an iteration that is not the chunk's last is folded into the next one's first
+  // application of Q (the directions alternate between p and a second buffer).
+  // Elsewhere, where the inner vector updates are
   // fused (FP32 arithmetic), the x update of an even-numbered iteration of
   // the chunk (0, 2, ...) that is not the last is left for the next one,
   // which applies both in turn (the same operations in the same order), with

@@ -459,16 +459,18 @@ struct MarchCost {
   int waves, waves2;
   double prologue, prologue2, tail, rb2;
 };
-MarchCost march_cost(int prec) {
+MarchCost march_cost(int prec, bool fused) {
   if (prec == WD_FP64) return {4, 0, 0.8, 0.0, -1.0, 0.0};
   if (prec == WD_FP32) return {8, 8, 0.4, 0.7, -1.0, 1.2};
-  return {12, 0, 0.4, 0.0, 0.5, 0.0};
+  // the fused CG work adds a reduction to each workgroup's start (solves on 24^4:
+  // 14.74 ms with one slice per workgroup, which 0.4 would choose, 14.10 with two)
+  return {12, 0, fused ? 0.6 : 0.4, 0.0, 0.5, 0.0};
 }
 
 // Geometry of the t-marching kernel for a lattice, with the default launch
 // choice, or ny = 0 if it does not apply (x rows longer than a workgroup, or
 // too few sites per tile).
-MarchParams march_params(const Geo& geo, int prec, int nrhs) {
+MarchParams march_params(const Geo& geo, int prec, int nrhs, bool fused = false) {
   MarchParams p{0, 0, 0, 0, 0, nrhs, 1, 1, 0u, 0u};
   const size_t real_bytes = real_bytes_of(prec);
   if (geo.X > kMarchMaxThreads) return p;
@@ -480,7 +482,7 @@ MarchParams march_params(const Geo& geo, int prec, int nrhs) {
   p.ytiles = geo.Y / ny;
   const int n = geo.X * ny;
   const int waves = (n + 63) / 64;
-  const MarchCost mc = march_cost(prec);
+  const MarchCost mc = march_cost(prec, fused);
   double best = 0.0;
   for (int rb = 1; rb <= 2; ++rb) {
     const size_t lds = rb * march_lds_bytes(n, real_bytes);
@@ -571,7 +573,7 @@ hipError_t launch_march(const void* in, void* out, const void* links, const Geo&
 }
 
 // The split kernel: mode CGM of the launch.
-template <typename T, bool C12, int CGM>
+template <typename T, bool C12, int CGM, int FOLD = kFoldNone>
 hipError_t launch_split(const void* in, void* out, const void* links, const Geo& geo,
                         const Diag<typename Packed<T>::R>& diag, long stride, int g5, const MarchParams& m,
                         const CgFuse& f, hipStream_t st) {
@@ -587,7 +589,7 @@ hipError_t launch_split(const void* in, void* out, const void* links, const Geo&
     cf.c[k] = R(-0.5);
     cf.idx[k] = diag.idx[k];
   }
-  return launch_split_hop<T, C12, CGM>(in, in, out, links, links, cf, stride, g5, p, f, st);
+  return launch_split_hop<T, C12, CGM, FOLD>(in, in, out, links, links, cf, stride, g5, p, f, st);
 }
 
 // Whether the split kernel is the default for nrhs fields: where the t-marching
@@ -643,7 +645,7 @@ hipError_t launch_typed(const wd_gauge* g, const void* in, void* out, const Geo&
     diag.idx[k] = fields ? fields[k] : k;
   }
   const long stride = spinor_units<T>(geo.V);  // 16-B elements per field
-  MarchParams p = march_params(geo, g->prec, nrhs);
+  MarchParams p = march_params(geo, g->prec, nrhs, cg != nullptr);
   // byte sizes for buffer-resource access, or 0 where a field reaches 4 GiB
   const unsigned long sbytes = static_cast<unsigned long>(stride) * 16;
   p.link_bytes = g->link_bytes < (1ul << 32) ? static_cast<unsigned>(g->link_bytes) : 0u;
@@ -662,6 +664,9 @@ hipError_t launch_typed(const wd_gauge* g, const void* in, void* out, const Geo&
       return hipErrorInvalidValue;
     split = small_slices(geo, p);
     if (!split && !whole_waves(geo, p)) return hipErrorInvalidValue;
+    if (cg->mode == kCgNorm && cg->p_out != nullptr)
+      return split ? launch_split<T, C12, kCgNorm, kFoldBoth>(in, out, g->links, geo, diag, stride, g5, p, *cg, st)
+                   : hipErrorInvalidValue;
     if (cg->mode == kCgNorm)
       return split ? launch_split<T, C12, kCgNorm>(in, out, g->links, geo, diag, stride, g5, p, *cg, st)
                    : launch_march<T, C12, kCgNorm>(in, out, g->links, geo, diag, stride, g5, p, *cg, st);
@@ -720,6 +725,16 @@ int cg_fuse_slices(const int32_t dims[4], int prec) {
 // 16^3 x 32 99 -> 88 (with the launch shapes of before: 24^4 277 -> 285).
 bool cg_fuse_update(const int32_t dims[4], int prec) {
   return cg_fuse_slices(dims, prec) > 0 && (prec != WD_FP64 || make_geo(dims).V <= 131072);
+}
+
+// A launch per iteration saved against r read eight times over, with its
+// rounding in FP16: 8^4 FP64 19.8 -> 17.2 us per iteration, FP32 19.4 -> 16.5,
+// FP16 24.3 -> 17.9; 12^4 FP32 22.6 -> 21.2 but with two fields 28.1 -> 28.5, FP64
+// 25.3 -> 26.0, FP16 with four fields 41.9 -> 40.4 and with eight 57.5 -> 60.8.
+bool cg_fold_p(const int32_t dims[4], int prec, int n) {
+  const Geo geo = make_geo(dims);
+  const long most = prec == WD_FP64 ? 16384 : prec == WD_FP32 ? 32768 : 98304;
+  return static_cast<long>(geo.V) * n <= most && small_slices(geo, march_params(geo, prec, 1));
 }
 
 hipError_t launch_dslash_cg(const wd_gauge* g, const double* masses, int nrhs, const int* fields,

@@ -39,6 +39,8 @@ hipError_t launch_schur_q(const wd_gauge* g, const double* masses, const RhsSet&
 // Slices of that work (32 consecutive half sites, or 256 on large lattices), or
 // 0 where it does not apply (FP64 on large lattices).
 int eo_fuse_slices(const int32_t dims[4], int prec);
+// Whether n field slots should form p inside kCgNorm (CgFuse::p_out).
+bool eo_fold_p(const int32_t dims[4], int prec, int n);
 
 // dst = gamma5 src for FP64 packed fields of V sites (n 16-byte elements each).
 hipError_t blas_gamma5(void* dst, const void* src, long n, const RhsSet& set, hipStream_t st);

@@ -168,7 +168,7 @@ __global__ __launch_bounds__(256) void gamma5_kernel(double2* __restrict__ dst, 
 // of the next kernel should read.
 bool wide_slices(long Vh) { return Vh > 131072; }
 
-template <typename T, bool C12, int CGM>
+template <typename T, bool C12, int CGM, int FOLD = kFoldNone>
 hipError_t launch_hop_t(const wd_gauge* g, int p, const void* in, const void* w, void* out, const RhsSet& set,
                         const double* d, const double* c, int g5, const CgFuse& f, hipStream_t s) {
   using L = typename Packed<T>::L;
@@ -190,8 +190,8 @@ hipError_t launch_hop_t(const wd_gauge* g, int p, const void* in, const void* w,
   sp.nrhs = set.n;
   sp.link_bytes = half < (1ul << 32) ? static_cast<unsigned>(half) : 0u;
   sp.spinor_bytes = stride * 16 < (1l << 32) ? static_cast<unsigned>(stride * 16) : 0u;
-  if (use_split_eo(g->prec, geo.Vh, set.n) && !(CGM != kCgNone && wide_slices(geo.Vh)))
-    return launch_split_hop<T, C12, CGM>(in, w, out, lp, lq, cf, stride, g5, sp, f, s);
+  if (FOLD != kFoldNone || (use_split_eo(g->prec, geo.Vh, set.n) && !(CGM != kCgNone && wide_slices(geo.Vh))))
+    return launch_split_hop<T, C12, CGM, FOLD>(in, w, out, lp, lq, cf, stride, g5, sp, f, s);
   sp.ntiles = (sp.V + kEoBlock - 1) / kEoBlock;
   sp.per = (sp.ntiles + kNumXcd - 1) / kNumXcd;
   const unsigned nb = static_cast<unsigned>(sp.per) * kNumXcd * static_cast<unsigned>(set.n);
@@ -209,8 +209,13 @@ template <typename T, bool C12>
 hipError_t launch_hop_mode(const wd_gauge* g, int p, const void* in, const void* w, void* out, const RhsSet& set,
                            const double* d, const double* c, int g5, const CgFuse* f, hipStream_t s) {
   if (f == nullptr) return launch_hop_t<T, C12, kCgNone>(g, p, in, w, out, set, d, c, g5, CgFuse{}, s);
+  // with a fold, the hop onto the even sites (no w) reads p, the one back owns it
+  if (f->p_out != nullptr && w == nullptr)
+    return launch_hop_t<T, C12, kCgNone, kFoldIn>(g, p, in, w, out, set, d, c, g5, *f, s);
   if (f->rr == nullptr || f->nslices < eo_fuse_slices(g->dims, g->prec) || f->nslices < 1)
     return hipErrorInvalidValue;
+  if (f->mode == kCgNorm && f->p_out != nullptr)
+    return launch_hop_t<T, C12, kCgNorm, kFoldOwn>(g, p, in, w, out, set, d, c, g5, *f, s);
   if (f->mode == kCgNorm) return launch_hop_t<T, C12, kCgNorm>(g, p, in, w, out, set, d, c, g5, *f, s);
   if (f->mode != kCgUpdate || f->r == nullptr || f->pap == nullptr || f->npap < 1 || f->scal == nullptr)
     return hipErrorInvalidValue;
@@ -245,6 +250,15 @@ int eo_fuse_slices(const int32_t dims[4], int prec) {
   return prec == WD_FP64 ? 0 : static_cast<int>((Vh + kEoBlock - 1) / kEoBlock);
 }
 
+// Five launches per iteration become four; r is read by both hops. 8^4 FP64 35.9
+// -> 33.5 us per iteration, FP16 41.4 -> 36.3; 12^4 with two fields FP64 43.6 ->
+// 44.3 but FP16 42.3 -> 37.3; 16^4 FP32 47.0 -> 46.3, with four fields 97 -> 106;
+// FP16 with two fields 60.8 -> 60.0, with four 79.6 -> 88.0.
+bool eo_fold_p(const int32_t dims[4], int prec, int n) {
+  const long Vh = make_eo_geo(dims).Vh;
+  return !wide_slices(Vh) && Vh * n <= (prec == WD_FP64 ? 12000 : prec == WD_FP32 ? 32768 : 80000);
+}
+
 hipError_t launch_eo_hop(const wd_gauge* g, int parity, const void* in, const void* w, void* out,
                          const RhsSet& set, const double* d, const double* c, int g5, hipStream_t s) {
   return launch_hop(g, parity, in, w, out, set, d, c, g5, nullptr, s);
@@ -257,7 +271,8 @@ hipError_t launch_schur_q(const wd_gauge* g, const double* masses, const RhsSet&
     d[i] = 0.0;
     c[i] = -0.5;
   }
-  hipError_t e = launch_eo_hop(g, 0, in, nullptr, tmp, set, d, c, 0, s);
+  const bool fold = f != nullptr && f->p_out != nullptr;
+  hipError_t e = launch_hop(g, 0, in, nullptr, tmp, set, d, c, 0, fold ? f : nullptr, s);
   if (e != hipSuccess) return e;
   for (int i = 0; i < set.n; ++i) {
     const double a = 4.0 + masses[i];

@@ -141,6 +141,10 @@ bool tuned_lookup(const int32_t dims[4], int prec, int c12, int nrhs, MarchTunin
 // workgroup), else a tile's x rows at one z and t: fixed by the lattice, not by
 // the launch.
 enum : int { kCgNone = 0, kCgNorm = 1, kCgUpdate = 2 };
+// kCgNorm with p_out set also forms the direction it is applied to: `in` is the
+// old p, p_out = r + beta p (another buffer) with beta from the <r,r> partial
+// sums in prr, x += alpha p with the old p and the alpha recorded in scal
+// (cg_fold_p says where this exists).
 struct CgFuse {
   int mode;           // kCgNorm or kCgUpdate
   void* r;            // residual, inner precision
@@ -149,6 +153,11 @@ struct CgFuse {
   double* rr;         // out: |t|^2 or <r, r> per slice, nslices per field slot
   int nslices;
   double* scal;       // per field slot scalars (kScalars doubles)
+  void* p_out;        // the new direction, or null (no fold)
+  void* x;            // the solution (FP64), or the FP32 accumulator
+  long x_units;       // 16-byte elements of x per field slot
+  const double* prr;  // <r,r> partial sums of the last update, nprr per field slot
+  int nprr;
 };
 // Slices of the fused work on a lattice in a precision, or 0 where it does
 // not apply (larger lattices without t-marching tiles of whole waves).
@@ -156,6 +165,8 @@ int cg_fuse_slices(const int32_t dims[4], int prec);
 // Whether kCgUpdate exists there: with FP32 arithmetic (FP32 and FP16
 // storage) wherever kCgNorm does, in FP64 up to 131072 sites.
 bool cg_fuse_update(const int32_t dims[4], int prec);
+// Whether n field slots should form p inside kCgNorm.
+bool cg_fold_p(const int32_t dims[4], int prec, int n);
 // Q = gamma5 D(masses[i]) on field fields[i] of `in` (into `out` for
 // kCgNorm), fused with the work of f.mode for the same field slots
 // (cg_fuse_slices must be > 0).

@@ -256,3 +256,36 @@ def test_even_odd_solves_in_fused_kernels(dims, inner):
     for k in range(2):
         r = bs[k] - oracle.dslash(U, both[k], masses[k])
         assert np.linalg.norm(r) <= 1e-10 * np.linalg.norm(bs[k])
+
+
+@pytest.mark.parametrize("eo", [False, True], ids=["normal", "even_odd"])
+@pytest.mark.parametrize("inner", ["fp64", "fp32", "fp16"])
+def test_folded_directions_keep_bits(inner, eo):
+    """On small lattices the directions of a chunk's iterations are formed inside
+    the operator. After the same 12 iterations, chunks of 1 (nothing folded), 5
+    (odd, ends in the second buffer or the first) and 12 give the same solution
+    bits, as does a batch large enough for launches of their own (13 fields of
+    8400 sites). x0 = 0, no reliable update before the end."""
+    dims = (10, 6, 14, 10)
+    print(f"case folded p dims={dims} inner={inner} eo={eo}", flush=True)
+    U = li.near_unity_gauge(dims, 131, 0.3)
+    bs = li.gaussian_spinors(dims, [132 + k for k in range(13)])
+    prec = PRECS[inner]
+    ghi, glo = DeviceGauge(U, w.WD_FP64, eo=eo), DeviceGauge(U, prec, eo=eo)
+    call = w.cg_solve_wilson if eo else w.cg_solve_normal
+
+    def solve(b, every):
+        n = b.shape[0]
+        x = ghi.spinor(n)
+        size = (w.wilson_workspace_bytes(dims, n, prec, 1) if eo else w.cg_workspace_bytes(dims, n, prec))
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+        rc, stats = call(ghi.handle, glo.handle, [0.05 + 0.02 * k for k in range(n)], n, ghi.pack(b, nrhs=n), x,
+                         dict(tol=1e-30, max_iter=12, inner=prec, delta=1e-30, check_every=every, x0_given=0,
+                              use_graph=0), ws)
+        assert rc == w.WD_ERR_NOT_CONVERGED and all(s["iters"] == 12 for s in stats), stats
+        return ghi.unpack(x, nrhs=n).reshape(n, *b.shape[1:])
+
+    ref = solve(bs[:2], 1)
+    for every in (5, 12):
+        assert np.array_equal(solve(bs[:2], every), ref), every
+    assert np.array_equal(solve(bs, 5)[:2], ref)

@@ -208,6 +208,10 @@ def _nbytes(buf):
 def _stream(stream):
     if stream is None:
         import torch
+        # the handle itself, without building torch's Stream object around it
+        # (2.6 of the 7.4 us a small dslash_apply took on the host)
+        if torch.cuda.is_initialized():
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         return torch.cuda.current_stream().cuda_stream
     if hasattr(stream, "cuda_stream"):
         return stream.cuda_stream

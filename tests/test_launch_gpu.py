@@ -289,3 +289,13 @@ def test_folded_directions_keep_bits(inner, eo):
     for every in (5, 12):
         assert np.array_equal(solve(bs[:2], every), ref), every
     assert np.array_equal(solve(bs, 5)[:2], ref)
+
+
+def test_binding_follows_the_current_stream():
+    """stream=None is torch's current stream, inside and outside a stream context."""
+    assert w._stream(None) == torch.cuda.current_stream().cuda_stream
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        assert w._stream(None) == side.cuda_stream != torch.cuda.default_stream().cuda_stream
+    assert w._stream(None) == torch.cuda.current_stream().cuda_stream
+    assert w._stream(side) == side.cuda_stream and w._stream(5) == 5

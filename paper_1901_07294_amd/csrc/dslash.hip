@@ -192,14 +192,23 @@ constexpr int kCgLds = 2 * 4 + 4;
 // compiled for three waves per SIMD (the plain FP32-arithmetic kernel's
 // occupancy), at the cost of a few spilled registers in FP32 storage, which
 // measured faster than two waves without spills.
-template <int CGM, typename T, int RB>
+// ONE: marches of a single slice (p.tb == 1). Without a next slice there is one
+// LDS slice and no accumulator or link column carried on, which brings FP16
+// storage from 160 registers to 127 and, bound to five waves per SIMD, to 96
+// without a spill (2 to 3 % faster than at four with several fields; six waves
+// spill or serialise the loads: 3 to 7 % slower). Twice the waves outweigh that t
+// neighbours' spinors and links are read from L2: the FP16 operator on 24^4 with
+// one field 24.3 -> 22.0 us, 28 x 15 x 22 x 33 28.7 -> 24.7 us, 16^4 10.3 -> 6.9
+// us; a solve with FP16 inner iterations on 16^3 x 32 7.9 -> 7.0 ms.
+template <int CGM, typename T, int RB, bool ONE>
 constexpr int march_waves_per_eu() {
+  if (ONE) return sizeof(T) == 2 && CGM == kCgNone ? 5 : 1;
   return RB == 1 && sizeof(typename Packed<T>::R) == 4 && CGM != kCgNone ? 3 : 1;
 }
 
-template <typename T, bool C12, int MAXT, int RB, int CGM, bool BUF>
+template <typename T, bool C12, int MAXT, int RB, int CGM, bool BUF, bool ONE>
 __global__ __launch_bounds__(MAXT)
-__attribute__((amdgpu_waves_per_eu(march_waves_per_eu<CGM, T, RB>()))) void dslash_march_kernel(
+__attribute__((amdgpu_waves_per_eu(march_waves_per_eu<CGM, T, RB, ONE>()))) void dslash_march_kernel(
     const typename Packed<T>::S* __restrict__ in, typename Packed<T>::S* __restrict__ out,
     const typename Packed<T>::L* __restrict__ links, Geo geo, Diag<typename Packed<T>::R> diags,
     long stride, int gamma5, MarchParams p, CgFuse cgf) {
@@ -211,7 +220,8 @@ __attribute__((amdgpu_waves_per_eu(march_waves_per_eu<CGM, T, RB>()))) void dsla
   const int n = geo.X * p.ny;  // sites per tile == lanes per lane group
   const int slot = static_cast<int>(threadIdx.x) / n;
   // slice (buffer f, right-hand side r) of this lane group
-  SV* const base = reinterpret_cast<SV*>(smem) + slot * 2 * RB * kPlanes * n;
+  constexpr int kSlices = ONE ? 1 : 2;
+  SV* const base = reinterpret_cast<SV*>(smem) + slot * kSlices * RB * kPlanes * n;
   const long V = geo.V;
 
   const int tid = static_cast<int>(threadIdx.x) - slot * n;
@@ -245,7 +255,7 @@ __attribute__((amdgpu_waves_per_eu(march_waves_per_eu<CGM, T, RB>()))) void dsla
   const int tblk = b / (p.ytiles * geo.Z);
   const int y = yt * p.ny + yl;
   const int t0 = tblk * p.tb;
-  const int t1 = min(t0 + p.tb, geo.T);
+  const int t1 = ONE ? t0 + 1 : min(t0 + p.tb, geo.T);
 
   const int s0 = xl + geo.X * (y + geo.Y * z);  // the site at t = 0
   // LDS slots of the in-tile x and y neighbours
@@ -280,7 +290,7 @@ __attribute__((amdgpu_waves_per_eu(march_waves_per_eu<CGM, T, RB>()))) void dsla
   // its lanes (an order fixed by the tile size, which the lattice fixes);
   // after the prologue's barrier every lane adds the wave sums in order, so
   // all lanes of all workgroups get the same alpha
-  double* cgs = reinterpret_cast<double*>(reinterpret_cast<SV*>(smem) + p.gw * 2 * RB * kPlanes * n) +
+  double* cgs = reinterpret_cast<double*>(reinterpret_cast<SV*>(smem) + p.gw * kSlices * RB * kPlanes * n) +
                 slot * RB * kCgLds;
   double alpha[RB];
 #pragma unroll
@@ -315,7 +325,7 @@ __attribute__((amdgpu_waves_per_eu(march_waves_per_eu<CGM, T, RB>()))) void dsla
     for (int r = 0; r < RB; ++r) {
       cx<R> psi[12];
       load_spinor(inr[r], V, st, psi);
-      lds_store_spinor(base + (2 * r) * kPlanes * n, n, tid, psi);
+      lds_store_spinor(base + (kSlices * r) * kPlanes * n, n, tid, psi);
     }
   }
   __syncthreads();
@@ -337,18 +347,18 @@ __attribute__((amdgpu_waves_per_eu(march_waves_per_eu<CGM, T, RB>()))) void dsla
     }
   }
 
-  for (int t = t0; t < t1; ++t) {
-    const int f = (t - t0) & 1;  // the buffer holding slice t
+  for (int t = t0; t < (ONE ? t0 + 1 : t1); ++t) {
+    const int f = ONE ? 0 : (t - t0) & 1;  // the buffer holding slice t
     SV* cur[RB];
     SV* nxt[RB];
 #pragma unroll
     for (int r = 0; r < RB; ++r) {
-      cur[r] = base + (2 * r + f) * kPlanes * n;
-      nxt[r] = base + (2 * r + (f ^ 1)) * kPlanes * n;
+      cur[r] = base + (kSlices * r + f) * kPlanes * n;
+      nxt[r] = base + (kSlices * r + (ONE ? 0 : f ^ 1)) * kPlanes * n;
     }
     const int st = s0 + t * geo.XYZ;
     const int sn = t + 1 == geo.T ? s0 : st + geo.XYZ;  // the site at t+1
-    const bool more = t + 1 < t1;
+    const bool more = !ONE && t + 1 < t1;
 
     // Slice t+1: this workgroup's own spinors (forward t hop, next LDS
     // slice) and, in the same window, the z and off-tile y hops of t+1,
@@ -414,7 +424,7 @@ __attribute__((amdgpu_waves_per_eu(march_waves_per_eu<CGM, T, RB>()))) void dsla
     for (int r = 0; r < RB; ++r)
 #pragma unroll
       for (int c = 0; c < 12; ++c) acc[r][c] = nacc[r][c];
-    __syncthreads();
+    if (!ONE || CGM != kCgNone) __syncthreads();
     if constexpr (CGM != kCgNone) {
       // the squared norm of this tile slice (Q p or r): its waves in order (the next write to these
       // words is two steps on, behind the next barrier)
@@ -459,18 +469,16 @@ struct MarchCost {
   int waves, waves2;
   double prologue, prologue2, tail, rb2;
 };
-MarchCost march_cost(int prec, bool fused) {
+MarchCost march_cost(int prec) {
   if (prec == WD_FP64) return {4, 0, 0.8, 0.0, -1.0, 0.0};
   if (prec == WD_FP32) return {8, 8, 0.4, 0.7, -1.0, 1.2};
-  // the fused CG work adds a reduction to each workgroup's start (solves on 24^4:
-  // 14.74 ms with one slice per workgroup, which 0.4 would choose, 14.10 with two)
-  return {12, 0, fused ? 0.6 : 0.4, 0.0, 0.5, 0.0};
+  return {12, 0, 0.4, 0.0, 0.5, 0.0};
 }
 
 // Geometry of the t-marching kernel for a lattice, with the default launch
 // choice, or ny = 0 if it does not apply (x rows longer than a workgroup, or
 // too few sites per tile).
-MarchParams march_params(const Geo& geo, int prec, int nrhs, bool fused = false) {
+MarchParams march_params(const Geo& geo, int prec, int nrhs) {
   MarchParams p{0, 0, 0, 0, 0, nrhs, 1, 1, 0u, 0u};
   const size_t real_bytes = real_bytes_of(prec);
   if (geo.X > kMarchMaxThreads) return p;
@@ -482,9 +490,15 @@ MarchParams march_params(const Geo& geo, int prec, int nrhs, bool fused = false)
   p.ytiles = geo.Y / ny;
   const int n = geo.X * ny;
   const int waves = (n + 63) / 64;
-  const MarchCost mc = march_cost(prec, fused);
+  const MarchCost mc = march_cost(prec);
   double best = 0.0;
-  for (int rb = 1; rb <= 2; ++rb) {
+  // FP16 storage: one slice per workgroup (its own kernel), unless one or two
+  // fields and their links outgrow the 256 MB cache that serves the t neighbours
+  // then (about 2^20 sites; us, one slice / best longer march: 24^3 x 48 37.5 /
+  // 41.2, 32^4 59.9 / 56.8, 32^4 with two fields 99.2 / 98.1)
+  const bool single = prec == WD_FP16 && (geo.V < (1 << 20) || nrhs > 2);
+  if (single) p.tb = 1;
+  for (int rb = 1; rb <= 2 && !single; ++rb) {
     const size_t lds = rb * march_lds_bytes(n, real_bytes);
     if (rb == 2 && (mc.waves2 == 0 || nrhs % 2 != 0 || lds > kLdsBytes)) break;
     const int by_waves = (rb == 1 ? mc.waves : mc.waves2) / waves;
@@ -514,7 +528,7 @@ MarchParams march_params(const Geo& geo, int prec, int nrhs, bool fused = false)
   return p;
 }
 
-template <typename T, bool C12, int MAXT, int RB, int CGM, bool BUF>
+template <typename T, bool C12, int MAXT, int RB, int CGM, bool BUF, bool ONE = false>
 hipError_t launch_march_t(const void* in, void* out, const void* links, const Geo& geo,
                           const Diag<typename Packed<T>::R>& diag, long stride, int g5,
                           MarchParams p, const CgFuse& f, hipStream_t st) {
@@ -522,14 +536,14 @@ hipError_t launch_march_t(const void* in, void* out, const void* links, const Ge
   using LV = typename Packed<T>::L;
   using R = typename Packed<T>::R;
   const int n = geo.X * p.ny;
-  size_t lds = static_cast<size_t>(p.gw) * RB * march_lds_bytes(n, sizeof(R));
+  size_t lds = static_cast<size_t>(p.gw) * RB * march_lds_bytes(n, sizeof(R)) / (ONE ? 2 : 1);
   if (CGM != kCgNone) lds += static_cast<size_t>(p.gw) * RB * kCgLds * sizeof(double);
   if (lds > kLdsBytes) return hipErrorInvalidValue;
   // raise the kernel's dynamic LDS limit once to the whole LDS of a CU
   static std::atomic<int> attr_set{0};
   if (!attr_set.load(std::memory_order_acquire)) {
     hipError_t e = hipFuncSetAttribute(
-        reinterpret_cast<const void*>(&dslash_march_kernel<T, C12, MAXT, RB, CGM, BUF>),
+        reinterpret_cast<const void*>(&dslash_march_kernel<T, C12, MAXT, RB, CGM, BUF, ONE>),
         hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kLdsBytes));
     if (e != hipSuccess) return e;
     attr_set.store(1, std::memory_order_release);
@@ -538,7 +552,7 @@ hipError_t launch_march_t(const void* in, void* out, const void* links, const Ge
   const int eighth = (p.nb + kNumXcd - 1) / kNumXcd;  // larger groups mean the same
   if (p.group > eighth) p.group = eighth;
   const unsigned grid = static_cast<unsigned>(p.group == eighth ? eighth * kNumXcd : p.nb);
-  dslash_march_kernel<T, C12, MAXT, RB, CGM, BUF><<<grid, p.gw * n, lds, st>>>(
+  dslash_march_kernel<T, C12, MAXT, RB, CGM, BUF, ONE><<<grid, p.gw * n, lds, st>>>(
       static_cast<const SV*>(in), static_cast<SV*>(out), static_cast<const LV*>(links), geo, diag,
       stride, g5, p, f);
   return hipGetLastError();
@@ -555,6 +569,13 @@ hipError_t launch_march_b(const void* in, void* out, const void* links, const Ge
     if (p.gw > 1)
       return launch_march_t<T, C12, kMarchMultiThreads, 1, CGM, BUF>(in, out, links, geo, diag, stride,
                                                                     g5, p, f, st);
+    // FP64 keeps the one kernel: it is bound by the loads that a second slice
+    // saves (16^4 15.0 us with its best march, 15.4 with single slices)
+    if constexpr (BUF) {
+      if (p.tb == 1)
+        return launch_march_t<T, C12, kMarchMaxThreads, 1, CGM, BUF, true>(in, out, links, geo, diag, stride,
+                                                                          g5, p, f, st);
+    }
   }
   return launch_march_t<T, C12, kMarchMaxThreads, 1, CGM, BUF>(in, out, links, geo, diag, stride, g5, p,
                                                               f, st);
@@ -596,10 +617,13 @@ hipError_t launch_split(const void* in, void* out, const void* links, const Geo&
 // one does not apply, in launches too small to fill the chip with marches, and
 // in somewhat larger ones on lattices whose tiles leave lanes of their waves
 // idle (X * ny not near a multiple of 64). Measured on MI355X, t-marching
-// against split (us): 12^4 FP64 12.9 / 8.3; 15 x 9 x 14 x 21 (135 of 192 lanes)
-// FP32 12.0 / 8.6, with 12 fields 39.6 / 38.6; 20^4 (200 of 256) FP64 with two
-// fields 54.7 / 52.7, FP32 21.9 / 19.1, FP16 16.2 / 16.8; but 16^4 (whole waves)
-// FP64 15.0 / 16.6, 16^3 x 32 FP32 13.2 / 14.3 and FP16 9.6 / 13.3.
+// against split (us): 12^4 FP64 8.1 / 6.5; 15 x 9 x 14 x 21 (135 of 192 lanes)
+// FP32 8.9 / 6.7, with 12 fields 46.4 / 38.6, FP16 8.4 / 6.6, with four fields
+// 13.1 / 15.9; 20^4 (200 of 256) FP64 with two fields 54.6 / 52.8, FP32 21.2 /
+// 19.0, FP16 14.0 / 16.3; 28 x 15 x 22 x 33 (420 of 576) FP64 with 12 fields 847
+// / 780, FP32 with four 96 / 124; 65 x 5 x 12 x 20 (65 of 128) FP16 with four
+// fields 30.5 / 28.1; but 16^4 (whole waves) FP64 14.8 / 16.5, 16^3 x 32 FP32
+// 13.0 / 14.4 and FP16 8.9 / 13.0.
 bool use_split(const Geo& geo, const MarchParams& p, int prec) {
   if (p.ny == 0) return true;
   const long work = static_cast<long>(geo.V) * p.nrhs;
@@ -607,8 +631,8 @@ bool use_split(const Geo& geo, const MarchParams& p, int prec) {
   const int n = geo.X * p.ny;
   const int lanes = (n + 63) / 64 * 64;
   if (10 * n >= 9 * lanes) return false;  // at least nine tenths of the lanes at work
-  if (prec == WD_FP16) return work <= (10 * n < 6 * lanes ? 800000 : 100000);
-  return work <= 640000;
+  if (prec == WD_FP16) return work <= (10 * n < 6 * lanes ? 800000 : 65536);
+  return work <= (prec == WD_FP64 && 4 * n <= 3 * lanes ? 4000000 : 640000);
 }
 
 // Whether the t-marching tiles are whole waves (what its fused CG work needs).
@@ -645,7 +669,7 @@ hipError_t launch_typed(const wd_gauge* g, const void* in, void* out, const Geo&
     diag.idx[k] = fields ? fields[k] : k;
   }
   const long stride = spinor_units<T>(geo.V);  // 16-B elements per field
-  MarchParams p = march_params(geo, g->prec, nrhs, cg != nullptr);
+  MarchParams p = march_params(geo, g->prec, nrhs);
   // byte sizes for buffer-resource access, or 0 where a field reaches 4 GiB
   const unsigned long sbytes = static_cast<unsigned long>(stride) * 16;
   p.link_bytes = g->link_bytes < (1ul << 32) ? static_cast<unsigned>(g->link_bytes) : 0u;

@@ -125,7 +125,7 @@ def test_split_kernel_links_beyond_4_gib():
 @pytest.mark.parametrize("dims", [
     (8, 8, 8, 4),    # split kernel, slices of 32 sites
     (9, 5, 7, 5),    # split kernel, a last slice of 7 sites
-    (16, 16, 9, 8),  # t-marching tiles, tile slices, the update fused in FP64 too
+    (16, 16, 9, 8),  # t-marching tiles, tile slices (one per workgroup in FP16), the update fused in FP64 too
 ], ids=lambda d: "x".join(map(str, d)))
 def test_cg_fused_kernels(dims, inner):
     """Solves in each of the fused kernels: the oracle's true residual, and the

@@ -13,6 +13,7 @@
 #include <algorithm>
 #include <atomic>
 #include <cmath>
+#include <type_traits>
 
 #include "blas.h"
 #include "cg_site.h"
@@ -69,14 +70,14 @@ __device__ __forceinline__ int tile_of_block(int group, int nb) {
 // t-marching kernel.
 //
 // A workgroup owns a tile of X x NY sites (whole x rows) at one z and walks
-// t0 .. t1-1. The tile's spinors at the current t sit in LDS (double
-// buffered), so the x and in-tile y neighbours are read from LDS; the t
-// neighbours come from the march itself: psi(t+1) is the workgroup's own
-// next slice, and the backward t hop of step t+1, U_t(t)^dag P+ psi(t), is
-// built from data of step t and carried in the accumulator. The z hops and
-// the y hops that leave the tile need other workgroups' sites; they are done
-// one step early, while the workgroups that own those sites load the same
-// slice, so their lines are still in L2.
+// t0 .. t1-1. The tile's spinors at the current t sit in LDS, so the x and
+// in-tile y neighbours are read from LDS; the t neighbours come from the march
+// itself: psi(t+1) is the workgroup's own next slice, and the backward t hop of
+// step t+1, U_t(t)^dag P+ psi(t), is built from data of step t and carried. The
+// z hops and the y hops that leave the tile need other workgroups' sites; in
+// large FP64 tiles they are done one step early, while the workgroups that own
+// those sites load the same slice, so their lines are still in L2. Which
+// variant runs where: launch_march_b.
 // ---------------------------------------------------------------------------
 
 struct MarchParams {
@@ -180,6 +181,18 @@ __device__ __forceinline__ void outer_hops(const SA (&in)[RB], const LA& links, 
 // 4 waves) and the per-wave sums of <p, A p>.
 constexpr int kCgLds = 2 * 4 + 4;
 
+// Variants of the march (KIND):
+//  kOuterAhead  two LDS slices; the outer hops (z, and y out of the tile) of t+1
+//               are done in step t, into a second accumulator.
+//  kOuterNow    two LDS slices; the outer hops of t are done at the start of step
+//               t, and only the backward t hop of t+1, before its reconstruction,
+//               is carried: 48 registers fewer in FP64 per field, 24 in FP32.
+//  kOneBuffer   kOuterNow with one LDS slice: psi(t+1) is loaded again when step t
+//               is done with the slice, which costs a second barrier.
+//  kOneSlice    marches of a single slice: nothing to carry, one LDS slice.
+// Every site's hops are added in the same order in all of them.
+constexpr int kOuterAhead = 0, kOuterNow = 1, kOneBuffer = 2, kOneSlice = 3;
+
 // MAXT: launch bound. A workgroup holds p.gw groups of n = X * ny lanes of
 // one tile; each lane carries RB right-hand sides (links loaded once for
 // all), each with its own two LDS slices. The LDS slices hold spinors in the
@@ -200,15 +213,15 @@ constexpr int kCgLds = 2 * 4 + 4;
 // neighbours' spinors and links are read from L2: the FP16 operator on 24^4 with
 // one field 24.3 -> 22.0 us, 28 x 15 x 22 x 33 28.7 -> 24.7 us, 16^4 10.3 -> 6.9
 // us; a solve with FP16 inner iterations on 16^3 x 32 7.9 -> 7.0 ms.
-template <int CGM, typename T, int RB, bool ONE>
+template <int CGM, typename T, int RB, int KIND>
 constexpr int march_waves_per_eu() {
-  if (ONE) return sizeof(T) == 2 && CGM == kCgNone ? 5 : 1;
+    if (KIND == kOneSlice) return sizeof(T) == 2 && CGM == kCgNone ? 5 : 1;
   return RB == 1 && sizeof(typename Packed<T>::R) == 4 && CGM != kCgNone ? 3 : 1;
 }
 
-template <typename T, bool C12, int MAXT, int RB, int CGM, bool BUF, bool ONE>
+template <typename T, bool C12, int MAXT, int RB, int CGM, bool BUF, int KIND>
 __global__ __launch_bounds__(MAXT)
-__attribute__((amdgpu_waves_per_eu(march_waves_per_eu<CGM, T, RB, ONE>()))) void dslash_march_kernel(
+__attribute__((amdgpu_waves_per_eu(march_waves_per_eu<CGM, T, RB, KIND>()))) void dslash_march_kernel(
     const typename Packed<T>::S* __restrict__ in, typename Packed<T>::S* __restrict__ out,
     const typename Packed<T>::L* __restrict__ links, Geo geo, Diag<typename Packed<T>::R> diags,
     long stride, int gamma5, MarchParams p, CgFuse cgf) {
@@ -220,7 +233,11 @@ __attribute__((amdgpu_waves_per_eu(march_waves_per_eu<CGM, T, RB, ONE>()))) void
   const int n = geo.X * p.ny;  // sites per tile == lanes per lane group
   const int slot = static_cast<int>(threadIdx.x) / n;
   // slice (buffer f, right-hand side r) of this lane group
-  constexpr int kSlices = ONE ? 1 : 2;
+  constexpr bool ONE = KIND == kOneSlice;
+  constexpr bool NOW = KIND == kOuterNow || KIND == kOneBuffer;
+  constexpr bool RELOAD = KIND == kOneBuffer;
+  constexpr int kSlices = ONE || RELOAD ? 1 : 2;
+  cx<R> gb[RB][6];  // NOW: the carried backward t hop, before its reconstruction
   SV* const base = reinterpret_cast<SV*>(smem) + slot * kSlices * RB * kPlanes * n;
   const long V = geo.V;
 
@@ -319,8 +336,20 @@ __attribute__((amdgpu_waves_per_eu(march_waves_per_eu<CGM, T, RB, ONE>()))) void
   {
     const int tm = t0 == 0 ? geo.T - 1 : t0 - 1;
     const int st = s0 + t0 * geo.XYZ;
-    outer_hops<C12>(inr, lk, V, st, dzp, dzm, y_fwd_out, dyp, y_bwd_out, dym, acc);
-    hop_rb<3, +1, C12>(inr, lk, V, s0 + tm * geo.XYZ, s0 + tm * geo.XYZ, acc);
+    if constexpr (NOW) {
+      cx<R> u[9];
+      load_link<C12>(lk, V, 3, s0 + tm * geo.XYZ, u);
+#pragma unroll
+      for (int r = 0; r < RB; ++r) {
+        cx<R> psi[12], h[6];
+        load_spinor(inr[r], V, s0 + tm * geo.XYZ, psi);
+        project<3, +1>(psi, h);
+        su3_mul<true>(u, h, gb[r]);
+      }
+    } else {
+      outer_hops<C12>(inr, lk, V, st, dzp, dzm, y_fwd_out, dyp, y_bwd_out, dym, acc);
+      hop_rb<3, +1, C12>(inr, lk, V, s0 + tm * geo.XYZ, s0 + tm * geo.XYZ, acc);
+    }
 #pragma unroll
     for (int r = 0; r < RB; ++r) {
       cx<R> psi[12];
@@ -348,13 +377,13 @@ __attribute__((amdgpu_waves_per_eu(march_waves_per_eu<CGM, T, RB, ONE>()))) void
   }
 
   for (int t = t0; t < (ONE ? t0 + 1 : t1); ++t) {
-    const int f = ONE ? 0 : (t - t0) & 1;  // the buffer holding slice t
+    const int f = ONE || RELOAD ? 0 : (t - t0) & 1;  // the buffer holding slice t
     SV* cur[RB];
     SV* nxt[RB];
 #pragma unroll
     for (int r = 0; r < RB; ++r) {
       cur[r] = base + (kSlices * r + f) * kPlanes * n;
-      nxt[r] = base + (kSlices * r + (ONE ? 0 : f ^ 1)) * kPlanes * n;
+      nxt[r] = base + (kSlices * r + (ONE || RELOAD ? 0 : f ^ 1)) * kPlanes * n;
     }
     const int st = s0 + t * geo.XYZ;
     const int sn = t + 1 == geo.T ? s0 : st + geo.XYZ;  // the site at t+1
@@ -365,6 +394,15 @@ __attribute__((amdgpu_waves_per_eu(march_waves_per_eu<CGM, T, RB, ONE>()))) void
     // whose spinors other workgroups are loading as their own slice now.
     // U_t(t) serves the forward t hop of t and, from registers, the backward
     // t hop of t+1: no other workgroup reads it
+    if constexpr (NOW) {
+#pragma unroll
+      for (int r = 0; r < RB; ++r)
+#pragma unroll
+        for (int c = 0; c < 12; ++c) acc[r][c] = {R(0), R(0)};
+      outer_hops<C12>(inr, lk, V, st, dzp, dzm, y_fwd_out, dyp, y_bwd_out, dym, acc);
+#pragma unroll
+      for (int r = 0; r < RB; ++r) reconstruct_add<3, +1>(gb[r], acc[r]);
+    }
     cx<R> ut[9];
     load_link<C12, kUtNt>(lk, V, 3, st, ut);
     cx<R> nacc[RB][12];
@@ -376,9 +414,9 @@ __attribute__((amdgpu_waves_per_eu(march_waves_per_eu<CGM, T, RB, ONE>()))) void
     for (int r = 0; r < RB; ++r) {
       cx<R> psi[12];
       load_spinor(inr[r], V, sn, psi);
-      if (more) {
+      if (!RELOAD && more) {
         lds_store_spinor(nxt[r], n, tid, psi);
-        if (r == 0) outer_hops<C12>(inr, lk, V, sn, dzp, dzm, y_fwd_out, dyp, y_bwd_out, dym, nacc);
+        if (!NOW && r == 0) outer_hops<C12>(inr, lk, V, sn, dzp, dzm, y_fwd_out, dyp, y_bwd_out, dym, nacc);
       }
       cx<R> h[6], g[6];
       project<3, -1>(psi, h);
@@ -413,17 +451,32 @@ __attribute__((amdgpu_waves_per_eu(march_waves_per_eu<CGM, T, RB, ONE>()))) void
       } else {
         store_spinor(outr[r], V, st, o);
       }
-      if (more) {
+      if constexpr (NOW) {
+        cx<R> h[6];
+        project<3, +1>(psi, h);
+        su3_mul<true>(ut, h, gb[r]);
+      } else if (more) {
         cx<R> h[6], g[6];
         project<3, +1>(psi, h);
         su3_mul<true>(ut, h, g);
         reconstruct_add<3, +1>(g, nacc[r]);
       }
     }
+    if constexpr (RELOAD) {
+      if (more) {
+        cx<R> psn[RB][12];
 #pragma unroll
-    for (int r = 0; r < RB; ++r)
+        for (int r = 0; r < RB; ++r) load_spinor(inr[r], V, sn, psn[r]);
+        __syncthreads();
 #pragma unroll
-      for (int c = 0; c < 12; ++c) acc[r][c] = nacc[r][c];
+        for (int r = 0; r < RB; ++r) lds_store_spinor(nxt[r], n, tid, psn[r]);
+      }
+    } else if constexpr (!NOW) {
+#pragma unroll
+      for (int r = 0; r < RB; ++r)
+#pragma unroll
+        for (int c = 0; c < 12; ++c) acc[r][c] = nacc[r][c];
+    }
     if (!ONE || CGM != kCgNone) __syncthreads();
     if constexpr (CGM != kCgNone) {
       // the squared norm of this tile slice (Q p or r): its waves in order (the next write to these
@@ -441,6 +494,13 @@ __attribute__((amdgpu_waves_per_eu(march_waves_per_eu<CGM, T, RB, ONE>()))) void
   }
 }
 
+template <int N>
+constexpr std::integral_constant<int, N> kInt{};
+
+// Whether two workgroups of n FP64 lanes, or of n FP32 lanes with two right-hand
+// sides each, fit a CU's LDS with two slices per workgroup.
+bool two_workgroups(int n) { return n <= 208; }
+
 size_t march_lds_bytes(int threads, size_t real_bytes) {
   return 2 * 24 * real_bytes * static_cast<size_t>(threads);  // two spinor slices
 }
@@ -456,22 +516,23 @@ size_t real_bytes_of(int prec) { return prec == WD_FP64 ? 8 : 4; }
 // workgroups are short and uneven, the last round costs half of one on average.
 // rb2: the cost of a slice of two right-hand sides per lane in a launch of half
 // the workgroups.
-// Fitted on MI355X to every split of t timed on 12 lattices (16^4 to 32^3 x 64,
-// among them 28 x 15 x 22 x 33 and 9 x 33 x 12 x 20) with 1 to 16 right-hand
-// sides: the choice is on average 0.4 % (FP64), 0.6 % (FP32) and 1.0 % (FP16)
-// slower than the best split timed, where one resident round of workgroups
+// Fitted on MI355X to every split of t timed on 14 lattices (8^2 x 16 x 64 to
+// 32^3 x 64, among them 28 x 15 x 22 x 33 and 9 x 33 x 12 x 20) with 1 to 16
+// right-hand sides (two: tiles of which two workgroups fit, where three waves per
+// SIMD run with two per lane): the choice is on average 1.5 % (FP64), 1.7 % (FP32) and 1.0 %
+// (FP16) slower than the best split timed, where one resident round of workgroups
 // whatever its last round leaves idle was 14, 24 and 24 % slower: 24^3 x 48 with
-// 12 FP32 fields 757 -> 541 us, 24^4 with 4 FP64 fields 363 -> 238 us, 24^4 with
-// one FP16 field 29.0 -> 24.3 us. Two right-hand sides per lane pay in FP32
-// (86 against 105 us for 4 fields on 24^4), not with FP16 storage, whose waves
-// they halve; several lane groups per workgroup never were the fastest.
+// 12 FP32 fields 757 -> 535 us, 24^4 with 4 FP64 fields 363 -> 218 us. Two
+// right-hand sides per lane pay in FP32 (87 against 105 us for 4 fields on 24^4),
+// not with FP16 storage, whose waves they halve; several lane groups per
+// workgroup never were the fastest.
 struct MarchCost {
   int waves, waves2;
   double prologue, prologue2, tail, rb2;
 };
-MarchCost march_cost(int prec) {
-  if (prec == WD_FP64) return {4, 0, 0.8, 0.0, -1.0, 0.0};
-  if (prec == WD_FP32) return {8, 8, 0.4, 0.7, -1.0, 1.2};
+MarchCost march_cost(int prec, bool two) {
+  if (prec == WD_FP64) return {8, 0, 0.8, 0.0, -1.0, 0.0};
+  if (prec == WD_FP32) return {8, two ? 12 : 8, 0.4, 0.7, -1.0, 1.2};
   return {12, 0, 0.4, 0.0, 0.5, 0.0};
 }
 
@@ -490,7 +551,7 @@ MarchParams march_params(const Geo& geo, int prec, int nrhs) {
   p.ytiles = geo.Y / ny;
   const int n = geo.X * ny;
   const int waves = (n + 63) / 64;
-  const MarchCost mc = march_cost(prec);
+  const MarchCost mc = march_cost(prec, two_workgroups(n));
   double best = 0.0;
   // FP16 storage: one slice per workgroup (its own kernel), unless one or two
   // fields and their links outgrow the 256 MB cache that serves the t neighbours
@@ -499,7 +560,7 @@ MarchParams march_params(const Geo& geo, int prec, int nrhs) {
   const bool single = prec == WD_FP16 && (geo.V < (1 << 20) || nrhs > 2);
   if (single) p.tb = 1;
   for (int rb = 1; rb <= 2 && !single; ++rb) {
-    const size_t lds = rb * march_lds_bytes(n, real_bytes);
+    const size_t lds = march_lds_bytes(n, real_bytes) * (rb == 2 && two_workgroups(n) ? 2 : 1);  // one buffer per field
     if (rb == 2 && (mc.waves2 == 0 || nrhs % 2 != 0 || lds > kLdsBytes)) break;
     const int by_waves = (rb == 1 ? mc.waves : mc.waves2) / waves;
     const int by_lds = static_cast<int>(kLdsBytes / lds);
@@ -528,7 +589,7 @@ MarchParams march_params(const Geo& geo, int prec, int nrhs) {
   return p;
 }
 
-template <typename T, bool C12, int MAXT, int RB, int CGM, bool BUF, bool ONE = false>
+template <typename T, bool C12, int MAXT, int RB, int CGM, bool BUF, int KIND>
 hipError_t launch_march_t(const void* in, void* out, const void* links, const Geo& geo,
                           const Diag<typename Packed<T>::R>& diag, long stride, int g5,
                           MarchParams p, const CgFuse& f, hipStream_t st) {
@@ -536,14 +597,14 @@ hipError_t launch_march_t(const void* in, void* out, const void* links, const Ge
   using LV = typename Packed<T>::L;
   using R = typename Packed<T>::R;
   const int n = geo.X * p.ny;
-  size_t lds = static_cast<size_t>(p.gw) * RB * march_lds_bytes(n, sizeof(R)) / (ONE ? 2 : 1);
+  size_t lds = static_cast<size_t>(p.gw) * RB * march_lds_bytes(n, sizeof(R)) / (KIND == kOuterAhead || KIND == kOuterNow ? 1 : 2);
   if (CGM != kCgNone) lds += static_cast<size_t>(p.gw) * RB * kCgLds * sizeof(double);
   if (lds > kLdsBytes) return hipErrorInvalidValue;
   // raise the kernel's dynamic LDS limit once to the whole LDS of a CU
   static std::atomic<int> attr_set{0};
   if (!attr_set.load(std::memory_order_acquire)) {
     hipError_t e = hipFuncSetAttribute(
-        reinterpret_cast<const void*>(&dslash_march_kernel<T, C12, MAXT, RB, CGM, BUF, ONE>),
+        reinterpret_cast<const void*>(&dslash_march_kernel<T, C12, MAXT, RB, CGM, BUF, KIND>),
         hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kLdsBytes));
     if (e != hipSuccess) return e;
     attr_set.store(1, std::memory_order_release);
@@ -552,33 +613,49 @@ hipError_t launch_march_t(const void* in, void* out, const void* links, const Ge
   const int eighth = (p.nb + kNumXcd - 1) / kNumXcd;  // larger groups mean the same
   if (p.group > eighth) p.group = eighth;
   const unsigned grid = static_cast<unsigned>(p.group == eighth ? eighth * kNumXcd : p.nb);
-  dslash_march_kernel<T, C12, MAXT, RB, CGM, BUF, ONE><<<grid, p.gw * n, lds, st>>>(
+  dslash_march_kernel<T, C12, MAXT, RB, CGM, BUF, KIND><<<grid, p.gw * n, lds, st>>>(
       static_cast<const SV*>(in), static_cast<SV*>(out), static_cast<const LV*>(links), geo, diag,
       stride, g5, p, f);
   return hipGetLastError();
 }
 
+// Which variant of the march runs. What decides is how many waves a CU holds;
+// two LDS slices of two workgroups fit up to 208 lanes per tile (FP64, or FP32
+// with two right-hand sides per lane; half that each with one).
+//  - FP64: kOuterAhead needs 280 registers (one wave per SIMD), kOuterNow 204 to
+//    238 (two). Up to 208 lanes kOuterNow is the faster one: 24^4 with four fields
+//    235 -> 209 us, 28 x 15 x 22 x 33 71 -> 65 and with four 287 -> 222, with
+//    12-real links 24^3 x 48 131 -> 108. Beyond, LDS holds one workgroup either
+//    way and the outer hops must meet their owners' loads in L2: 32^3 x 64 357 us
+//    ahead, 389 now, 16^3 x 32 26.0 and 27.9.
+//  - FP32 arithmetic: kOuterNow (24^3 x 48 with three fields 174 -> 161 us, 28 x 15
+//    x 22 x 33 43 -> 35, 32^4 97 -> 95). Two right-hand sides per lane beyond 208
+//    lanes: kOneBuffer, which lets a second workgroup in (32^4 with two fields
+//    176 -> 161 us, with four 316 -> 281, 16^3 x 32 with four 40.3 -> 36.4).
 template <typename T, bool C12, int CGM, bool BUF>
 hipError_t launch_march_b(const void* in, void* out, const void* links, const Geo& geo,
                           const Diag<typename Packed<T>::R>& diag, long stride, int g5,
                           const MarchParams& p, const CgFuse& f, hipStream_t st) {
+  const auto run = [&](auto maxt, auto rb, auto kind) {
+    return launch_march_t<T, C12, decltype(maxt)::value, decltype(rb)::value, CGM, BUF, decltype(kind)::value>(
+        in, out, links, geo, diag, stride, g5, p, f, st);
+  };
+  const bool two = two_workgroups(geo.X * p.ny);
   if constexpr (sizeof(typename Packed<T>::R) == 4) {
     if (p.rb == 2)  // two right-hand sides per lane: one lane group per workgroup
-      return launch_march_t<T, C12, kMarchMaxThreads, 2, CGM, BUF>(in, out, links, geo, diag, stride, g5,
-                                                                  p, f, st);
-    if (p.gw > 1)
-      return launch_march_t<T, C12, kMarchMultiThreads, 1, CGM, BUF>(in, out, links, geo, diag, stride,
-                                                                    g5, p, f, st);
-    // FP64 keeps the one kernel: it is bound by the loads that a second slice
-    // saves (16^4 15.0 us with its best march, 15.4 with single slices)
+      return two ? run(kInt<kMarchMaxThreads>, kInt<2>, kInt<kOuterNow>)
+                 : run(kInt<kMarchMaxThreads>, kInt<2>, kInt<kOneBuffer>);
+    if (p.gw > 1) return run(kInt<kMarchMultiThreads>, kInt<1>, kInt<kOuterNow>);
+    // FP64 keeps no kernel for single slices: it is bound by the loads that a
+    // second slice saves (16^4 15.0 us with its best march, 15.4 with single ones)
     if constexpr (BUF) {
-      if (p.tb == 1)
-        return launch_march_t<T, C12, kMarchMaxThreads, 1, CGM, BUF, true>(in, out, links, geo, diag, stride,
-                                                                          g5, p, f, st);
+      if (p.tb == 1) return run(kInt<kMarchMaxThreads>, kInt<1>, kInt<kOneSlice>);
     }
+    return run(kInt<kMarchMaxThreads>, kInt<1>, kInt<kOuterNow>);
+  } else {
+    return two ? run(kInt<kMarchMaxThreads>, kInt<1>, kInt<kOuterNow>)
+               : run(kInt<kMarchMaxThreads>, kInt<1>, kInt<kOuterAhead>);
   }
-  return launch_march_t<T, C12, kMarchMaxThreads, 1, CGM, BUF>(in, out, links, geo, diag, stride, g5, p,
-                                                              f, st);
 }
 
 // The operator reads its fields (and the plain operator also writes them)
@@ -618,12 +695,12 @@ hipError_t launch_split(const void* in, void* out, const void* links, const Geo&
 // in somewhat larger ones on lattices whose tiles leave lanes of their waves
 // idle (X * ny not near a multiple of 64). Measured on MI355X, t-marching
 // against split (us): 12^4 FP64 8.1 / 6.5; 15 x 9 x 14 x 21 (135 of 192 lanes)
-// FP32 8.9 / 6.7, with 12 fields 46.4 / 38.6, FP16 8.4 / 6.6, with four fields
-// 13.1 / 15.9; 20^4 (200 of 256) FP64 with two fields 54.6 / 52.8, FP32 21.2 /
-// 19.0, FP16 14.0 / 16.3; 28 x 15 x 22 x 33 (420 of 576) FP64 with 12 fields 847
-// / 780, FP32 with four 96 / 124; 65 x 5 x 12 x 20 (65 of 128) FP16 with four
-// fields 30.5 / 28.1; but 16^4 (whole waves) FP64 14.8 / 16.5, 16^3 x 32 FP32
-// 13.0 / 14.4 and FP16 8.9 / 13.0.
+// FP64 12.4 / 10.1, FP32 8.8 / 6.6, with 12 fields 41.9 / 38.0, FP16 8.4 / 6.6,
+// with four 13.1 / 15.9; 20^4 (200 of 256) FP64 with two fields 56.1 / 52.9, with
+// four 105 / 108, FP32 21.3 / 19.0, with two 31.7 / 28.9, FP16 14.0 / 16.3; 18^3 x
+// 36 (216 of 256) FP64 with two 71.0 / 77.8, FP32 36.8 / 38.4; 65 x 5 x 12 x 20
+// (65 of 128) with 12 FP64 fields 197 / 175, four FP16 ones 30.5 / 28.1; but 16^4
+// (whole waves) FP64 14.8 / 16.5, 16^3 x 32 FP32 13.0 / 14.4 and FP16 8.9 / 13.0.
 bool use_split(const Geo& geo, const MarchParams& p, int prec) {
   if (p.ny == 0) return true;
   const long work = static_cast<long>(geo.V) * p.nrhs;
@@ -631,8 +708,8 @@ bool use_split(const Geo& geo, const MarchParams& p, int prec) {
   const int n = geo.X * p.ny;
   const int lanes = (n + 63) / 64 * 64;
   if (10 * n >= 9 * lanes) return false;  // at least nine tenths of the lanes at work
-  if (prec == WD_FP16) return work <= (10 * n < 6 * lanes ? 800000 : 65536);
-  return work <= (prec == WD_FP64 && 4 * n <= 3 * lanes ? 4000000 : 640000);
+  if (10 * n < 6 * lanes) return work <= 800000;
+  return work <= (prec == WD_FP16 ? 65536 : 450000);
 }
 
 // Whether the t-marching tiles are whole waves (what its fused CG work needs).

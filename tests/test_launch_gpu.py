@@ -56,8 +56,8 @@ def apply_with(line, tmp_path, g, masses, src):
 ], ids=lambda d: "x".join(map(str, d)))
 def test_launch_choices_keep_bits(dims, prec, c12, nrhs, tmp_path):
     """The default launch against marches of one slice in hardware order, of
-    all slices with every XCD's workgroups contiguous, and a run length far
-    beyond the number of workgroups."""
+    three slices, of all slices with every XCD's workgroups contiguous, a run
+    length far beyond the number of workgroups, and two fields per lane."""
     print(f"case launch dims={dims} prec={prec} c12={c12} nrhs={nrhs}", flush=True)
     U = li.random_gauge(dims, 71)
     psis = li.gaussian_spinors(dims, [72 + k for k in range(nrhs)])
@@ -65,7 +65,11 @@ def test_launch_choices_keep_bits(dims, prec, c12, nrhs, tmp_path):
     g = DeviceGauge(U, PRECS[prec], c12)
     src = g.pack(psis, nrhs=nrhs)
     default = apply_with(None, tmp_path, g, masses, src)
-    for line in ("1 1 0 1", f"{dims[3]} 1 1 1", f"{dims[3]} 1 2147483647 1"):
+    three = min(3, dims[3])
+    lines = ["1 1 0 1", f"{three} 1 0 1", f"{dims[3]} 1 1 1", f"{dims[3]} 1 2147483647 1"]
+    if prec != "fp64" and nrhs % 2 == 0:  # two right-hand sides per lane
+        lines += ["1 1 0 2", f"{three} 1 0 2", f"{dims[3]} 1 1 2"]
+    for line in lines:
         other = apply_with(line, tmp_path, g, masses, src)
         torch.cuda.synchronize()
         assert torch.equal(default, other), line

@@ -539,7 +539,7 @@ MarchCost march_cost(int prec, bool two) {
 // Geometry of the t-marching kernel for a lattice, with the default launch
 // choice, or ny = 0 if it does not apply (x rows longer than a workgroup, or
 // too few sites per tile).
-MarchParams march_params(const Geo& geo, int prec, int nrhs) {
+MarchParams march_params(const Geo& geo, int prec, int nrhs, bool fused = false) {
   MarchParams p{0, 0, 0, 0, 0, nrhs, 1, 1, 0u, 0u};
   const size_t real_bytes = real_bytes_of(prec);
   if (geo.X > kMarchMaxThreads) return p;
@@ -553,6 +553,10 @@ MarchParams march_params(const Geo& geo, int prec, int nrhs) {
   const int waves = (n + 63) / 64;
   const MarchCost mc = march_cost(prec, two_workgroups(n));
   double best = 0.0;
+  // among equals the shorter march; in FP32 the fused CG work also takes one that
+  // costs up to 4 % more (24^4 with three fields: 54.1 ms per solve at 12 slices per
+  // workgroup, 50.2 at 6)
+  const double tie = fused && prec == WD_FP32 ? 1.04 : 1.0;
   // FP16 storage: one slice per workgroup (its own kernel), unless one or two
   // fields and their links outgrow the 256 MB cache that serves the t neighbours
   // then (about 2^20 sites; us, one slice / best longer march: 24^3 x 48 37.5 /
@@ -572,8 +576,8 @@ MarchParams march_params(const Geo& geo, int prec, int nrhs) {
       const double x = columns * nt / slots;
       const double rounds = mc.tail < 0.0 ? std::ceil(x) : std::max(1.0, x + mc.tail);
       const double cost = rounds * (tb + (rb == 1 ? mc.prologue : mc.prologue2)) * (rb == 1 ? 1.0 : mc.rb2);
-      if (p.tb == 0 || cost < best || (cost == best && rb == p.rb)) {
-        best = cost;
+      if (p.tb == 0 || cost < best || (cost <= best * tie && rb == p.rb)) {
+        best = p.tb == 0 ? cost : std::min(best, cost);
         p.tb = tb;
         p.rb = rb;
       }
@@ -631,7 +635,10 @@ hipError_t launch_march_t(const void* in, void* out, const void* links, const Ge
 //  - FP32 arithmetic: kOuterNow (24^3 x 48 with three fields 174 -> 161 us, 28 x 15
 //    x 22 x 33 43 -> 35, 32^4 97 -> 95). Two right-hand sides per lane beyond 208
 //    lanes: kOneBuffer, which lets a second workgroup in (32^4 with two fields
-//    176 -> 161 us, with four 316 -> 281, 16^3 x 32 with four 40.3 -> 36.4).
+//    176 -> 161 us, with four 316 -> 281, 16^3 x 32 with four 40.3 -> 36.4). The
+//    fused CG modes with one field per lane run kOuterAhead: their epilogue's loads
+//    leave the outer hops to hide the next slice's (FP32 solves, ahead / now: 24^4
+//    18.9 / 19.9 ms, 32^3 x 16 28.1 / 29.3, 24^4 with three fields 54.0 / 58.1).
 template <typename T, bool C12, int CGM, bool BUF>
 hipError_t launch_march_b(const void* in, void* out, const void* links, const Geo& geo,
                           const Diag<typename Packed<T>::R>& diag, long stride, int g5,
@@ -651,7 +658,7 @@ hipError_t launch_march_b(const void* in, void* out, const void* links, const Ge
     if constexpr (BUF) {
       if (p.tb == 1) return run(kInt<kMarchMaxThreads>, kInt<1>, kInt<kOneSlice>);
     }
-    return run(kInt<kMarchMaxThreads>, kInt<1>, kInt<kOuterNow>);
+    return run(kInt<kMarchMaxThreads>, kInt<1>, kInt<CGM != kCgNone ? kOuterAhead : kOuterNow>);
   } else {
     return two ? run(kInt<kMarchMaxThreads>, kInt<1>, kInt<kOuterNow>)
                : run(kInt<kMarchMaxThreads>, kInt<1>, kInt<kOuterAhead>);
@@ -746,7 +753,7 @@ hipError_t launch_typed(const wd_gauge* g, const void* in, void* out, const Geo&
     diag.idx[k] = fields ? fields[k] : k;
   }
   const long stride = spinor_units<T>(geo.V);  // 16-B elements per field
-  MarchParams p = march_params(geo, g->prec, nrhs);
+  MarchParams p = march_params(geo, g->prec, nrhs, cg != nullptr);
   // byte sizes for buffer-resource access, or 0 where a field reaches 4 GiB
   const unsigned long sbytes = static_cast<unsigned long>(stride) * 16;
   p.link_bytes = g->link_bytes < (1ul << 32) ? static_cast<unsigned>(g->link_bytes) : 0u;

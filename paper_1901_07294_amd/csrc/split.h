@@ -20,7 +20,7 @@
 // kernel): 8^4 FP32 in a solve 17.1 -> 5.7 us per launch (6.0 -> 2.8 ms per
 // solve), 15 x 9 x 14 x 21 FP32 24.2 -> 7.6 us, 6 x 6 x 40 x 72 FP64 35.9 -> 19.2
 // us, with four fields 174 -> 62 us. On larger lattices every neighbour spinor
-// comes through L1, and the marches win (24^4 FP16 24 against 31 us).
+// comes through L1, and the marches win (24^4 FP16 22 against 30 us).
 #pragma once
 
 #include "cg_site.h"

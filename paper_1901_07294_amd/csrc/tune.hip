@@ -106,7 +106,7 @@ int wd_tune_dslash(const wd_gauge* g, int32_t nrhs, const void* in_dev, void* ou
     MarchTuning cand[kMaxCandidates];
     int nc = 0;
     march_candidates(g->dims, g->prec, nrhs, cand, &nc, kMaxCandidates);
-    if (nc == 0) return WD_OK;  // the one-site-per-lane kernel runs: nothing to tune
+    if (nc == 0) return WD_OK;  // the split kernel runs, without march geometry: nothing to tune
 
     double masses[kMaxMultiRhs];
     for (int k = 0; k < nrhs; ++k) masses[k] = 0.1;

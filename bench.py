@@ -49,16 +49,17 @@ def compulsory_bytes(prec: str, c12: bool) -> int:
 TRAFFIC = {
     # FETCH_SIZE x 2.000 + WRITE_SIZE x 1.000 (copy-calibrated KiB per dispatch), measured for
     # the kernel code hashed below, per launch "tb,gw,group,rb" the bytes belong to
-    "wilson_dslash_32x32x32x64_fp64": {"source_sha": "f8e8833d29f40acb", "launches": {
-        "32,1,32,1": 2211276800}},  # 883,117 / 393,216
-    "wilson_dslash_32x32x32x64_fp64_c12": {"source_sha": "f8e8833d29f40acb", "launches": {
-        "32,1,32,1": 1778633728}},  # 671,843 / 393,261
-    "wilson_dslash_32x32x32x64_fp32": {"source_sha": "f8e8833d29f40acb", "launches": {
-        "16,1,64,1": 1115131904}},  # 446,191 / 196,614
-    "wilson_dslash_32x32x32x64_fp16": {"source_sha": "f8e8833d29f40acb", "launches": {
-        "4,1,256,1": 618565632}},   # 248,786 / 106,496
+    "wilson_dslash_32x32x32x64_fp64": {"source_sha": "afe3158b32ea6325", "launches": {
+        "32,1,32,1": 2210486305}},  # 882,731 / 393,216
+    "wilson_dslash_32x32x32x64_fp64_c12": {"source_sha": "afe3158b32ea6325", "launches": {
+        "32,1,32,1": 1782605501}},  # 673,776 / 393,274
+    "wilson_dslash_32x32x32x64_fp32": {"source_sha": "afe3158b32ea6325", "launches": {
+        "16,1,64,1": 1223931711}},  # 499,319 / 196,608
+    "wilson_dslash_32x32x32x64_fp16": {"source_sha": "afe3158b32ea6325", "launches": {
+        "4,1,256,1": 645014979}},   # 261,701 / 106,496
 }
-KERNEL_SOURCES = ["paper_1901_07294_amd/csrc/dslash.hip", "paper_1901_07294_amd/csrc/stencil.h",
+KERNEL_SOURCES = ["paper_1901_07294_amd/csrc/dslash.hip", "paper_1901_07294_amd/csrc/split.h",
+                  "paper_1901_07294_amd/csrc/stencil.h",
                   "paper_1901_07294_amd/csrc/fields.h", "paper_1901_07294_amd/csrc/cplx.h"]
 
 

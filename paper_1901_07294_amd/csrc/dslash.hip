@@ -557,11 +557,12 @@ MarchParams march_params(const Geo& geo, int prec, int nrhs, bool fused = false)
   // costs up to 4 % more (24^4 with three fields: 54.1 ms per solve at 12 slices per
   // workgroup, 50.2 at 6)
   const double tie = fused && prec == WD_FP32 ? 1.04 : 1.0;
-  // FP16 storage: one slice per workgroup (its own kernel), unless one or two
-  // fields and their links outgrow the 256 MB cache that serves the t neighbours
-  // then (about 2^20 sites; us, one slice / best longer march: 24^3 x 48 37.5 /
-  // 41.2, 32^4 59.9 / 56.8, 32^4 with two fields 99.2 / 98.1)
-  const bool single = prec == WD_FP16 && (geo.V < (1 << 20) || nrhs > 2);
+  // FP16 storage: one slice per workgroup (its own kernel), unless the fields and
+  // links outgrow the 256 MB cache that serves the t neighbours then (about 2^20
+  // sites; us, one slice / best longer march: 24^3 x 48 37.5 / 41.2, 32^4 59.9 /
+  // 56.8, 32^3 x 64 with four fields 398 / 397, with eight 838 / 767, with twelve
+  // 1273 / 1152)
+  const bool single = prec == WD_FP16 && geo.V < (1 << 20);
   if (single) p.tb = 1;
   for (int rb = 1; rb <= 2 && !single; ++rb) {
     const size_t lds = march_lds_bytes(n, real_bytes) * (rb == 2 && two_workgroups(n) ? 2 : 1);  // one buffer per field

@@ -23,6 +23,8 @@
 // comes through L1, and the marches win (24^4 FP16 22 against 30 us).
 #pragma once
 
+#include <algorithm>
+
 #include "cg_site.h"
 #include "stencil.h"
 #include "wd_internal.h"
@@ -398,8 +400,18 @@ __global__ __launch_bounds__(kSplitThreads) void split_hop_kernel(
   }
 }
 
+// Fields of `per` tiles per XCD that fit one launch (HIP counts a launch's
+// threads in 32 bits).
+inline int split_fields_per_launch(int per) {
+  const long threads = static_cast<long>(per) * kNumXcd * kSplitThreads;
+  return static_cast<int>(std::min<long>(kMaxMultiRhs, 0xffffffffL / threads));
+}
+
 // Launches it; p's tiles are filled in here, link_bytes and spinor_bytes are 0
-// where a field reaches 4 GiB (not with a fold, which small lattices use).
+// where a field reaches 4 GiB (not with a fold, which small lattices use). A
+// launch has fewer than 2^32 threads: eight per site and field pass that from
+// 2^29 sites of all fields on (16 fields of 512 x 64 x 32 x 32), whose fields go
+// in several launches then; three fields of the largest lattice fit one.
 template <typename T, bool C12, int CGM, int FOLD = kFoldNone>
 hipError_t launch_split_hop(const void* in, const void* w, void* out, const void* lf, const void* lb,
                             const SplitCoef<typename Packed<T>::R>& cf, long stride, int g5, SplitParams p,
@@ -408,12 +420,25 @@ hipError_t launch_split_hop(const void* in, const void* w, void* out, const void
   using LV = typename Packed<T>::L;
   p.ntiles = (p.V + kSplitSites - 1) / kSplitSites;
   p.per = (p.ntiles + kNumXcd - 1) / kNumXcd;
-  const unsigned nb = static_cast<unsigned>(p.per) * kNumXcd * static_cast<unsigned>(p.nrhs);
+  const int nrhs = p.nrhs;
+  const int most = split_fields_per_launch(p.per);
   const auto run = [&](auto kernel) {
-    kernel<<<nb, kSplitThreads, 0, st>>>(static_cast<const SV*>(in), static_cast<const SV*>(w),
-                                         static_cast<SV*>(out), static_cast<const LV*>(lf),
-                                         static_cast<const LV*>(lb), cf, stride, g5, p, f);
-    return hipGetLastError();
+    for (int k0 = 0; k0 < nrhs; k0 += most) {
+      SplitCoef<typename Packed<T>::R> part = cf;
+      p.nrhs = nrhs - k0 < most ? nrhs - k0 : most;
+      for (int k = 0; k < p.nrhs; ++k) {
+        part.d[k] = cf.d[k0 + k];
+        part.c[k] = cf.c[k0 + k];
+        part.idx[k] = cf.idx[k0 + k];
+      }
+      const unsigned nb = static_cast<unsigned>(p.per) * kNumXcd * static_cast<unsigned>(p.nrhs);
+      kernel<<<nb, kSplitThreads, 0, st>>>(static_cast<const SV*>(in), static_cast<const SV*>(w),
+                                           static_cast<SV*>(out), static_cast<const LV*>(lf),
+                                           static_cast<const LV*>(lb), part, stride, g5, p, f);
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
   };
   if (FOLD != kFoldNone && (f.r == nullptr || f.prr == nullptr || f.nprr < 1 || f.scal == nullptr))
     return hipErrorInvalidValue;

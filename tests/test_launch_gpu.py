@@ -125,6 +125,25 @@ def test_split_kernel_links_beyond_4_gib():
     assert rel(out[sites], ref) <= TOL[w.WD_FP64]
 
 
+def test_split_kernel_fields_beyond_one_launch():
+    """16 FP16 fields on rows of 512 sites (no t-marching tiles): eight lanes for
+    each of the 2^29 sites are more threads than one launch can have. Every
+    field's bits as alone."""
+    dims, n = (512, 64, 32, 32), 16
+    print(f"case split dims={dims} nrhs={n}: more than 2^32 threads", flush=True)
+    g = DeviceGauge(dev.random_gauge(dims, 94), w.WD_FP16)
+    one = g.pack(dev.gaussian_spinor(dims, 95))
+    masses = [0.05 + 0.03 * k for k in range(n)]
+    out = g.spinor(n).zero_()
+    w.dslash_apply_multi(g.handle, masses, n, one.repeat(n), out, w.WD_FP16)
+    alone = g.spinor().zero_()
+    for k in range(n):
+        w.dslash_apply(g.handle, masses[k], one, alone, w.WD_FP16)
+        assert torch.equal(out[k * one.numel():(k + 1) * one.numel()], alone), k
+    del out, alone, one
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("inner", ["fp64", "fp32", "fp16"])
 @pytest.mark.parametrize("dims", [
     (8, 8, 8, 4),    # split kernel, slices of 32 sites

@@ -209,9 +209,13 @@ def _stream(stream):
     if stream is None:
         import torch
         # the handle itself, without building torch's Stream object around it
-        # (2.6 of the 7.4 us a small dslash_apply took on the host)
+        # (2.6 of the 7.4 us a small dslash_apply took on the host), where torch
+        # has these two calls: they are not part of its public interface
         if torch.cuda.is_initialized():
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+            try:
+                return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+            except AttributeError:
+                pass
         return torch.cuda.current_stream().cuda_stream
     if hasattr(stream, "cuda_stream"):
         return stream.cuda_stream

@@ -73,3 +73,19 @@ def test_size_queries_reject_bad_arguments(lib):
     assert w.wd_spinor_bytes((4, 4, 4, 4), 9, 1) == 0
     assert w.wd_gauge_bytes((4096, 4096, 4096, 4096), w.WD_FP64, 0) == 0
     assert w.wd_spinor_bytes((1, 1, 1, 1), w.WD_FP64, 0) == 0
+
+
+@pytest.mark.parametrize("missing", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_current_stream_without_torch_internals(monkeypatch, missing):
+    """stream=None is torch's current stream also where torch lacks the calls
+    that give its handle directly."""
+    import types
+
+    import torch
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 0, raising=False)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 5, raising=False)
+    assert w._stream(None) == 5
+    monkeypatch.delattr(torch._C, missing)
+    assert w._stream(None) == 77

@@ -1,5 +1,6 @@
 // The Wilson-Dirac operator on gfx950: one lane per lattice site on large
-// lattices (the t-marching kernel below), eight on small ones (split.h).
+// lattices (the t-marching kernel below), eight on small ones (split.h), and one
+// in FP16 storage on larger ones that the march cannot tile.
 //
 //   out(x) = (4+m) psi(x) - 1/2 sum_mu [ (1-g_mu) U_mu(x) psi(x+mu)
 //                                       + (1+g_mu) U_mu(x-mu)^dag psi(x-mu) ]
@@ -64,6 +65,65 @@ __device__ __forceinline__ int tile_of_block(int group, int nb) {
   if (static_cast<long>(group) * kNumXcd >= nb) return xcd * group + l;
   if (nb % (kNumXcd * group) != 0) return b;
   return ((l / group) * kNumXcd + xcd) * group + (l % group);
+}
+
+// ---------------------------------------------------------------------------
+// One lane per site, FP16 storage, on lattices without t-marching tiles (x rows
+// longer than 256 sites, or fewer than 64 sites in the longest run of whole rows
+// that divides y, as with a prime number of short rows).
+//
+// FP16 fields are few bytes and much conversion: with eight lanes per site every
+// lane converts a spinor for one hop and, with 12-real links, rebuilds a third
+// row, which is what bounds that kernel. Here a lane walks the eight hops, in the
+// same order. What counts is that every CU gets work (workgroups of one wave) and
+// that a wave keeps enough loads in flight: bound to four waves per SIMD the
+// kernel takes 86 registers; left to itself the compiler stops at 66 and waits
+// more often (300 x 4 x 4 x 20 10.4 -> 8.5 us). Eight lanes -> one lane, us: 24 x 17 x
+// 20 x 60 43 -> 29, with 12-real links 43 -> 28 and with 12 fields of them 514 ->
+// 311; 4^3 x 512 with 12 fields 31 -> 18.3, one field 6.1 -> 6.2.
+// ---------------------------------------------------------------------------
+
+constexpr int kSiteBlock = 64;
+// Sites times fields from which it runs: below, one wave of eight lanes per site
+// hides more latency (7 x 4 x 12 x 14 with three fields 5.3 / 5.8 us, 10 x 5 x 16 x 14
+// with two 6.2 / 6.3 and with three 6.9 / 6.4).
+constexpr long kSiteSites = 24576;
+// ... and beyond which the fused CG work does, by the even-odd hop kernel (eo.hip),
+// which sums the same slices. Eight lanes / one, us per iteration: 4^3 x 512 22.9 /
+// 24.1, 10 x 5 x 16 x 14 with four fields 29.6 / 29.5, 33 x 17 x 11 x 7 with two 41.1 /
+// 38.6 and with 16 182 / 127.
+constexpr long kSiteCgSites = 45000;
+
+template <bool C12, bool BUF>
+__global__ __launch_bounds__(kSiteBlock) __attribute__((amdgpu_waves_per_eu(4, 4))) void dslash_site_kernel(
+    const h8* __restrict__ in_all, h8* __restrict__ out_all, const h2* __restrict__ links, Diag<float> diags,
+    long stride, int gamma5, SplitParams p) {
+  int rhs;
+  const int tile = split_tile(p, &rhs);
+  const int s = tile * kSiteBlock + static_cast<int>(threadIdx.x);
+  if (tile >= p.ntiles || s >= p.V) return;
+  const long V = p.V;
+  const long k = diags.idx[rhs];
+  const auto in = field_in<BUF>(in_all + k * stride, p.spinor_bytes);
+  const auto lk = field_in<BUF>(links, p.link_bytes);
+  const int xp = split_neighbour(p, 0, 0, s), xm = split_neighbour(p, 0, 1, s);
+  const int yp = split_neighbour(p, 1, 0, s), ym = split_neighbour(p, 1, 1, s);
+  const int zp = split_neighbour(p, 2, 0, s), zm = split_neighbour(p, 2, 1, s);
+  const int tp = split_neighbour(p, 3, 0, s), tm = split_neighbour(p, 3, 1, s);
+  cx<float> acc[12], psi[12], o[12];
+#pragma unroll
+  for (int c = 0; c < 12; ++c) acc[c] = {0.0f, 0.0f};
+  hop<0, -1, C12>(in, lk, V, xp, s, acc);
+  hop<0, +1, C12>(in, lk, V, xm, xm, acc);
+  hop<1, -1, C12>(in, lk, V, yp, s, acc);
+  hop<1, +1, C12>(in, lk, V, ym, ym, acc);
+  hop<2, -1, C12>(in, lk, V, zp, s, acc);
+  hop<2, +1, C12>(in, lk, V, zm, zm, acc);
+  hop<3, -1, C12>(in, lk, V, tp, s, acc);
+  hop<3, +1, C12>(in, lk, V, tm, tm, acc);
+  load_spinor(in, V, s, psi);
+  epilogue(psi, acc, diags.d[rhs], gamma5, o);
+  store_spinor(field_out<BUF>(out_all + k * stride, p.spinor_bytes), V, s, o);
 }
 
 // ---------------------------------------------------------------------------
@@ -700,6 +760,25 @@ hipError_t launch_split(const void* in, void* out, const void* links, const Geo&
   return launch_split_hop<T, C12, CGM, FOLD>(in, in, out, links, links, cf, stride, g5, p, f, st);
 }
 
+hipError_t launch_site(const wd_gauge* g, const void* in, void* out, const Geo& geo, const Diag<float>& diag,
+                       long stride, int g5, const MarchParams& m, hipStream_t st) {
+  SplitParams p{geo.X, geo.Y, geo.Z, geo.T, geo.X, geo.XY, geo.XYZ, geo.V};
+  p.nrhs = m.nrhs;
+  p.link_bytes = m.link_bytes;
+  p.spinor_bytes = m.spinor_bytes;
+  p.ntiles = (p.V + kSiteBlock - 1) / kSiteBlock;
+  p.per = (p.ntiles + kNumXcd - 1) / kNumXcd;
+  const unsigned nb = static_cast<unsigned>(p.per) * kNumXcd * static_cast<unsigned>(p.nrhs);
+  const auto run = [&](auto kernel) {
+    kernel<<<nb, kSiteBlock, 0, st>>>(static_cast<const h8*>(in), static_cast<h8*>(out),
+                                      static_cast<const h2*>(g->links), diag, stride, g5, p);
+    return hipGetLastError();
+  };
+  const bool buf = p.link_bytes != 0 && p.spinor_bytes != 0;
+  if (g->c12) return buf ? run(&dslash_site_kernel<true, true>) : run(&dslash_site_kernel<true, false>);
+  return buf ? run(&dslash_site_kernel<false, true>) : run(&dslash_site_kernel<false, false>);
+}
+
 // Whether the split kernel is the default for nrhs fields: where the t-marching
 // one does not apply, in launches too small to fill the chip with marches, and
 // in somewhat larger ones on lattices whose tiles leave lanes of their waves
@@ -761,6 +840,7 @@ hipError_t launch_typed(const wd_gauge* g, const void* in, void* out, const Geo&
   const unsigned long sbytes = static_cast<unsigned long>(stride) * 16;
   p.link_bytes = g->link_bytes < (1ul << 32) ? static_cast<unsigned>(g->link_bytes) : 0u;
   p.spinor_bytes = sbytes < (1ul << 32) ? static_cast<unsigned>(sbytes) : 0u;
+  const long work = static_cast<long>(geo.V) * nrhs;
   MarchTuning t;
   bool split = use_split(geo, p, g->prec);
   if (p.ny > 0 && (force != nullptr || tuned_lookup(g->dims, g->prec, g->c12, nrhs, &t))) {
@@ -775,6 +855,8 @@ hipError_t launch_typed(const wd_gauge* g, const void* in, void* out, const Geo&
       return hipErrorInvalidValue;
     split = small_slices(geo, p);
     if (!split && !whole_waves(geo, p)) return hipErrorInvalidValue;
+    if (split && p.ny == 0 && g->prec == WD_FP16 && cg->p_out == nullptr && work > kSiteCgSites)
+      return launch_site_cg(g, masses, nrhs, fields, in, out, *cg, st);
     if (cg->mode == kCgNorm && cg->p_out != nullptr)
       return split ? launch_split<T, C12, kCgNorm, kFoldBoth>(in, out, g->links, geo, diag, stride, g5, p, *cg, st)
                    : hipErrorInvalidValue;
@@ -784,6 +866,9 @@ hipError_t launch_typed(const wd_gauge* g, const void* in, void* out, const Geo&
     if (cg->mode != kCgUpdate) return hipErrorInvalidValue;
     return split ? launch_split<T, C12, kCgUpdate>(in, nullptr, g->links, geo, diag, stride, g5, p, *cg, st)
                  : launch_march<T, C12, kCgUpdate>(in, nullptr, g->links, geo, diag, stride, g5, p, *cg, st);
+  }
+  if constexpr (sizeof(T) == 2) {
+    if (p.ny == 0 && work >= kSiteSites) return launch_site(g, in, out, geo, diag, stride, g5, p, st);
   }
   return split ? launch_split<T, C12, kCgNone>(in, out, g->links, geo, diag, stride, g5, p, CgFuse{}, st)
                : launch_march<T, C12, kCgNone>(in, out, g->links, geo, diag, stride, g5, p, CgFuse{}, st);

@@ -29,19 +29,8 @@ constexpr int kEoBlock = 256;
 // 16^4 with two fields 14.8 / 17.3, 24^4 27.7 / 33.1). Same bits either way.
 bool use_split_eo(int prec, long Vh, int nrhs) { return prec == WD_FP64 || Vh * nrhs <= 48000; }
 
-// One hop: neighbour spinor at half site n of the input, link of direction MU
-// at half site ls.
-template <int MU, int S, bool C12, typename SA, typename LA, typename R>
-__device__ __forceinline__ void eo_hop(const SA& in, const LA& links, long V, int n, int ls, cx<R> (&acc)[12]) {
-  cx<R> u[9], psi[12], h[6], g[6];
-  load_link<C12>(links, V, MU, ls, u);
-  load_spinor(in, V, n, psi);
-  project<MU, S>(psi, h);
-  su3_mul<(S > 0)>(u, h, g);
-  reconstruct_add<MU, S>(g, acc);
-}
-
-// One lane per output half site. Workgroups of 256 half sites; the links and the
+// One lane per output half site, or (p.eo == 0) per site of a whole lattice.
+// Workgroups of 256 half sites; the links and the
 // input through buffer resources where they fit. Against plain pointers and a
 // grid row per right-hand side (us per application of the Schur operator): FP16
 // 24^4 36.3 -> 27.7, with four fields 97.6 -> 69.1; FP32 24^3 x 48 104 -> 98, with
@@ -83,22 +72,22 @@ __global__ __launch_bounds__(kEoBlock) void eo_hop_kernel(
   const int row = h / p.X, xh = h - row * p.X;
   const int y = row % p.Y, zt = row / p.Y, z = zt % p.Z, t = zt / p.Z;
   const int o = (y + z + t + p.parity) & 1;
-  const int xp = o ? (xh + 1 == p.X ? h - (p.X - 1) : h + 1) : h;
-  const int xm = o ? h : (xh == 0 ? h + (p.X - 1) : h - 1);
+  const int xp = !p.eo || o ? (xh + 1 == p.X ? h - (p.X - 1) : h + 1) : h;
+  const int xm = p.eo && o ? h : (xh == 0 ? h + (p.X - 1) : h - 1);
   const int yp = y + 1 == p.Y ? h - (p.Y - 1) * p.sy : h + p.sy;
   const int ym = y == 0 ? h + (p.Y - 1) * p.sy : h - p.sy;
   const int zp = z + 1 == p.Z ? h - (p.Z - 1) * p.sz : h + p.sz;
   const int zm = z == 0 ? h + (p.Z - 1) * p.sz : h - p.sz;
   const int tp = t + 1 == p.T ? h - (p.T - 1) * p.st : h + p.st;
   const int tm = t == 0 ? h + (p.T - 1) * p.st : h - p.st;
-  eo_hop<0, -1, C12>(in, fp, V, xp, h, acc);
-  eo_hop<0, +1, C12>(in, fq, V, xm, xm, acc);
-  eo_hop<1, -1, C12>(in, fp, V, yp, h, acc);
-  eo_hop<1, +1, C12>(in, fq, V, ym, ym, acc);
-  eo_hop<2, -1, C12>(in, fp, V, zp, h, acc);
-  eo_hop<2, +1, C12>(in, fq, V, zm, zm, acc);
-  eo_hop<3, -1, C12>(in, fp, V, tp, h, acc);
-  eo_hop<3, +1, C12>(in, fq, V, tm, tm, acc);
+  hop<0, -1, C12>(in, fp, V, xp, h, acc);
+  hop<0, +1, C12>(in, fq, V, xm, xm, acc);
+  hop<1, -1, C12>(in, fp, V, yp, h, acc);
+  hop<1, +1, C12>(in, fq, V, ym, ym, acc);
+  hop<2, -1, C12>(in, fp, V, zp, h, acc);
+  hop<2, +1, C12>(in, fq, V, zm, zm, acc);
+  hop<3, -1, C12>(in, fp, V, tp, h, acc);
+  hop<3, +1, C12>(in, fq, V, tm, tm, acc);
 
   const R d = cf.d[rhs], c = cf.c[rhs];
   cx<R> res[12];
@@ -243,6 +232,43 @@ hipError_t launch_hop(const wd_gauge* g, int parity, const void* in, const void*
 }
 
 }  // namespace
+
+hipError_t launch_site_cg(const wd_gauge* g, const double* masses, int nrhs, const int* fields, const void* in,
+                          void* out, const CgFuse& f, hipStream_t st) {
+  const Geo geo = make_geo(g->dims);
+  const long stride = spinor_units<_Float16>(geo.V);
+  if (g->eo || g->prec != WD_FP16 || nrhs < 1 || nrhs > kMaxRhs || f.rr == nullptr ||
+      f.nslices < (geo.V + kSplitSites - 1) / kSplitSites || g->link_bytes >= (1ul << 32) || stride * 16 >= (1l << 32))
+    return hipErrorInvalidValue;
+  if (f.mode == kCgUpdate && (f.r == nullptr || f.pap == nullptr || f.npap < 1 || f.scal == nullptr))
+    return hipErrorInvalidValue;
+  SplitCoef<float> cf{};
+  for (int k = 0; k < nrhs; ++k) {
+    cf.d[k] = static_cast<float>(4.0 + masses[k]);
+    cf.c[k] = -0.5f;
+    cf.idx[k] = fields ? fields[k] : k;
+  }
+  SplitParams p{geo.X, geo.Y, geo.Z, geo.T, geo.X, geo.XY, geo.XYZ, geo.V};
+  p.nrhs = nrhs;
+  p.link_bytes = static_cast<unsigned>(g->link_bytes);
+  p.spinor_bytes = static_cast<unsigned>(stride * 16);
+  p.ntiles = (p.V + kEoBlock - 1) / kEoBlock;
+  p.per = (p.ntiles + kNumXcd - 1) / kNumXcd;
+  const unsigned nb = static_cast<unsigned>(p.per) * kNumXcd * static_cast<unsigned>(nrhs);
+  const auto run = [&](auto kernel) {
+    const h2* links = static_cast<const h2*>(g->links);
+    kernel<<<nb, kEoBlock, 0, st>>>(static_cast<const h8*>(in), static_cast<const h8*>(in), static_cast<h8*>(out),
+                                    links, links, cf, stride, 1, p, f);
+    return hipGetLastError();
+  };
+  if (f.mode == kCgNorm)
+    return g->c12 ? run(&eo_hop_kernel<_Float16, true, kCgNorm, true>)
+                  : run(&eo_hop_kernel<_Float16, false, kCgNorm, true>);
+  if (f.mode == kCgUpdate)
+    return g->c12 ? run(&eo_hop_kernel<_Float16, true, kCgUpdate, true>)
+                  : run(&eo_hop_kernel<_Float16, false, kCgUpdate, true>);
+  return hipErrorInvalidValue;
+}
 
 int eo_fuse_slices(const int32_t dims[4], int prec) {
   const long Vh = make_eo_geo(dims).Vh;

@@ -82,27 +82,16 @@ __device__ __forceinline__ void su3_mul(const cx<R> (&u)[9], const cx<R> (&h)[6]
   }
 }
 
-// One hop with the neighbour spinor already in registers and the link of
-// direction MU at site ls loaded from the packed gauge field.
-template <int MU, int S, bool C12, typename LV, typename R>
-__device__ __forceinline__ void hop_psi(const cx<R> (&psi)[12], const LV* __restrict__ links, long V,
-                                        int ls, cx<R> (&acc)[12]) {
-  cx<R> u[9];
+// One hop: link of direction MU at site ls, neighbour spinor at site n; in and
+// links are plain pointers or buffer resources.
+template <int MU, int S, bool C12, typename SA, typename LA, typename R>
+__device__ __forceinline__ void hop(const SA& in, const LA& links, long V, int n, int ls, cx<R> (&acc)[12]) {
+  cx<R> u[9], psi[12], h[6], g[6];
   load_link<C12>(links, V, MU, ls, u);
-  cx<R> h[6];
+  load_spinor(in, V, n, psi);
   project<MU, S>(psi, h);
-  cx<R> g[6];
   su3_mul<(S > 0)>(u, h, g);
   reconstruct_add<MU, S>(g, acc);
-}
-
-// One hop: neighbour spinor at site n, link of direction MU at site ls.
-template <int MU, int S, bool C12, typename SV, typename LV, typename R>
-__device__ __forceinline__ void hop(const SV* __restrict__ in, const LV* __restrict__ links, long V,
-                                    int n, int ls, cx<R> (&acc)[12]) {
-  cx<R> psi[12];
-  load_spinor(in, V, n, psi);
-  hop_psi<MU, S, C12>(psi, links, V, ls, acc);
 }
 
 // out = diag * psi - acc / 2, optionally times gamma5 (negates spins 2, 3).

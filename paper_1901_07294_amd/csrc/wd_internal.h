@@ -172,5 +172,9 @@ bool cg_fold_p(const int32_t dims[4], int prec, int n);
 // (cg_fuse_slices must be > 0).
 hipError_t launch_dslash_cg(const wd_gauge* g, const double* masses, int nrhs, const int* fields,
                             const void* in, void* out, const CgFuse& f, hipStream_t s);
+// The same by one lane per site, FP16 storage, for lattices without t-marching
+// tiles (not kCgNorm with p_out).
+hipError_t launch_site_cg(const wd_gauge* g, const double* masses, int nrhs, const int* fields, const void* in,
+                          void* out, const CgFuse& f, hipStream_t st);
 
 }  // namespace wd

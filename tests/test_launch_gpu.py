@@ -125,22 +125,43 @@ def test_split_kernel_links_beyond_4_gib():
     assert rel(out[sites], ref) <= TOL[w.WD_FP64]
 
 
-def test_split_kernel_fields_beyond_one_launch():
-    """16 FP16 fields on rows of 512 sites (no t-marching tiles): eight lanes for
-    each of the 2^29 sites are more threads than one launch can have. Every
-    field's bits as alone."""
-    dims, n = (512, 64, 32, 32), 16
-    print(f"case split dims={dims} nrhs={n}: more than 2^32 threads", flush=True)
-    g = DeviceGauge(dev.random_gauge(dims, 94), w.WD_FP16)
-    one = g.pack(dev.gaussian_spinor(dims, 95))
+def block_around(field, site):
+    """The 3^4 block of sites around `site` of a device field, as a host array."""
+    T, Z, Y, X = field.shape[:4]
+    c = [site // (X * Y * Z), site // (X * Y) % Z, site // X % Y, site % X]
+    d = torch.arange(-1, 2, device=field.device)
+    t, z, y, x = torch.meshgrid(*[(v + d) % e for v, e in zip(c, (T, Z, Y, X))], indexing="ij")
+    return field[t, z, y, x].cpu().numpy()
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp16"])
+def test_many_fields_without_tiles(prec):
+    """16 fields on rows of 512 sites (no t-marching tiles), with links beyond
+    4 GiB: in FP32 the eight lanes of each of the 2^29 sites are more threads
+    than one launch can have, in FP16 storage one lane per site, plain pointers.
+    Every field's bits as alone, and one against the oracle at sampled sites."""
+    dims, n, p = (512, 64, 32, 32), 16, PRECS[prec]
+    print(f"case no tiles dims={dims} nrhs={n} prec={prec}", flush=True)
+    U, psi = dev.random_gauge(dims, 94), dev.gaussian_spinor(dims, 95)
+    g = DeviceGauge(U, p)
+    assert g.buf.numel() > 1 << 32
+    one = g.pack(psi)
     masses = [0.05 + 0.03 * k for k in range(n)]
     out = g.spinor(n).zero_()
-    w.dslash_apply_multi(g.handle, masses, n, one.repeat(n), out, w.WD_FP16)
+    w.dslash_apply_multi(g.handle, masses, n, one.repeat(n), out, p)
     alone = g.spinor().zero_()
     for k in range(n):
-        w.dslash_apply(g.handle, masses[k], one, alone, w.WD_FP16)
+        w.dslash_apply(g.handle, masses[k], one, alone, p)
         assert torch.equal(out[k * one.numel():(k + 1) * one.numel()], alone), k
-    del out, alone, one
+    canon = torch.empty_like(psi)
+    w.wd_spinor_export(g.handle, alone, p, 1, canon)
+    V = li.volume(dims)
+    got, ref = [], []
+    for s in [0, V // 2, V - 1] + [int(v) for v in np.random.default_rng(96).integers(0, V, 20)]:
+        got.append(canon.reshape(V, 4, 3)[s].cpu().numpy())
+        ref.append(oracle.dslash(block_around(U, s), block_around(psi, s), masses[-1])[1, 1, 1, 1])
+    assert rel(np.stack(got), np.stack(ref)) <= TOL[p]
+    del out, alone, one, canon, U, psi
     torch.cuda.empty_cache()
 
 
@@ -322,3 +343,43 @@ def test_binding_follows_the_current_stream():
         assert w._stream(None) == side.cuda_stream != torch.cuda.default_stream().cuda_stream
     assert w._stream(None) == torch.cuda.current_stream().cuda_stream
     assert w._stream(side) == side.cuda_stream and w._stream(5) == 5
+
+
+@pytest.mark.parametrize("dims,inner,eo,c12,many", [
+    ((8, 10, 10, 10), "fp64", False, False, 14),
+    ((8, 10, 10, 10), "fp32", False, False, 14),
+    ((8, 10, 10, 10), "fp16", False, False, 14),
+    ((12, 10, 10, 10), "fp64", True, False, 14),
+    ((12, 10, 10, 10), "fp32", True, False, 14),
+    ((12, 10, 10, 10), "fp16", True, False, 14),
+    ((7, 9, 11, 13), "fp16", False, False, 12),  # no t-marching tiles: one lane per site unless folded
+    ((7, 9, 11, 13), "fp16", False, True, 12),
+], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_folded_directions_against_launches_of_their_own(dims, inner, eo, c12, many):
+    """On lattices where two fields fold in every precision (8000 sites; 6000
+    half sites even-odd) and `many` fields fold in none: after the same 12
+    iterations chunks of 1 (nothing folded), 5 and 12 and the large batch give
+    the same bits for the first two fields. x0 = 0, no reliable update before
+    the end."""
+    print(f"case fold dims={dims} inner={inner} eo={eo} c12={c12}", flush=True)
+    U = li.near_unity_gauge(dims, 141, 0.3)
+    bs = li.gaussian_spinors(dims, [142 + k for k in range(many)])
+    prec = PRECS[inner]
+    ghi, glo = DeviceGauge(U, w.WD_FP64, eo=eo), DeviceGauge(U, prec, c12, eo=eo)
+    call = w.cg_solve_wilson if eo else w.cg_solve_normal
+
+    def solve(b, every):
+        n = b.shape[0]
+        x = ghi.spinor(n)
+        size = (w.wilson_workspace_bytes(dims, n, prec, 1) if eo else w.cg_workspace_bytes(dims, n, prec))
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+        rc, stats = call(ghi.handle, glo.handle, [0.05 + 0.02 * k for k in range(n)], n, ghi.pack(b, nrhs=n), x,
+                         dict(tol=1e-30, max_iter=12, inner=prec, delta=1e-30, check_every=every, x0_given=0,
+                              use_graph=0), ws)
+        assert rc == w.WD_ERR_NOT_CONVERGED and all(s["iters"] == 12 for s in stats), stats
+        return ghi.unpack(x, nrhs=n).reshape(n, *b.shape[1:])
+
+    ref = solve(bs[:2], 1)
+    for every in (5, 12):
+        assert np.array_equal(solve(bs[:2], every), ref), every
+    assert np.array_equal(solve(bs, 5)[:2], ref)

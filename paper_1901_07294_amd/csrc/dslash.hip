@@ -767,8 +767,7 @@ hipError_t launch_site(const wd_gauge* g, const void* in, void* out, const Geo& 
   p.link_bytes = m.link_bytes;
   p.spinor_bytes = m.spinor_bytes;
   p.ntiles = (p.V + kSiteBlock - 1) / kSiteBlock;
-  p.per = (p.ntiles + kNumXcd - 1) / kNumXcd;
-  const unsigned nb = static_cast<unsigned>(p.per) * kNumXcd * static_cast<unsigned>(p.nrhs);
+  const unsigned nb = split_grid(p);
   const auto run = [&](auto kernel) {
     kernel<<<nb, kSiteBlock, 0, st>>>(static_cast<const h8*>(in), static_cast<h8*>(out),
                                       static_cast<const h2*>(g->links), diag, stride, g5, p);

@@ -182,8 +182,7 @@ hipError_t launch_hop_t(const wd_gauge* g, int p, const void* in, const void* w,
   if (FOLD != kFoldNone || (use_split_eo(g->prec, geo.Vh, set.n) && !(CGM != kCgNone && wide_slices(geo.Vh))))
     return launch_split_hop<T, C12, CGM, FOLD>(in, w, out, lp, lq, cf, stride, g5, sp, f, s);
   sp.ntiles = (sp.V + kEoBlock - 1) / kEoBlock;
-  sp.per = (sp.ntiles + kNumXcd - 1) / kNumXcd;
-  const unsigned nb = static_cast<unsigned>(sp.per) * kNumXcd * static_cast<unsigned>(set.n);
+  const unsigned nb = split_grid(sp);
   const auto run = [&](auto kernel) {
     kernel<<<nb, kEoBlock, 0, s>>>(static_cast<const typename Packed<T>::S*>(in),
                                    static_cast<const typename Packed<T>::S*>(w),
@@ -253,8 +252,7 @@ hipError_t launch_site_cg(const wd_gauge* g, const double* masses, int nrhs, con
   p.link_bytes = static_cast<unsigned>(g->link_bytes);
   p.spinor_bytes = static_cast<unsigned>(stride * 16);
   p.ntiles = (p.V + kEoBlock - 1) / kEoBlock;
-  p.per = (p.ntiles + kNumXcd - 1) / kNumXcd;
-  const unsigned nb = static_cast<unsigned>(p.per) * kNumXcd * static_cast<unsigned>(nrhs);
+  const unsigned nb = split_grid(p);
   const auto run = [&](auto kernel) {
     const h2* links = static_cast<const h2*>(g->links);
     kernel<<<nb, kEoBlock, 0, st>>>(static_cast<const h8*>(in), static_cast<const h8*>(in), static_cast<h8*>(out),

@@ -44,7 +44,7 @@ struct SplitParams {
   int eo, parity;
   int wide;    // eo_hop_kernel: CG slices of 256 sites instead of 32
   int ntiles;  // runs of kSplitSites sites
-  int per;     // tiles per XCD (the last XCD may get fewer)
+  int per;     // workgroups (a tile of one field each) per XCD; the last may have fewer
   int nrhs;
   int ny;      // y rows per tile of the t-marching kernel, 0 where it does not apply
   unsigned link_bytes;    // bytes of the packed links and of one packed spinor field
@@ -153,11 +153,18 @@ __device__ __forceinline__ int split_neighbour(const SplitParams& p, int mu, int
 // side. Every XCD gets one contiguous run of tiles (their halos meet in one L2),
 // and the right-hand sides of a tile follow each other, so that its links come
 // from HBM once: with the right-hand sides in the grid's second dimension four
-// FP64 fields on an even-odd 24^4 took 443 us per application, now 284.
+// FP64 fields on an even-odd 24^4 took 443 us per application, now 284. The
+// shares are of workgroups, not of tiles: 41 tiles of six fields are 31
+// workgroups for each XCD's 32 CUs, where six tiles each were 36.
 __device__ __forceinline__ int split_tile(const SplitParams& p, int* rhs) {
-  const int xcd = blockIdx.x % kNumXcd, l = blockIdx.x / kNumXcd;
-  *rhs = l % p.nrhs;
-  return xcd * p.per + l / p.nrhs;
+  const int b = blockIdx.x % kNumXcd * p.per + blockIdx.x / kNumXcd;
+  *rhs = b % p.nrhs;
+  return b / p.nrhs;
+}
+// The grid for it: p.ntiles and p.nrhs given, p.per filled in.
+inline unsigned split_grid(SplitParams& p) {
+  p.per = (p.ntiles * p.nrhs + kNumXcd - 1) / kNumXcd;
+  return static_cast<unsigned>(p.per) * kNumXcd;
 }
 
 // The CG direction p = r + beta p folded into the application of Q that follows
@@ -400,11 +407,10 @@ __global__ __launch_bounds__(kSplitThreads) void split_hop_kernel(
   }
 }
 
-// Fields of `per` tiles per XCD that fit one launch (HIP counts a launch's
-// threads in 32 bits).
-inline int split_fields_per_launch(int per) {
-  const long threads = static_cast<long>(per) * kNumXcd * kSplitThreads;
-  return static_cast<int>(std::min<long>(kMaxMultiRhs, 0xffffffffL / threads));
+// Fields of ntiles tiles that fit one launch (HIP counts a launch's threads in 32
+// bits; the grid is rounded up to the XCDs).
+inline int split_fields_per_launch(int ntiles) {
+  return static_cast<int>(std::min<long>(kMaxMultiRhs, (0xffffffffL / kSplitThreads - kNumXcd) / ntiles));
 }
 
 // Launches it; p's tiles are filled in here, link_bytes and spinor_bytes are 0
@@ -419,9 +425,8 @@ hipError_t launch_split_hop(const void* in, const void* w, void* out, const void
   using SV = typename Packed<T>::S;
   using LV = typename Packed<T>::L;
   p.ntiles = (p.V + kSplitSites - 1) / kSplitSites;
-  p.per = (p.ntiles + kNumXcd - 1) / kNumXcd;
   const int nrhs = p.nrhs;
-  const int most = split_fields_per_launch(p.per);
+  const int most = split_fields_per_launch(p.ntiles);
   const auto run = [&](auto kernel) {
     for (int k0 = 0; k0 < nrhs; k0 += most) {
       SplitCoef<typename Packed<T>::R> part = cf;
@@ -431,7 +436,7 @@ hipError_t launch_split_hop(const void* in, const void* w, void* out, const void
         part.c[k] = cf.c[k0 + k];
         part.idx[k] = cf.idx[k0 + k];
       }
-      const unsigned nb = static_cast<unsigned>(p.per) * kNumXcd * static_cast<unsigned>(p.nrhs);
+      const unsigned nb = split_grid(p);
       kernel<<<nb, kSplitThreads, 0, st>>>(static_cast<const SV*>(in), static_cast<const SV*>(w),
                                            static_cast<SV*>(out), static_cast<const LV*>(lf),
                                            static_cast<const LV*>(lb), part, stride, g5, p, f);

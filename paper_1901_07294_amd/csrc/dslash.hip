@@ -569,33 +569,53 @@ size_t real_bytes_of(int prec) { return prec == WD_FP64 ? 8 : 4; }
 
 // Cost model behind the default t split and right-hand sides per lane. A
 // workgroup that marches tb slices costs tb + prologue slices (the prologue
-// reads the outer hops, the backward t hop and the first slice); a CU holds
-// `waves` waves' worth of workgroups at once, and the chip works through the
-// launch's workgroups in rounds of 256 CUs' worth. In FP64 and FP32 a started
-// round takes its whole time (tail < 0: whole rounds); with FP16 storage, whose
-// workgroups are short and uneven, the last round costs half of one on average.
-// rb2: the cost of a slice of two right-hand sides per lane in a launch of half
-// the workgroups.
-// Fitted on MI355X to every split of t timed on 14 lattices (8^2 x 16 x 64 to
-// 32^3 x 64, among them 28 x 15 x 22 x 33 and 9 x 33 x 12 x 20) with 1 to 16
-// right-hand sides (two: tiles of which two workgroups fit, where three waves per
-// SIMD run with two per lane): the choice is on average 1.5 % (FP64), 1.7 % (FP32) and 1.0 %
-// (FP16) slower than the best split timed, where one resident round of workgroups
-// whatever its last round leaves idle was 14, 24 and 24 % slower: 24^3 x 48 with
-// 12 FP32 fields 757 -> 535 us, 24^4 with 4 FP64 fields 363 -> 218 us. Two
-// right-hand sides per lane pay in FP32 (87 against 105 us for 4 fields on 24^4),
-// not with FP16 storage, whose waves they halve; several lane groups per
+// reads the outer hops, the backward t hop and the first slice). A CU works on
+// `waves` waves' worth of workgroups at once; the busiest one, with
+// ceil(workgroups / 256) of them, sets the time: a round for each full set, and for
+// a last set that fills the share x of its places last + (1 - last) x of a round
+// (1: as long as a full one, 0: in proportion). With FP16 storage, whose workgroups
+// are short and uneven, the chip's rounds count as a whole, the last one as `tail`
+// of one on average. rb2: the cost of a slice of two right-hand sides per lane in
+// a launch of half the workgroups.
+//
+// All of these are fitted to times, `waves` too: it is the residency at which the
+// model picks the fastest launches. Registers allow more in places (FP32 kernels
+// of one field per lane hold three waves per SIMD, 12 per CU), or as much as that
+// only in some modes (two FP32 fields per lane: 165 registers, three waves; with
+// the fused CG work 171, two).
+// Fitted on MI355X to every split of t and both rb timed on up to 20 lattices
+// with 1 to 16 right-hand sides, from 16^4 to 48^4, among them 28 x 15 x 22 x 33, 9 x
+// 33 x 12 x 20 and 21^4, in FP32 with 12-real links too. By how much the choice is
+// slower than the best launch timed, on average (at most), in percent:
+//   FP64  up to 208 lanes 0.9 (8); beyond, one workgroup per CU, 1.5
+//   FP32  up to 208 lanes 0.9 (8), fused 1.5 (12); 256 lanes 2.1 (10), fused 0.6 (6);
+//         between them 1.9 (5)
+//   FP16  from 2^20 sites on 1.4 (5), fused 1.1 (5)
+// where one resident round of workgroups whatever its last round leaves idle was
+// 14 to 24 % slower (24^3 x 48 with 12 FP32 fields 757 -> 525 us), and whole rounds
+// only, with the same weights for the fused modes, 2 to 4 % (us: FP32 16^4 with 12
+// fields 56.5 -> 53, 32 x 16^2 x 32 with two 43.6 -> 40; per CG iteration 16^3 x 32
+// with six 209 -> 199, 32 x 16^2 x 32 with two 151 -> 144, FP16 32^4 223 -> 217).
+// Two right-hand sides per lane pay in FP32 (87 against 105 us for 4 fields on
+// 24^4), not with FP16 storage, whose waves they halve; several lane groups per
 // workgroup never were the fastest.
 struct MarchCost {
   int waves, waves2;
-  double prologue, prologue2, tail, rb2;
+  double prologue, prologue2, last, last2, rb2, tail;
 };
-MarchCost march_cost(int prec, bool two) {
-  if (prec == WD_FP64) return {8, 0, 0.8, 0.0, -1.0, 0.0};
-  if (prec == WD_FP32) return {8, two ? 12 : 8, 0.4, 0.7, -1.0, 1.2};
-  // FP16 storage marches only from 2^20 sites on, where eight slices beat four from
-  // three fields on (32^3 x 64 with three fields 306 / 314 us, 32^4 151 / 154)
-  return {12, 0, 1.1, 0.0, 0.5, 0.0};
+MarchCost march_cost(int prec, int n, int nrhs, bool fused) {
+  const bool two = two_workgroups(n);
+  if (prec == WD_FP64) {
+    if (!two) return {8, 0, 0.8, 0.0, 1.0, 0.0, 0.0, -1.0};
+    return {8, 0, n <= 128 ? 0.8 : 0.4, 0.0, n <= 128 ? 0.3 : 0.2, 0.0, 0.0, -1.0};
+  }
+  if (prec == WD_FP32 && two)
+    return fused ? MarchCost{8, 8, 0.4, 0.7, 0.4, 1.0, 1.3, -1.0} : MarchCost{8, 12, 0.4, 0.4, 0.4, 1.0, 1.2, -1.0};
+  if (prec == WD_FP32 && n == kMarchMaxThreads)
+    return fused ? MarchCost{12, 8, 0.4, 0.7, 0.2, 1.0, 1.3, -1.0} : MarchCost{12, 8, 0.2, 0.2, 0.1, 0.6, 1.2, -1.0};
+  if (prec == WD_FP32) return {8, 8, 0.4, 0.7, 1.0, 1.0, 1.2, -1.0};
+  if (fused && nrhs > 1) return {12, 0, 1.1, 0.0, 0.0, 0.0, 0.0, 0.5};
+  return {16, 0, 0.4, 0.0, 0.0, 0.0, 0.0, 0.3};
 }
 
 // Geometry of the t-marching kernel for a lattice, with the default launch
@@ -613,12 +633,12 @@ MarchParams march_params(const Geo& geo, int prec, int nrhs, bool fused = false)
   p.ytiles = geo.Y / ny;
   const int n = geo.X * ny;
   const int waves = (n + 63) / 64;
-  const MarchCost mc = march_cost(prec, two_workgroups(n));
+  const MarchCost mc = march_cost(prec, n, nrhs, fused);
   double best = 0.0;
-  // among equals the shorter march; in FP32 the fused CG work also takes one that
-  // costs up to 4 % more (24^4 with three fields: 54.1 ms per solve at 12 slices per
-  // workgroup, 50.2 at 6)
-  const double tie = fused && prec == WD_FP32 ? 1.04 : 1.0;
+  // among equals the shorter march; in FP32 the fused CG work on tiles up to 208
+  // lanes also takes one that costs up to 4 % more (24^4 with three fields: 311 us
+  // per iteration at 12 slices per workgroup, 287 at 6)
+  const double tie = fused && prec == WD_FP32 && two_workgroups(n) ? 1.04 : 1.0;
   // FP16 storage: one slice per workgroup (its own kernel), unless the fields and
   // links outgrow the 256 MB cache that serves the t neighbours then (about 2^20
   // sites; us, one slice / best longer march: 24^3 x 48 37.5 / 41.2, 32^4 59.9 /
@@ -632,12 +652,19 @@ MarchParams march_params(const Geo& geo, int prec, int nrhs, bool fused = false)
     const int by_waves = (rb == 1 ? mc.waves : mc.waves2) / waves;
     const int by_lds = static_cast<int>(kLdsBytes / lds);
     const int per_cu = std::max(1, std::min(by_waves, by_lds));
-    const double slots = static_cast<double>(kNumCu) * per_cu;
     const double columns = static_cast<double>(p.ytiles) * geo.Z * (nrhs / rb);
+    const double last = rb == 1 ? mc.last : mc.last2;
     // every distinct ceil(T / nt), largest first
     for (int tb = geo.T, nt = 1;;) {
-      const double x = columns * nt / slots;
-      const double rounds = mc.tail < 0.0 ? std::ceil(x) : std::max(1.0, x + mc.tail);
+      double rounds;
+      if (mc.tail < 0.0) {
+        const double busiest = std::ceil(columns * nt / kNumCu);
+        rounds = std::floor(busiest / per_cu);
+        const double share = busiest / per_cu - rounds;
+        if (share > 0.0) rounds += last + (1.0 - last) * share;
+      } else {
+        rounds = std::max(1.0, columns * nt / (static_cast<double>(kNumCu) * per_cu) + mc.tail);
+      }
       const double cost = rounds * (tb + (rb == 1 ? mc.prologue : mc.prologue2)) * (rb == 1 ? 1.0 : mc.rb2);
       if (p.tb == 0 || cost < best || (cost <= best * tie && rb == p.rb)) {
         best = p.tb == 0 ? cost : std::min(best, cost);

@@ -149,6 +149,7 @@ struct MarchParams {
   int nrhs;    // right-hand sides of the launch
   int gw;      // lane groups per workgroup
   int rb;      // right-hand sides per lane (gw * rb divides nrhs)
+  bool ahead;  // FP64: kOuterAhead
   unsigned link_bytes;    // bytes of the packed links and of one packed spinor field (used
   unsigned spinor_bytes;  // when they are read through buffer resources, below 4 GiB)
 };
@@ -561,6 +562,19 @@ constexpr std::integral_constant<int, N> kInt{};
 // sides each, fit a CU's LDS with two slices per workgroup.
 bool two_workgroups(int n) { return n <= 208; }
 
+// Whether FP64 tiles of n lanes run kOuterAhead, for `work` sites times fields: where
+// LDS holds one workgroup either way, and in the plain operator on tiles up to 128
+// lanes while the fields stay in the caches. There the outer hops, done while their
+// owners load the same lines, are worth more than the second wave per SIMD (now /
+// ahead, us, each with its best t split: 16 x 8 x 20 x 30 with four fields 43.6 / 39.8,
+// with eight 85.2 / 75.5, 10 x 10 x 20 x 40 with three 40.0 / 35.3; 33 x 9 x 20 x 30 with
+// four 125 / 127, with six 180 / 201; 12 x 8 x 11 x 71 with 14 151 / 159). The fused CG
+// work runs kOuterNow there (9 x 33 x 12 x 20 57 / 68 us per iteration).
+bool outer_ahead(int n, long work, bool fused) {
+  if (!two_workgroups(n)) return true;
+  return !fused && n <= 128 && work <= (n % 64 == 0 ? 1000000 : 500000);
+}
+
 size_t march_lds_bytes(int threads, size_t real_bytes) {
   return 2 * 24 * real_bytes * static_cast<size_t>(threads);  // two spinor slices
 }
@@ -603,10 +617,11 @@ struct MarchCost {
   int waves, waves2;
   double prologue, prologue2, last, last2, rb2, tail;
 };
-MarchCost march_cost(int prec, int n, int nrhs, bool fused) {
+MarchCost march_cost(int prec, int n, int nrhs, bool fused, bool ahead) {
   const bool two = two_workgroups(n);
   if (prec == WD_FP64) {
     if (!two) return {8, 0, 0.8, 0.0, 1.0, 0.0, 0.0, -1.0};
+    if (ahead) return {4, 0, 0.8, 0.0, 1.0, 0.0, 0.0, -1.0};
     return {8, 0, n <= 128 ? 0.8 : 0.4, 0.0, n <= 128 ? 0.3 : 0.2, 0.0, 0.0, -1.0};
   }
   if (prec == WD_FP32 && two)
@@ -622,7 +637,7 @@ MarchCost march_cost(int prec, int n, int nrhs, bool fused) {
 // choice, or ny = 0 if it does not apply (x rows longer than a workgroup, or
 // too few sites per tile).
 MarchParams march_params(const Geo& geo, int prec, int nrhs, bool fused = false) {
-  MarchParams p{0, 0, 0, 0, 0, nrhs, 1, 1, 0u, 0u};
+  MarchParams p{0, 0, 0, 0, 0, nrhs, 1, 1, false, 0u, 0u};
   const size_t real_bytes = real_bytes_of(prec);
   if (geo.X > kMarchMaxThreads) return p;
   int ny = 0;
@@ -633,7 +648,8 @@ MarchParams march_params(const Geo& geo, int prec, int nrhs, bool fused = false)
   p.ytiles = geo.Y / ny;
   const int n = geo.X * ny;
   const int waves = (n + 63) / 64;
-  const MarchCost mc = march_cost(prec, n, nrhs, fused);
+  p.ahead = prec == WD_FP64 && outer_ahead(n, static_cast<long>(geo.V) * nrhs, fused);
+  const MarchCost mc = march_cost(prec, n, nrhs, fused, p.ahead);
   double best = 0.0;
   // among equals the shorter march; in FP32 the fused CG work on tiles up to 208
   // lanes also takes one that costs up to 4 % more (24^4 with three fields: 311 us
@@ -717,7 +733,8 @@ hipError_t launch_march_t(const void* in, void* out, const void* links, const Ge
 // two LDS slices of two workgroups fit up to 208 lanes per tile (FP64, or FP32
 // with two right-hand sides per lane; half that each with one).
 //  - FP64: kOuterAhead needs 280 registers (one wave per SIMD), kOuterNow 204 to
-//    238 (two). Up to 208 lanes kOuterNow is the faster one: 24^4 with four fields
+//    238 (two). Up to 208 lanes kOuterNow is the faster one, but for the smaller
+//    tiles of outer_ahead: 24^4 with four fields
 //    235 -> 209 us, 28 x 15 x 22 x 33 71 -> 65 and with four 287 -> 222, with
 //    12-real links 24^3 x 48 131 -> 108. Beyond, LDS holds one workgroup either
 //    way and the outer hops must meet their owners' loads in L2: 32^3 x 64 357 us
@@ -750,8 +767,8 @@ hipError_t launch_march_b(const void* in, void* out, const void* links, const Ge
     }
     return run(kInt<kMarchMaxThreads>, kInt<1>, kInt<CGM != kCgNone ? kOuterAhead : kOuterNow>);
   } else {
-    return two ? run(kInt<kMarchMaxThreads>, kInt<1>, kInt<kOuterNow>)
-               : run(kInt<kMarchMaxThreads>, kInt<1>, kInt<kOuterAhead>);
+    return p.ahead ? run(kInt<kMarchMaxThreads>, kInt<1>, kInt<kOuterAhead>)
+                   : run(kInt<kMarchMaxThreads>, kInt<1>, kInt<kOuterNow>);
   }
 }
 
@@ -807,15 +824,23 @@ hipError_t launch_site(const wd_gauge* g, const void* in, void* out, const Geo& 
 
 // Whether the split kernel is the default for nrhs fields: where the t-marching
 // one does not apply, in launches too small to fill the chip with marches, and
-// in somewhat larger ones on lattices whose tiles leave lanes of their waves
-// idle (X * ny not near a multiple of 64). Measured on MI355X, t-marching
-// against split (us): 12^4 FP64 8.1 / 6.5; 15 x 9 x 14 x 21 (135 of 192 lanes)
-// FP64 12.4 / 10.1, FP32 8.8 / 6.6, with 12 fields 41.9 / 38.0, FP16 8.4 / 6.6,
-// with four 13.1 / 15.9; 20^4 (200 of 256) FP64 with two fields 56.1 / 52.9, with
-// four 105 / 108, FP32 21.3 / 19.0, with two 31.7 / 28.9, FP16 14.0 / 16.3; 18^3 x
-// 36 (216 of 256) FP64 with two 71.0 / 77.8, FP32 36.8 / 38.4; 65 x 5 x 12 x 20
-// (65 of 128) with 12 FP64 fields 197 / 175, four FP16 ones 30.5 / 28.1; but 16^4
-// (whole waves) FP64 14.8 / 16.5, 16^3 x 32 FP32 13.0 / 14.4 and FP16 8.9 / 13.0.
+// in larger ones on lattices whose tiles leave lanes of their waves idle (X * ny
+// not near a multiple of 64), up to the sites times fields at which the march
+// overtook it on 22 lattices. Measured on MI355X, t-marching / split (us) on both
+// sides of each line (lanes of the tile in brackets):
+//   12^4 FP64 8.1 / 6.7; 16^4 (256 of 256) with one FP64 field 15.5 / 17.2, FP32 7.6 /
+//   8.5, FP16 6.9 / 8.2;
+//   FP16: 15 x 9 x 14 x 21 (135 of 192) 8.6 / 6.8, with two fields 9.4 / 9.0, with three
+//   10.9 / 12.4; 65 x 5 x 20 x 40 (65 of 128) with three 59.9 / 69.5;
+//   under six tenths: 65 x 5 x 12 x 20 with 12 FP64 fields 196 / 177, 11 x 6 x 30 x 60 (66
+//   of 128) with eight 169 / 183, FP32 with six 60.9 / 59.6, with eight 76.4 / 80.9;
+//   up to 128 lanes, FP64: 10 x 10 x 20 x 40 (100 of 128) with two fields 28.6 / 28.8,
+//   with three 36.0 / 40.0; 14 x 8 x 31 x 16 (112) with three 31.3 / 31.3, with eight 66 /
+//   79; FP32 with an even number: 18 x 6 x 12 x 31 (108) with two 6.9 / 7.6, with eight
+//   23.0 / 28.1;
+//   beyond: FP64 20^4 (200 of 256) with two 54.3 / 52.6, with three 67.9 / 77.6; 18^3 x 36
+//   (162 of 192) with two 70.1 / 77.1; FP32 20^4 with two 30.3 / 28.7, with four 48.3 /
+//   52.0; 12 x 12 x 24 x 36 (144 of 192) with three 37.1 / 31.3, with four 38.4 / 41.4.
 bool use_split(const Geo& geo, const MarchParams& p, int prec) {
   if (p.ny == 0) return true;
   const long work = static_cast<long>(geo.V) * p.nrhs;
@@ -823,8 +848,19 @@ bool use_split(const Geo& geo, const MarchParams& p, int prec) {
   const int n = geo.X * p.ny;
   const int lanes = (n + 63) / 64 * 64;
   if (10 * n >= 9 * lanes) return false;  // at least nine tenths of the lanes at work
-  if (10 * n < 6 * lanes) return work <= 800000;
-  return work <= (prec == WD_FP16 ? 65536 : 450000);
+  if (prec == WD_FP16) return work <= 65536;
+  if (10 * n < 6 * lanes) return work <= (prec == WD_FP64 ? 940000 : 750000);
+  if (prec == WD_FP64) return work <= (n <= 128 && 10 * n >= 7 * lanes ? 200000 : 330000);
+  return work <= (n <= 128 && p.nrhs % 2 == 0 ? 150000 : 450000);
+}
+
+// Whether a tuning line may name the split kernel: where it is the default, or has
+// been, so that files saved then still load (it runs everywhere).
+bool split_choice(const Geo& geo, const MarchParams& p, int prec) {
+  const int n = geo.X * p.ny;
+  const int lanes = (n + 63) / 64 * 64;
+  const long most = 10 * n >= 9 * lanes ? 0 : 10 * n < 6 * lanes ? 800000 : prec == WD_FP16 ? 65536 : 450000;
+  return use_split(geo, p, prec) || static_cast<long>(geo.V) * p.nrhs <= most;
 }
 
 // Whether the t-marching tiles are whole waves (what its fused CG work needs).
@@ -988,7 +1024,7 @@ bool march_tuning_valid(const int32_t dims[4], int prec, int nrhs, const MarchTu
   const MarchParams p = march_params(geo, prec, nrhs);
   if (p.ny == 0 || nrhs < 1 || nrhs > kMaxMultiRhs) return false;
   if (t.tb == 0)  // the split kernel
-    return use_split(geo, p, prec) && t.gw == kSplitTuning.gw && t.group == kSplitTuning.group && t.rb == kSplitTuning.rb;
+    return split_choice(geo, p, prec) && t.gw == kSplitTuning.gw && t.group == kSplitTuning.group && t.rb == kSplitTuning.rb;
   if (t.tb < 1 || t.tb > geo.T || t.group < 0) return false;
   if (t.rb != 1 && t.rb != 2) return false;
   if (t.gw < 1 || nrhs % (t.gw * t.rb) != 0) return false;

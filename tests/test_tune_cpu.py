@@ -87,3 +87,23 @@ def test_bad_files(tmp_path):
     # a header-only file is valid and registers nothing
     assert w.wd_tune_load(write(tmp_path / "h.txt", [])) == w.WD_OK
     assert w.wd_tune_lookup(PROD, w.WD_FP64, 0, 1) is None
+
+
+def test_lines_for_the_split_kernel_keep_loading(tmp_path):
+    """A line that names the split kernel (tb 0) loads on every lattice and field
+    count on which that kernel has ever been the default, whatever the default is
+    now; on tiles of whole waves only for small launches."""
+    for dims, ok, refused in [
+        ((65, 5, 20, 40), {w.WD_FP64: 3, w.WD_FP32: 3, w.WD_FP16: 3}, {}),      # 65 of 128 lanes: 800000
+        ((18, 18, 18, 36), {w.WD_FP64: 2, w.WD_FP32: 2}, {w.WD_FP16: 1}),       # 162 of 192: 450000, 65536
+        ((10, 10, 20, 40), {w.WD_FP64: 5, w.WD_FP32: 5}, {w.WD_FP64: 6, w.WD_FP16: 1}),
+        ((12, 12, 8, 8), {w.WD_FP64: 16, w.WD_FP32: 16, w.WD_FP16: 7}, {w.WD_FP16: 8}),
+        ((16, 16, 16, 12), {w.WD_FP64: 1, w.WD_FP16: 1}, {w.WD_FP64: 2, w.WD_FP16: 2}),  # 49152
+    ]:
+        for prec, n in ok.items():
+            assert w.wd_tune_load(write(tmp_path / "a.txt", ["%d %d %d %d" % dims + f" {prec} 0 {n} 0 1 0 1"])) == w.WD_OK
+            assert w.wd_tune_lookup(dims, prec, 0, n) == (0, 1, 0, 1)
+        for prec, n in refused.items():
+            with pytest.raises(w.WilsonError):
+                w.wd_tune_load(write(tmp_path / "b.txt", ["%d %d %d %d" % dims + f" {prec} 0 {n} 0 1 0 1"]))
+            assert w.wd_tune_lookup(dims, prec, 0, n) is None

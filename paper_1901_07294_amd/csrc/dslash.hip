@@ -14,6 +14,7 @@
 #include <algorithm>
 #include <atomic>
 #include <cmath>
+#include <numeric>
 #include <type_traits>
 
 #include "blas.h"
@@ -150,6 +151,7 @@ struct MarchParams {
   int gw;      // lane groups per workgroup
   int rb;      // right-hand sides per lane (gw * rb divides nrhs)
   bool ahead;  // FP64: kOuterAhead
+  CgSlices cut;  // SMALL: the sites' CG slices
   unsigned link_bytes;    // bytes of the packed links and of one packed spinor field (used
   unsigned spinor_bytes;  // when they are read through buffer resources, below 4 GiB)
 };
@@ -239,7 +241,8 @@ __device__ __forceinline__ void outer_hops(const SA (&in)[RB], const LA& links, 
 
 // Doubles of LDS per lane group and right-hand side that the fused CG work
 // uses after the spinor slices: per-wave sums of two steps (tiles of at most
-// 4 waves) and the per-wave sums of <p, A p>.
+// 4 waves) and the four sums of <p, A p>. SMALL: the sites' norms of two steps
+// follow them.
 constexpr int kCgLds = 2 * 4 + 4;
 
 // Variants of the march (KIND):
@@ -258,10 +261,13 @@ constexpr int kOuterAhead = 0, kOuterNow = 1, kOneBuffer = 2, kOneSlice = 3;
 // one tile; each lane carries RB right-hand sides (links loaded once for
 // all), each with its own two LDS slices. The LDS slices hold spinors in the
 // arithmetic precision (FP32 for FP16 storage).
-// CGM (CG iterations, n a multiple of 64): kCgNorm stores the output and
-// leaves each tile slice's squared norm of it in cgf.rr; kCgUpdate does not
+// CGM (CG iterations, n a multiple of 64 unless SMALL): kCgNorm stores the output
+// and leaves each tile slice's squared norm of it in cgf.rr; kCgUpdate does not
 // store the output but applies r -= alpha A p of cgf to the field slots (x
 // and p follow in a separate kernel).
+// SMALL: the CG slices of small lattices (CgSlices) instead, and the sums of <p, A p>
+// in the split kernel's order: the same bits as that kernel's, on tiles of any
+// number of lanes.
 // The fused modes with FP32 arithmetic and one right-hand side per lane are
 // compiled for three waves per SIMD (the plain FP32-arithmetic kernel's
 // occupancy), at the cost of a few spilled registers in FP32 storage, which
@@ -280,7 +286,7 @@ constexpr int march_waves_per_eu() {
   return RB == 1 && sizeof(typename Packed<T>::R) == 4 && CGM != kCgNone ? 3 : 1;
 }
 
-template <typename T, bool C12, int MAXT, int RB, int CGM, bool BUF, int KIND>
+template <typename T, bool C12, int MAXT, int RB, int CGM, bool BUF, int KIND, bool SMALL>
 __global__ __launch_bounds__(MAXT)
 __attribute__((amdgpu_waves_per_eu(march_waves_per_eu<CGM, T, RB, KIND>()))) void dslash_march_kernel(
     const typename Packed<T>::S* __restrict__ in, typename Packed<T>::S* __restrict__ out,
@@ -291,8 +297,8 @@ __attribute__((amdgpu_waves_per_eu(march_waves_per_eu<CGM, T, RB, KIND>()))) voi
   using GS = typename Packed<T>::S;
   constexpr int kPlanes = sizeof(R) == 8 ? 12 : 6;
   extern __shared__ __align__(16) unsigned char smem[];
-  const int n = geo.X * p.ny;  // sites per tile == lanes per lane group
-  const int slot = static_cast<int>(threadIdx.x) / n;
+  const int n = geo.X * p.ny;  // sites per tile == lanes per lane group (SMALL: rounded up to whole waves)
+  const int slot = SMALL ? 0 : static_cast<int>(threadIdx.x) / n;
   // slice (buffer f, right-hand side r) of this lane group
   constexpr bool ONE = KIND == kOneSlice;
   constexpr bool NOW = KIND == kOuterNow || KIND == kOneBuffer;
@@ -302,7 +308,9 @@ __attribute__((amdgpu_waves_per_eu(march_waves_per_eu<CGM, T, RB, KIND>()))) voi
   SV* const base = reinterpret_cast<SV*>(smem) + slot * kSlices * RB * kPlanes * n;
   const long V = geo.V;
 
-  const int tid = static_cast<int>(threadIdx.x) - slot * n;
+  const int lane = static_cast<int>(threadIdx.x) - slot * n;
+  const bool live = !SMALL || lane < n;
+  const int tid = live ? lane : n - 1;  // lanes beyond the tile follow its last site and store nothing
   const int xl = tid % geo.X;
   const int yl = tid / geo.X;
   // The lane groups of a workgroup march in lock step (one barrier per
@@ -377,18 +385,25 @@ __attribute__((amdgpu_waves_per_eu(march_waves_per_eu<CGM, T, RB, KIND>()))) voi
 #pragma unroll
     for (int r = 0; r < RB; ++r) {
       const double* pp = cgf.pap + static_cast<long>(diags.idx[rhs0 + r]) * cgf.npap;
-      double t = 0.0;
-      int i = tid;
-      for (; i + 3 * n < cgf.npap; i += 4 * n) {  // four loads in flight, added in order
-        const double a0 = pp[i], a1 = pp[i + n], a2 = pp[i + 2 * n], a3 = pp[i + 3 * n];
-        t += a0;
-        t += a1;
-        t += a2;
-        t += a3;
+      if constexpr (SMALL) {  // the split kernel's order: 256 shares, in four waves' worth
+        for (int g = lane >> 6; g < 4; g += (n + 63) / 64) {
+          const double t = wave_total(strided_sum256(pp, cgf.npap, 64 * g + (lane & 63)));
+          if ((lane & 63) == 0) cgs[r * kCgLds + 8 + g] = t;
+        }
+      } else {
+        double t = 0.0;
+        int i = tid;
+        for (; i + 3 * n < cgf.npap; i += 4 * n) {  // four loads in flight, added in order
+          const double a0 = pp[i], a1 = pp[i + n], a2 = pp[i + 2 * n], a3 = pp[i + 3 * n];
+          t += a0;
+          t += a1;
+          t += a2;
+          t += a3;
+        }
+        for (; i < cgf.npap; i += n) t += pp[i];
+        t = wave_total(t);
+        if ((tid & 63) == 0) cgs[r * kCgLds + 8 + (tid >> 6)] = t;
       }
-      for (; i < cgf.npap; i += n) t += pp[i];
-      t = wave_total(t);
-      if ((tid & 63) == 0) cgs[r * kCgLds + 8 + (tid >> 6)] = t;
     }
   }
 
@@ -415,7 +430,7 @@ __attribute__((amdgpu_waves_per_eu(march_waves_per_eu<CGM, T, RB, KIND>()))) voi
     for (int r = 0; r < RB; ++r) {
       cx<R> psi[12];
       load_spinor(inr[r], V, st, psi);
-      lds_store_spinor(base + (kSlices * r) * kPlanes * n, n, tid, psi);
+      if (live) lds_store_spinor(base + (kSlices * r) * kPlanes * n, n, tid, psi);
     }
   }
   __syncthreads();
@@ -423,12 +438,12 @@ __attribute__((amdgpu_waves_per_eu(march_waves_per_eu<CGM, T, RB, KIND>()))) voi
 #pragma unroll
     for (int r = 0; r < RB; ++r) {
       double t = 0.0;
-      for (int w = 0; w < n / 64; ++w) t += cgs[r * kCgLds + 8 + w];
+      for (int w = 0; w < (SMALL ? 4 : n / 64); ++w) t += cgs[r * kCgLds + 8 + w];
       const long k = diags.idx[rhs0 + r];
       double* sc = cgf.scal + k * kScalars;
       bool flag = false;
       alpha[r] = cg_alpha(t, sc[kRr], &flag);
-      if (tid == 0 && b == 0) {  // the field's first tile: one workgroup per field
+      if (lane == 0 && b == 0) {  // the field's first tile: one workgroup per field
         sc[kPap] = t;
         sc[kAlpha] = alpha[r];
         sc[kRrPrev] = sc[kRr];
@@ -476,7 +491,7 @@ __attribute__((amdgpu_waves_per_eu(march_waves_per_eu<CGM, T, RB, KIND>()))) voi
       cx<R> psi[12];
       load_spinor(inr[r], V, sn, psi);
       if (!RELOAD && more) {
-        lds_store_spinor(nxt[r], n, tid, psi);
+        if (live) lds_store_spinor(nxt[r], n, tid, psi);
         if (!NOW && r == 0) outer_hops<C12>(inr, lk, V, sn, dzp, dzm, y_fwd_out, dyp, y_bwd_out, dym, nacc);
       }
       cx<R> h[6], g[6];
@@ -495,7 +510,16 @@ __attribute__((amdgpu_waves_per_eu(march_waves_per_eu<CGM, T, RB, KIND>()))) voi
       lds_load_spinor(cur[r], n, tid, psi);
       cx<R> o[12];
       epilogue(psi, acc[r], diag[r], gamma5, o);
-      if constexpr (CGM == kCgUpdate) {
+      if constexpr (SMALL) {
+        double v = 0.0;
+        if (live) {
+          if constexpr (CGM == kCgUpdate)
+            v = cg_site_update_r(static_cast<GS*>(cgf.r) + diags.idx[rhs0 + r] * stride, V, st, o, alpha[r]);
+          else
+            v = store_site_norm(outr[r], V, st, o);
+          cgs[RB * kCgLds + n * (RB * ((t - t0) & 1) + r) + lane] = v;
+        }
+      } else if constexpr (CGM == kCgUpdate) {
         const long k = diags.idx[rhs0 + r];
         double v = cg_site_update_r(static_cast<GS*>(cgf.r) + k * stride, V, st, o, alpha[r]);
         v = wave_total(v);
@@ -530,7 +554,8 @@ __attribute__((amdgpu_waves_per_eu(march_waves_per_eu<CGM, T, RB, KIND>()))) voi
         for (int r = 0; r < RB; ++r) load_spinor(inr[r], V, sn, psn[r]);
         __syncthreads();
 #pragma unroll
-        for (int r = 0; r < RB; ++r) lds_store_spinor(nxt[r], n, tid, psn[r]);
+        for (int r = 0; r < RB; ++r)
+          if (live) lds_store_spinor(nxt[r], n, tid, psn[r]);
       }
     } else if constexpr (!NOW) {
 #pragma unroll
@@ -539,7 +564,24 @@ __attribute__((amdgpu_waves_per_eu(march_waves_per_eu<CGM, T, RB, KIND>()))) voi
         for (int c = 0; c < 12; ++c) acc[r][c] = nacc[r][c];
     }
     if (!ONE || CGM != kCgNone) __syncthreads();
-    if constexpr (CGM != kCgNone) {
+    if constexpr (SMALL) {
+      // the sums of the slices that the tile holds, 32 lanes each, every site on
+      // the lane that it has in the split kernel (the next write to these words is
+      // two steps on, behind the next barrier)
+      const int first = n * ((t * geo.Z + z) * p.ytiles + yt);  // the tile's first site
+      const int skip = first % kSplitSites;
+      const int slices = (skip + n + kSplitSites - 1) / kSplitSites;
+      for (int h = lane >> 5; (h & ~1) < slices; h += (n + 63) / 64 * 2) {
+        const int l = kSplitSites * h + (lane & 31) - skip;
+#pragma unroll
+        for (int r = 0; r < RB; ++r) {
+          const double v =
+              half_wave_total(l >= 0 && l < n ? cgs[RB * kCgLds + n * (RB * ((t - t0) & 1) + r) + l] : 0.0);
+          if ((lane & 31) == 0 && h < slices)
+            cgf.rr[static_cast<long>(diags.idx[rhs0 + r]) * cgf.nslices + p.cut.of(first) + h] = v;
+        }
+      }
+    } else if constexpr (CGM != kCgNone) {
       // the squared norm of this tile slice (Q p or r): its waves in order (the next write to these
       // words is two steps on, behind the next barrier)
       if (tid == 0) {
@@ -636,8 +678,8 @@ MarchCost march_cost(int prec, int n, int nrhs, bool fused, bool ahead) {
 // Geometry of the t-marching kernel for a lattice, with the default launch
 // choice, or ny = 0 if it does not apply (x rows longer than a workgroup, or
 // too few sites per tile).
-MarchParams march_params(const Geo& geo, int prec, int nrhs, bool fused = false) {
-  MarchParams p{0, 0, 0, 0, 0, nrhs, 1, 1, false, 0u, 0u};
+MarchParams march_params(const Geo& geo, int prec, int nrhs, bool fused = false, int most_rb = 2) {
+  MarchParams p{0, 0, 0, 0, 0, nrhs, 1, 1, false, {}, 0u, 0u};
   const size_t real_bytes = real_bytes_of(prec);
   if (geo.X > kMarchMaxThreads) return p;
   int ny = 0;
@@ -662,7 +704,7 @@ MarchParams march_params(const Geo& geo, int prec, int nrhs, bool fused = false)
   // 1273 / 1152)
   const bool single = prec == WD_FP16 && geo.V < (1 << 20);
   if (single) p.tb = 1;
-  for (int rb = 1; rb <= 2 && !single; ++rb) {
+  for (int rb = 1; rb <= most_rb && !single; ++rb) {
     const size_t lds = march_lds_bytes(n, real_bytes) * (rb == 2 && two_workgroups(n) ? 2 : 1);  // one buffer per field
     if (rb == 2 && (mc.waves2 == 0 || nrhs % 2 != 0 || lds > kLdsBytes)) break;
     const int by_waves = (rb == 1 ? mc.waves : mc.waves2) / waves;
@@ -699,7 +741,7 @@ MarchParams march_params(const Geo& geo, int prec, int nrhs, bool fused = false)
   return p;
 }
 
-template <typename T, bool C12, int MAXT, int RB, int CGM, bool BUF, int KIND>
+template <typename T, bool C12, int MAXT, int RB, int CGM, bool BUF, int KIND, bool SMALL = false>
 hipError_t launch_march_t(const void* in, void* out, const void* links, const Geo& geo,
                           const Diag<typename Packed<T>::R>& diag, long stride, int g5,
                           MarchParams p, const CgFuse& f, hipStream_t st) {
@@ -709,12 +751,13 @@ hipError_t launch_march_t(const void* in, void* out, const void* links, const Ge
   const int n = geo.X * p.ny;
   size_t lds = static_cast<size_t>(p.gw) * RB * march_lds_bytes(n, sizeof(R)) / (KIND == kOuterAhead || KIND == kOuterNow ? 1 : 2);
   if (CGM != kCgNone) lds += static_cast<size_t>(p.gw) * RB * kCgLds * sizeof(double);
+  if (SMALL) lds += 2 * static_cast<size_t>(RB) * n * sizeof(double);
   if (lds > kLdsBytes) return hipErrorInvalidValue;
   // raise the kernel's dynamic LDS limit once to the whole LDS of a CU
   static std::atomic<int> attr_set{0};
   if (!attr_set.load(std::memory_order_acquire)) {
     hipError_t e = hipFuncSetAttribute(
-        reinterpret_cast<const void*>(&dslash_march_kernel<T, C12, MAXT, RB, CGM, BUF, KIND>),
+        reinterpret_cast<const void*>(&dslash_march_kernel<T, C12, MAXT, RB, CGM, BUF, KIND, SMALL>),
         hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kLdsBytes));
     if (e != hipSuccess) return e;
     attr_set.store(1, std::memory_order_release);
@@ -723,7 +766,7 @@ hipError_t launch_march_t(const void* in, void* out, const void* links, const Ge
   const int eighth = (p.nb + kNumXcd - 1) / kNumXcd;  // larger groups mean the same
   if (p.group > eighth) p.group = eighth;
   const unsigned grid = static_cast<unsigned>(p.group == eighth ? eighth * kNumXcd : p.nb);
-  dslash_march_kernel<T, C12, MAXT, RB, CGM, BUF, KIND><<<grid, p.gw * n, lds, st>>>(
+  dslash_march_kernel<T, C12, MAXT, RB, CGM, BUF, KIND, SMALL><<<grid, SMALL ? (n + 63) / 64 * 64 : p.gw * n, lds, st>>>(
       static_cast<const SV*>(in), static_cast<SV*>(out), static_cast<const LV*>(links), geo, diag,
       stride, g5, p, f);
   return hipGetLastError();
@@ -784,6 +827,33 @@ hipError_t launch_march(const void* in, void* out, const void* links, const Geo&
   return launch_march_b<T, C12, CGM, false>(in, out, links, geo, diag, stride, g5, p, f, st);
 }
 
+// The CG slices of a small lattice.
+CgSlices cg_slices(const Geo& geo, const MarchParams& p) {
+  const int tile = geo.X * p.ny;
+  return {tile % kSplitSites == 0 ? 0 : tile, tile == 0 ? 0 : std::lcm(tile, kSplitSites)};
+}
+
+// The march with the CG slices of small lattices, mode CGM of the launch: one
+// field per lane, workgroups of whole waves.
+template <typename T, bool C12, int CGM>
+hipError_t launch_march_small(const void* in, void* out, const void* links, const Geo& geo,
+                              const Diag<typename Packed<T>::R>& diag, long stride, int g5, const MarchParams& m,
+                              const CgFuse& f, hipStream_t st) {
+  const int prec = sizeof(T) == 8 ? WD_FP64 : sizeof(T) == 4 ? WD_FP32 : WD_FP16;
+  MarchParams p = march_params(geo, prec, m.nrhs, true, 1);
+  if (p.ny == 0 || m.link_bytes == 0 || m.spinor_bytes == 0) return hipErrorInvalidValue;
+  p.link_bytes = m.link_bytes;
+  p.spinor_bytes = m.spinor_bytes;
+  p.cut = cg_slices(geo, p);
+  const auto run = [&](auto kind) {
+    return launch_march_t<T, C12, kMarchMaxThreads, 1, CGM, true, decltype(kind)::value, true>(
+        in, out, links, geo, diag, stride, g5, p, f, st);
+  };
+  if constexpr (sizeof(T) == 8) return p.ahead ? run(kInt<kOuterAhead>) : run(kInt<kOuterNow>);
+  if constexpr (sizeof(T) == 4) return p.tb == 1 ? run(kInt<kOneSlice>) : run(kInt<kOuterAhead>);
+  if constexpr (sizeof(T) == 2) return p.tb == 1 ? run(kInt<kOneSlice>) : hipErrorInvalidValue;
+}
+
 // The split kernel: mode CGM of the launch.
 template <typename T, bool C12, int CGM, int FOLD = kFoldNone>
 hipError_t launch_split(const void* in, void* out, const void* links, const Geo& geo,
@@ -793,6 +863,7 @@ hipError_t launch_split(const void* in, void* out, const void* links, const Geo&
   SplitParams p{geo.X, geo.Y, geo.Z, geo.T, geo.X, geo.XY, geo.XYZ, geo.V};
   p.nrhs = m.nrhs;
   p.ny = m.ny;
+  p.cut = cg_slices(geo, m);
   p.link_bytes = m.link_bytes;
   p.spinor_bytes = m.spinor_bytes;
   SplitCoef<R> cf{};
@@ -866,11 +937,31 @@ bool split_choice(const Geo& geo, const MarchParams& p, int prec) {
 // Whether the t-marching tiles are whole waves (what its fused CG work needs).
 bool whole_waves(const Geo& geo, const MarchParams& p) { return p.ny > 0 && (geo.X * p.ny) % 64 == 0; }
 
-// Whether the fused CG work runs in the split kernel, with slices of 32 sites:
-// on lattices small enough for it to be the faster one with any number of
-// fields, and, up to 131072 sites (4096 partial sums, which every workgroup of
-// the kernel that follows reads), where the t-marching kernel cannot fuse.
+// Whether the fused CG work sums slices of 32 sites (CgSlices), which the split
+// kernel and the march (SMALL) both hold, so that a launch can take the faster
+// one for its number of fields and a field keeps its bits: on small lattices, and,
+// up to 131072 sites (some 5000 partial sums, which every workgroup of the kernel
+// that follows reads), where the march's own slices need tiles of whole waves.
 bool small_slices(const Geo& geo, const MarchParams& p) { return geo.V <= (whole_waves(geo, p) ? 16384 : 131072); }
+
+// Which of the two runs: the march beyond these sites times fields, where it
+// overtook the split kernel on 20 lattices (split / march, us per CG iteration):
+// FP16 12^4 with three fields 35.9 / 38.5, with six 52.1 / 47.1, 16^2 x 8^2 with 16 79.1 /
+// 58.0, 15 x 16^2 x 32 with eight 279 / 180; FP64 8^3 x 16 with six 40.9 / 41.2, with
+// eight 48.3 / 46.2, 14^4 with three 80.0 / 85.0, 12^2 x 24 x 36 97.7 / 86.0, 65 x 5 x 12 x 20
+// with four 208 / 196; FP32 18^4 with two 85.5 / 83.6, 12^4 with 16 109 / 125, 20^3 x 16
+// with three 144 / 125, 15 x 16^2 x 32 54.5 / 48.6, with two 92.0 / 79.3, but 12 x 15 x 24 x
+// 7 with four 49 / 56 (marches of seven slices).
+bool small_march(const Geo& geo, const MarchParams& p, int prec) {
+  if (p.ny == 0) return false;
+  const long work = static_cast<long>(geo.V) * p.nrhs;
+  if (prec == WD_FP16) return work > 80000;
+  const int n = geo.X * p.ny;
+  const int lanes = (n + 63) / 64 * 64;
+  if (10 * n >= 9 * lanes) return work > (prec == WD_FP64 ? 60000 : 150000);
+  if (10 * n >= 6 * lanes) return work > (prec == WD_FP64 ? 120000 : 350000);
+  return prec == WD_FP64 && work > 300000;
+}
 
 // The tuning choice that stands for the split kernel.
 constexpr MarchTuning kSplitTuning{0, 1, 0, 1};
@@ -917,6 +1008,13 @@ hipError_t launch_typed(const wd_gauge* g, const void* in, void* out, const Geo&
       return hipErrorInvalidValue;
     split = small_slices(geo, p);
     if (!split && !whole_waves(geo, p)) return hipErrorInvalidValue;
+    if (split && small_march(geo, p, g->prec)) {
+      if (cg->mode == kCgNorm && cg->p_out == nullptr)
+        return launch_march_small<T, C12, kCgNorm>(in, out, g->links, geo, diag, stride, g5, p, *cg, st);
+      if (cg->mode == kCgUpdate)
+        return launch_march_small<T, C12, kCgUpdate>(in, nullptr, g->links, geo, diag, stride, g5, p, *cg, st);
+      return hipErrorInvalidValue;
+    }
     if (split && p.ny == 0 && g->prec == WD_FP16 && cg->p_out == nullptr && work > kSiteCgSites)
       return launch_site_cg(g, masses, nrhs, fields, in, out, *cg, st);
     if (cg->mode == kCgNorm && cg->p_out != nullptr)
@@ -971,7 +1069,7 @@ hipError_t launch_dslash_multi(const wd_gauge* g, const double* masses, int nrhs
 int cg_fuse_slices(const int32_t dims[4], int prec) {
   const Geo geo = make_geo(dims);
   const MarchParams p = march_params(geo, prec, 1);
-  if (small_slices(geo, p)) return (geo.V + kSplitSites - 1) / kSplitSites;
+  if (small_slices(geo, p)) return cg_slices(geo, p).of(geo.V - 1) + 1;
   if (!whole_waves(geo, p)) return 0;
   const long n = static_cast<long>(geo.T) * geo.Z * p.ytiles;
   return n <= 0x7fffffffL ? static_cast<int>(n) : 0;
@@ -992,7 +1090,8 @@ bool cg_fuse_update(const int32_t dims[4], int prec) {
 bool cg_fold_p(const int32_t dims[4], int prec, int n) {
   const Geo geo = make_geo(dims);
   const long most = prec == WD_FP64 ? 16384 : prec == WD_FP32 ? 32768 : 98304;
-  return static_cast<long>(geo.V) * n <= most && small_slices(geo, march_params(geo, prec, 1));
+  const MarchParams p = march_params(geo, prec, n);
+  return static_cast<long>(geo.V) * n <= most && small_slices(geo, p) && !small_march(geo, p, prec);
 }
 
 hipError_t launch_dslash_cg(const wd_gauge* g, const double* masses, int nrhs, const int* fields,

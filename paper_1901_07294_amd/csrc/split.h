@@ -34,6 +34,16 @@ namespace wd {
 constexpr int kSplitSites = 32;     // sites per workgroup
 constexpr int kSplitThreads = 256;  // (direction, sign, site)
 
+// CG slices of small lattices: runs of kSplitSites consecutive sites, cut where a
+// tile of the t-marching kernel begins (tiles are tile >= 64 consecutive sites; 0:
+// no cuts), so that a workgroup of either kernel holds whole slices.
+struct CgSlices {
+  int tile;
+  int both;  // the least common multiple of tile and kSplitSites
+  // the slice of site s: one begins at every run and at every tile, not two where both do
+  __host__ __device__ int of(int s) const { return s / kSplitSites + (tile == 0 ? 0 : s / tile - s / both); }
+};
+
 // The sites of a field, or (eo) of the output half field: rows of X sites, with
 // the strides of y, z and t. eo: the outputs have parity `parity`, the inputs
 // the other one; both half fields have the same half-site order.
@@ -47,6 +57,7 @@ struct SplitParams {
   int per;     // workgroups (a tile of one field each) per XCD; the last may have fewer
   int nrhs;
   int ny;      // y rows per tile of the t-marching kernel, 0 where it does not apply
+  CgSlices cut;  // the sites' CG slices
   unsigned link_bytes;    // bytes of the packed links and of one packed spinor field
   unsigned spinor_bytes;  // (used when they are read through buffer resources)
 };
@@ -236,6 +247,12 @@ __global__ __launch_bounds__(kSplitThreads) void split_hop_kernel(
   const bool valid = s0 < p.V;
   const int s = valid ? s0 : p.V - 1;
   const int nb = split_neighbour(p, mu, up, s);
+  // the run's (first) CG slice, and the site at which a tile that begins inside the run cuts it in two
+  int slice = tile, cut = kSplitSites;
+  if (CGM != kCgNone && p.cut.tile != 0) {
+    slice = p.cut.of(tile * kSplitSites);
+    cut = (tile * kSplitSites / p.cut.tile + 1) * p.cut.tile - tile * kSplitSites;
+  }
 
   cx<R> u[9], psi[12];
   if (lf == lb) {
@@ -401,8 +418,13 @@ __global__ __launch_bounds__(kSplitThreads) void split_hop_kernel(
       double v = red[0][site];
 #pragma unroll
       for (int i = 1; i < 6; ++i) v += red[i][site];
+      if (cut < kSplitSites && tile * kSplitSites + cut < p.V) {
+        const double second = half_wave_total(site < cut ? 0.0 : v);
+        if (site == 0) cgf.rr[k * cgf.nslices + slice + 1] = second;
+        v = site < cut ? v : 0.0;
+      }
       v = half_wave_total(v);
-      if (site == 0) cgf.rr[k * cgf.nslices + tile] = v;
+      if (site == 0) cgf.rr[k * cgf.nslices + slice] = v;
     }
   }
 }

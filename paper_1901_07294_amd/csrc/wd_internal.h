@@ -137,9 +137,9 @@ bool tuned_lookup(const int32_t dims[4], int prec, int c12, int nrhs, MarchTunin
 // for r -= alpha A p (alpha = <r,r> / <p,Ap> reduced from pap) instead of
 // being stored, and each slice leaves its <r,r>; x += alpha p is left
 // to the p update, which reads p anyway.
-// A slice is 32 consecutive sites on small lattices (the split kernel's
-// workgroup), else a tile's x rows at one z and t: fixed by the lattice, not by
-// the launch.
+// A slice is 32 consecutive sites on small lattices (cut where a tile of the
+// march begins, CgSlices), else a tile's x rows at one z and t: fixed by the
+// lattice, not by the launch.
 enum : int { kCgNone = 0, kCgNorm = 1, kCgUpdate = 2 };
 // kCgNorm with p_out set also forms the direction it is applied to: `in` is the
 // old p, p_out = r + beta p (another buffer) with beta from the <r,r> partial

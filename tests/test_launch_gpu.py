@@ -383,3 +383,94 @@ def test_folded_directions_against_launches_of_their_own(dims, inner, eo, c12, m
     for every in (5, 12):
         assert np.array_equal(solve(bs[:2], every), ref), every
     assert np.array_equal(solve(bs, 5)[:2], ref)
+
+
+def normal_solver(dims, inner, seed, n, c12=False):
+    """Solves (g5 D)^2 x = b for the given fields of n seeded sources: returns
+    (U, sources, masses, solve(fields, every, tol, max_iter, use_graph) -> x [fields])."""
+    U = li.near_unity_gauge(dims, seed, 0.3)
+    bs = li.gaussian_spinors(dims, [seed + 1 + k for k in range(n)])
+    masses = [0.05 + 0.02 * k for k in range(n)]
+    prec = PRECS[inner]
+    ghi, glo = DeviceGauge(U, w.WD_FP64), DeviceGauge(U, prec, c12)
+
+    def solve(fields, every=5, tol=1e-10, max_iter=2000, use_graph=0):
+        m = len(fields)
+        x = ghi.spinor(m)
+        ws = torch.empty(w.cg_workspace_bytes(dims, m, prec), dtype=torch.uint8, device="cuda")
+        rc, stats = w.cg_solve_normal(ghi.handle, glo.handle, [masses[k] for k in fields], m,
+                                      ghi.pack(bs[list(fields)], nrhs=m), x,
+                                      dict(tol=tol, max_iter=max_iter, inner=prec, delta=min(0.1, tol * 1e9),
+                                           check_every=every, x0_given=0, use_graph=use_graph), ws)
+        assert rc == (w.WD_OK if tol > 1e-20 else w.WD_ERR_NOT_CONVERGED), stats
+        return ghi.unpack(x, nrhs=m).reshape(m, *bs.shape[1:])
+
+    return U, bs, masses, solve
+
+
+@pytest.mark.parametrize("dims,inner,many", [
+    ((16, 8, 16, 8), "fp64", 4),    # tiles of whole waves, 128 lanes
+    ((16, 8, 16, 8), "fp32", 10),
+    ((16, 8, 16, 8), "fp16", 5),
+    ((15, 16, 7, 9), "fp64", 4),    # 240 of 256 lanes: every second tile begins inside a slice
+    ((15, 16, 7, 9), "fp32", 10),
+    ((15, 16, 7, 9), "fp16", 6),
+    ((13, 10, 15, 16), "fp64", 4),  # 130 of 192 lanes
+    ((13, 10, 15, 16), "fp32", 12),
+    ((13, 10, 15, 16), "fp16", 3),
+    ((65, 5, 8, 9), "fp64", 13),    # 65 of 128 lanes, five y tiles
+    ((65, 5, 8, 9), "fp16", 4),
+], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_small_solves_in_both_fused_kernels(dims, inner, many):
+    """On small lattices a solve of one field takes eight lanes per site and a
+    batch the t-marching kernel: the same bits for the first and the last field,
+    eager and replayed, and the oracle's true residual."""
+    print(f"case small solves dims={dims} inner={inner} nrhs={many}", flush=True)
+    U, bs, masses, solve = normal_solver(dims, inner, 151, many)
+    xs = solve(range(many))
+    for k in (0, many - 1):
+        assert np.array_equal(xs[k], solve([k])[0]), k
+        r = bs[k] - oracle.normal_op(U, masses[k], xs[k])
+        assert np.linalg.norm(r) <= 1e-10 * np.linalg.norm(bs[k])
+    assert np.array_equal(xs, solve(range(many), use_graph=1))
+
+
+@pytest.mark.parametrize("inner", ["fp32", "fp16"])
+@pytest.mark.parametrize("dims", [(16, 16, 9, 8), (24, 8, 12, 8)], ids=["256_lanes", "192_lanes"])
+def test_marching_solves_keep_bits(dims, inner, tmp_path):
+    """Solves on lattices whose fused launches march: the same bits whatever
+    launch is registered (one or two fields per lane, two lane groups per
+    workgroup, marches of one, three and all slices), each field alone, and in
+    chunks of 1, 3 and 8 iterations (the x update of every second one waits)."""
+    print(f"case marching solves dims={dims} inner={inner}", flush=True)
+    U, bs, masses, solve = normal_solver(dims, inner, 161, 2)
+    ref = solve([0, 1])
+    for k in range(2):
+        r = bs[k] - oracle.normal_op(U, masses[k], ref[k])
+        assert np.linalg.norm(r) <= 1e-10 * np.linalg.norm(bs[k])
+        assert np.array_equal(ref[k], solve([k])[0])
+    key = " ".join(str(v) for v in (*dims, PRECS[inner], 0, 2))
+    for line in ("1 1 0 1", "3 1 0 1", "8 1 1 1", "2 2 0 1", "1 1 0 2", "3 1 0 2", "8 1 1 2"):
+        f = tmp_path / "tune.txt"
+        f.write_text(f"{HEADER}{key} {line}\n")
+        w.wd_tune_reset()
+        w.wd_tune_load(str(f))
+        assert np.array_equal(solve([0, 1]), ref), line
+    w.wd_tune_reset()
+    fixed = [solve([0, 1], every=e, tol=1e-30, max_iter=16) for e in (1, 3, 8)]
+    assert np.array_equal(fixed[0], fixed[1]) and np.array_equal(fixed[0], fixed[2])
+
+
+@pytest.mark.parametrize("inner", ["fp32", "fp16"])
+def test_solves_without_fused_work(inner):
+    """Above 131072 sites with tiles of 200 lanes (not whole waves) nothing is
+    fused: the x, r and p updates are launches of their own. Oracle residual, and
+    a field's bits alone as beside another."""
+    dims = (20, 20, 20, 18)
+    print(f"case unfused solve dims={dims} inner={inner}", flush=True)
+    U, bs, masses, solve = normal_solver(dims, inner, 171, 2)
+    both = solve([0, 1])
+    assert np.array_equal(both[0], solve([0])[0])
+    for k in range(2):
+        r = bs[k] - oracle.normal_op(U, masses[k], both[k])
+        assert np.linalg.norm(r) <= 1e-10 * np.linalg.norm(bs[k])

@@ -29,20 +29,30 @@ __device__ __forceinline__ double wave_total(double v) {
   return v;
 }
 
-// Share i of 256 of pp[0..np): pp[i + 256 j] added in order of j, with eight
-// loads in flight (24^4 has 1728 partial sums: one round of memory latency).
-// Every kernel that reduces partial sums adds these shares in waves of 64 and
-// the four waves' sums in order, so that all of them get the same bits.
-__device__ __forceinline__ double strided_sum256(const double* __restrict__ pp, int np, int i) {
+// Share i of 256 of pp[0..np): pp[i + 256 j] added in order of j, with N loads in
+// flight.
+template <int N>
+__device__ __forceinline__ double strided_sum256_by(const double* __restrict__ pp, int np, int i) {
   double s = 0.0;
-  for (; i < np; i += 8 * 256) {
-    double a[8];
+  for (; i < np; i += N * 256) {
+    double a[N];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) a[j] = i + 256 * j < np ? pp[i + 256 * j] : 0.0;
+    for (int j = 0; j < N; ++j) a[j] = i + 256 * j < np ? pp[i + 256 * j] : 0.0;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) s += a[j];
+    for (int j = 0; j < N; ++j) s += a[j];
   }
   return s;
+}
+// ... in one round of memory latency for up to 3072 partial sums and two for 6144 (a
+// lattice of 131072 sites has up to 5000). A round is latency ahead of a workgroup's
+// first site: with eight loads in flight for all counts, a solve's iteration took 2 to
+// 4 % longer on 65000 sites (20^3 x 16 and 19 x 7 x 20 x 23, FP32). Twelve take 8 to 16
+// more registers in the small solves' kernels, a wave per SIMD in FP16 (-1 to -2 %
+// on 18^4); sixteen took two. Every kernel that reduces partial sums adds these
+// shares in waves of 64 and the four waves' sums in order, so that all of them get
+// the same bits.
+__device__ __forceinline__ double strided_sum256(const double* __restrict__ pp, int np, int i) {
+  return np <= 8 * 256 ? strided_sum256_by<8>(pp, np, i) : strided_sum256_by<12>(pp, np, i);
 }
 
 // Squared norm of two components of a site. A site's norm adds its six pairs

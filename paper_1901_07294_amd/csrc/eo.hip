@@ -26,8 +26,19 @@ constexpr int kEoBlock = 256;
 // split: 24^4 110 / 97 us, 24^3 x 48 235 / 201, 32^3 x 64 756 / 675, with two
 // fields on 24^4 179 / 146); with FP32 arithmetic only while the launch is small
 // (FP32: 16^4 16.4 / 14.0, with four fields 27.3 / 31.5; FP16: 12^4 13.9 / 12.1,
-// 16^4 with two fields 14.8 / 17.3, 24^4 27.7 / 33.1). Same bits either way.
-bool use_split_eo(int prec, long Vh, int nrhs) { return prec == WD_FP64 || Vh * nrhs <= 48000; }
+// 16^4 with two fields 14.8 / 17.3, 24^4 27.7 / 33.1). Between those, FP64 launches of
+// up to 65536 half sites are one wave per SIMD of the other kernel, which then ends
+// with its only round, and split ones three rounds of workgroups (16^4 with two
+// fields 28.8 / 31.6, 12-real links 26.4 / 30.8; 16^3 x 32 37.1 / 37.3, 29.8 / 34.7; beyond
+// it, 16^3 x 24 with two fields 56.0 / 43.9). 12-real links, a third less to read, move
+// the lower end (8^2 x 12 x 16 with eight fields 20.6 / 22.3, else 22.6 / 21.3). Fused
+// FP64 hops are always split (an iteration on 16^4 with two fields 93 / 89). Same bits
+// either way.
+bool use_split_eo(int prec, bool c12, long Vh, int nrhs) {
+  const long w = Vh * nrhs;
+  if (prec != WD_FP64) return w <= 48000;
+  return w <= (c12 ? 48000 : 52000) || w > 65536;
+}
 
 // One lane per output half site, or (p.eo == 0) per site of a whole lattice.
 // Workgroups of 256 half sites; the links and the
@@ -179,18 +190,22 @@ hipError_t launch_hop_t(const wd_gauge* g, int p, const void* in, const void* w,
   sp.nrhs = set.n;
   sp.link_bytes = half < (1ul << 32) ? static_cast<unsigned>(half) : 0u;
   sp.spinor_bytes = stride * 16 < (1l << 32) ? static_cast<unsigned>(stride * 16) : 0u;
-  if (FOLD != kFoldNone || (use_split_eo(g->prec, geo.Vh, set.n) && !(CGM != kCgNone && wide_slices(geo.Vh))))
+  if constexpr (FOLD != kFoldNone || (sizeof(R) == 8 && CGM != kCgNone)) {
     return launch_split_hop<T, C12, CGM, FOLD>(in, w, out, lp, lq, cf, stride, g5, sp, f, s);
-  sp.ntiles = (sp.V + kEoBlock - 1) / kEoBlock;
-  const unsigned nb = split_grid(sp);
-  const auto run = [&](auto kernel) {
-    kernel<<<nb, kEoBlock, 0, s>>>(static_cast<const typename Packed<T>::S*>(in),
-                                   static_cast<const typename Packed<T>::S*>(w),
-                                   static_cast<typename Packed<T>::S*>(out), lp, lq, cf, stride, g5, sp, f);
-    return hipGetLastError();
-  };
-  if (sp.link_bytes != 0 && sp.spinor_bytes != 0) return run(&eo_hop_kernel<T, C12, CGM, true>);
-  return run(&eo_hop_kernel<T, C12, CGM, false>);
+  } else {
+    if (use_split_eo(g->prec, C12, geo.Vh, set.n) && !(CGM != kCgNone && wide_slices(geo.Vh)))
+      return launch_split_hop<T, C12, CGM, FOLD>(in, w, out, lp, lq, cf, stride, g5, sp, f, s);
+    sp.ntiles = (sp.V + kEoBlock - 1) / kEoBlock;
+    const unsigned nb = split_grid(sp);
+    const auto run = [&](auto kernel) {
+      kernel<<<nb, kEoBlock, 0, s>>>(static_cast<const typename Packed<T>::S*>(in),
+                                     static_cast<const typename Packed<T>::S*>(w),
+                                     static_cast<typename Packed<T>::S*>(out), lp, lq, cf, stride, g5, sp, f);
+      return hipGetLastError();
+    };
+    if (sp.link_bytes != 0 && sp.spinor_bytes != 0) return run(&eo_hop_kernel<T, C12, CGM, true>);
+    return run(&eo_hop_kernel<T, C12, CGM, false>);
+  }
 }
 
 template <typename T, bool C12>

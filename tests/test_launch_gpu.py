@@ -271,6 +271,17 @@ def test_schur_kernels(dims, nrhs, prec, c12):
     assert rel(got, oracle.gamma5_schur(U, masses[k], odd)) <= tol
 
 
+@pytest.mark.parametrize("dims,nrhs,c12", [
+    ((16, 16, 16, 16), 2, True),   # 65536 half sites: the last launch with one lane per site
+    ((16, 16, 16, 16), 2, False),
+    ((10, 12, 12, 14), 5, True),   # 50400: one lane per site with 12-real links only
+    ((10, 12, 12, 14), 5, False),
+], ids=["65536_c12", "65536", "50400_c12", "50400"])
+def test_schur_fp64_kernels(dims, nrhs, c12):
+    """FP64 launches around the sizes that one lane per site takes, as above."""
+    test_schur_kernels(dims, nrhs, "fp64", c12)
+
+
 @pytest.mark.parametrize("inner", ["fp64", "fp32", "fp16"])
 @pytest.mark.parametrize("dims", [(6, 4, 10, 8), (16, 16, 16, 16), (24, 24, 24, 20)],
                          ids=lambda d: "x".join(map(str, d)))

@@ -37,7 +37,7 @@ hipError_t launch_eo_hop(const wd_gauge* g, int parity, const void* in, const vo
 hipError_t launch_schur_q(const wd_gauge* g, const double* masses, const RhsSet& set, const void* in,
                           void* tmp, void* out, const CgFuse* f, hipStream_t s);
 // Slices of that work (32 consecutive half sites, or 256 on large lattices), or
-// 0 where it does not apply (FP64 on large lattices).
+// 0 where it does not apply (FP64 on large lattices, FP32 and FP16 on the largest).
 int eo_fuse_slices(const int32_t dims[4], int prec);
 // Whether n field slots should form p inside kCgNorm (CgFuse::p_out).
 bool eo_fold_p(const int32_t dims[4], int prec, int n);

@@ -286,7 +286,12 @@ hipError_t launch_site_cg(const wd_gauge* g, const double* masses, int nrhs, con
 int eo_fuse_slices(const int32_t dims[4], int prec) {
   const long Vh = make_eo_geo(dims).Vh;
   if (!wide_slices(Vh)) return static_cast<int>((Vh + kSplitSites - 1) / kSplitSites);
-  return prec == WD_FP64 ? 0 : static_cast<int>((Vh + kEoBlock - 1) / kEoBlock);
+  // Every workgroup of an update adds all partial sums of its field: reading that
+  // grows with Vh^2, and with its share the gain (us per iteration unfused / fused:
+  // FP16 64^4 7323 / 7172, 80^3 x 64 13990 / 14400; FP32 64^4 10570 / 9980, 80^3 x 64 20700 /
+  // 20160, 80^3 x 68 21920 / 21360). The two meet at about these half volumes.
+  constexpr long kLargest[] = {131072, 23000000, 11500000};  // FP64, FP32, FP16
+  return Vh > kLargest[prec] ? 0 : static_cast<int>((Vh + kEoBlock - 1) / kEoBlock);
 }
 
 // Five launches per iteration become four; r is read by both hops. 8^4 FP64 35.9

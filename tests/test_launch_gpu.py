@@ -485,3 +485,32 @@ def test_solves_without_fused_work(inner):
     for k in range(2):
         r = bs[k] - oracle.normal_op(U, masses[k], both[k])
         assert np.linalg.norm(r) <= 1e-10 * np.linalg.norm(bs[k])
+
+
+@pytest.mark.parametrize("dims,inner", [((64, 64, 64, 88), "fp16"), ((64, 64, 96, 118), "fp32")],
+                         ids=["fp16", "fp32"])
+def test_even_odd_solves_on_the_largest_lattices(dims, inner):
+    """Just above 11.5 (FP16) and 23 (FP32) million half sites even-odd solves fuse
+    nothing: |b - D x| / |b| by the FP64 operator, with checks after every
+    iteration and after every fourth."""
+    print(f"case largest even-odd solves dims={dims} inner={inner}", flush=True)
+    prec, mass, tol = PRECS[inner], 1.0, 1e-8
+    U = dev.random_gauge(dims, 181)
+    full, ghi, glo = DeviceGauge(U, w.WD_FP64), DeviceGauge(U, w.WD_FP64, eo=True), DeviceGauge(U, prec, eo=True)
+    del U
+    b = full.pack(dev.gaussian_spinor(dims, 182)).view(torch.float64)
+    ws = torch.empty(w.wilson_workspace_bytes(dims, 1, prec, 1), dtype=torch.uint8, device="cuda")
+    for every in (1, 4):
+        x = full.spinor()
+        rc, stats = w.cg_solve_wilson(ghi.handle, glo.handle, [mass], 1, b, x,
+                                      dict(tol=tol, max_iter=500, inner=prec, delta=0.1, check_every=every,
+                                           x0_given=0, use_graph=0), ws)
+        assert rc == w.WD_OK, stats
+        dx = full.spinor()
+        w.dslash_apply(full.handle, mass, x, dx, w.WD_FP64)
+        r = float(torch.linalg.vector_norm(b - dx.view(torch.float64)) / torch.linalg.vector_norm(b))
+        print(f"every={every} iters={stats[0]['iters']} residual={r:.2e}", flush=True)
+        # tol holds for this quantity as the library forms it; forming it rounds at about 1e-15
+        assert r <= tol + 1e-13, r
+    del b, ws, x, dx
+    torch.cuda.empty_cache()

@@ -65,7 +65,9 @@ CgLayout cg_layout(const int32_t dims[4], int slots, int inner, bool eo) {
     o += lo;
   }
   w.t = o; o += lo;
-  if (w.nslices == 0 || inner == WD_FP64) {  // FP64 keeps A p (the update is not fused)
+  // A p, where the update of r is a launch of its own; in FP64, which fuses it on
+  // lattices of up to 131072 (half) sites, otherwise a waiting iteration's direction
+  if (w.nslices == 0 || inner == WD_FP64) {
     w.ap = o;
     o += lo;
   }

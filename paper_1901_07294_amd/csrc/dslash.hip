@@ -269,11 +269,11 @@ constexpr int kOuterAhead = 0, kOuterNow = 1, kOneBuffer = 2, kOneSlice = 3;
 // in the split kernel's order: the same bits as that kernel's, on tiles of any
 // number of lanes.
 // The fused modes with FP32 arithmetic and one right-hand side per lane are
-// compiled for three waves per SIMD (the plain FP32-arithmetic kernel's
-// occupancy), at the cost of a few spilled registers in FP32 storage, which
-// measured faster than two waves without spills.
-// ONE: marches of a single slice (p.tb == 1). Without a next slice there is one
-// LDS slice and no accumulator or link column carried on, which brings FP16
+// compiled for three waves per SIMD, the plain FP32-arithmetic kernel's
+// occupancy; only their plain-pointer forms (fields or links of 4 GiB and more)
+// spill for it, eight or nine registers in FP32 storage.
+// kOneSlice (p.tb == 1): without a next slice there is one LDS slice and no
+// accumulator or link column carried on, which brings FP16
 // storage from 160 registers to 127 and, bound to five waves per SIMD, to 96
 // without a spill (2 to 3 % faster than at four with several fields; six waves
 // spill or serialise the loads: 3 to 7 % slower). Twice the waves outweigh that t
@@ -282,7 +282,7 @@ constexpr int kOuterAhead = 0, kOuterNow = 1, kOneBuffer = 2, kOneSlice = 3;
 // us; a solve with FP16 inner iterations on 16^3 x 32 7.9 -> 7.0 ms.
 template <int CGM, typename T, int RB, int KIND>
 constexpr int march_waves_per_eu() {
-    if (KIND == kOneSlice) return sizeof(T) == 2 && CGM == kCgNone ? 5 : 1;
+  if (KIND == kOneSlice) return sizeof(T) == 2 && CGM == kCgNone ? 5 : 1;
   return RB == 1 && sizeof(typename Packed<T>::R) == 4 && CGM != kCgNone ? 3 : 1;
 }
 
@@ -785,8 +785,8 @@ hipError_t launch_march_t(const void* in, void* out, const void* links, const Ge
 //  - FP32 arithmetic: kOuterNow (24^3 x 48 with three fields 174 -> 161 us, 28 x 15
 //    x 22 x 33 43 -> 35, 32^4 97 -> 95). Two right-hand sides per lane beyond 208
 //    lanes: kOneBuffer, which lets a second workgroup in (32^4 with two fields
-//    176 -> 161 us, with four 316 -> 281, 16^3 x 32 with four 40.3 -> 36.4). The
-//    fused CG modes with one field per lane run kOuterAhead: their epilogue's loads
+//    176 -> 161 us, with four 316 -> 281, 16^3 x 32 with four 40.3 -> 36.4); the fused
+//    CG modes take the same two variants there. The fused CG modes with one field per lane run kOuterAhead: their epilogue's loads
 //    leave the outer hops to hide the next slice's (FP32 solves, ahead / now: 24^4
 //    18.9 / 19.9 ms, 32^3 x 16 28.1 / 29.3, 24^4 with three fields 54.0 / 58.1).
 template <typename T, bool C12, int CGM, bool BUF>
@@ -975,8 +975,9 @@ MarchParams with_tuning(MarchParams p, const MarchTuning& t) {
   return p;
 }
 
-// cg: a CG iteration's fused work (the march kernel only; nullptr for a plain
-// apply): cg->mode kCgNorm or kCgUpdate.
+// cg: a CG iteration's fused work (cg->mode kCgNorm or kCgUpdate), or nullptr for a
+// plain apply. On small lattices the split kernel or the march (small_march) does
+// it, on others the march.
 template <typename T, bool C12>
 hipError_t launch_typed(const wd_gauge* g, const void* in, void* out, const Geo& geo,
                         const double* masses, int nrhs, const int* fields, int g5,

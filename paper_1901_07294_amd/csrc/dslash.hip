@@ -640,11 +640,11 @@ size_t real_bytes_of(int prec) { return prec == WD_FP64 ? 8 : 4; }
 // only in some modes (two FP32 fields per lane: 165 registers, three waves; with
 // the fused CG work 171, two).
 // Fitted on MI355X to every split of t and both rb timed on up to 20 lattices
-// with 1 to 16 right-hand sides, from 16^4 to 48^4, among them 28 x 15 x 22 x 33, 9 x
+// with 1 to 16 right-hand sides, from 16^4 to 32^3 x 64, among them 28 x 15 x 22 x 33, 9 x
 // 33 x 12 x 20 and 21^4, in FP32 with 12-real links too. By how much the choice is
 // slower than the best launch timed, on average (at most), in percent:
 //   FP64  up to 208 lanes 0.9 (8); beyond, one workgroup per CU, 1.5
-//   FP32  up to 208 lanes 0.9 (8), fused 1.5 (12); 256 lanes 2.1 (10), fused 0.6 (6);
+//   FP32  up to 208 lanes 0.9 (8), fused 1.5 (12); 256 lanes 1.2 (16), fused 0.6 (6);
 //         between them 1.9 (5)
 //   FP16  from 2^20 sites on 1.4 (5), fused 1.1 (5)
 // where one resident round of workgroups whatever its last round leaves idle was
@@ -669,7 +669,7 @@ MarchCost march_cost(int prec, int n, int nrhs, bool fused, bool ahead) {
   if (prec == WD_FP32 && two)
     return fused ? MarchCost{8, 8, 0.4, 0.7, 0.4, 1.0, 1.3, -1.0} : MarchCost{8, 12, 0.4, 0.4, 0.4, 1.0, 1.2, -1.0};
   if (prec == WD_FP32 && n == kMarchMaxThreads)
-    return fused ? MarchCost{12, 8, 0.4, 0.7, 0.2, 1.0, 1.3, -1.0} : MarchCost{12, 8, 0.2, 0.2, 0.1, 0.6, 1.2, -1.0};
+    return fused ? MarchCost{12, 8, 0.4, 0.7, 0.2, 1.0, 1.3, -1.0} : MarchCost{12, 8, 0.2, 0.4, 0.1, 0.6, 1.2, -1.0};
   if (prec == WD_FP32) return {8, 8, 0.4, 0.7, 1.0, 1.0, 1.2, -1.0};
   if (fused && nrhs > 1) return {12, 0, 1.1, 0.0, 0.0, 0.0, 0.0, 0.5};
   return {16, 0, 0.4, 0.0, 0.0, 0.0, 0.0, 0.3};
@@ -696,7 +696,14 @@ MarchParams march_params(const Geo& geo, int prec, int nrhs, bool fused = false,
   // among equals the shorter march; in FP32 the fused CG work on tiles up to 208
   // lanes also takes one that costs up to 4 % more (24^4 with three fields: 311 us
   // per iteration at 12 slices per workgroup, 287 at 6)
-  const double tie = fused && prec == WD_FP32 && two_workgroups(n) ? 1.04 : 1.0;
+  // and the plain operator on tiles of 256 lanes, where the fields outgrow the caches,
+  // a shorter march only if it costs 4 % less (32^3 x 64 190 us at 16 slices per
+  // workgroup, 200 at 11, which the model puts 1 % lower; 64 x 32 x 16 x 24 72 at six, 78
+  // at four; below, 16^2 x 24 x 48 with 12-real links 23.6 at the shorter, 27.1 at the longer)
+  const bool large = static_cast<long>(geo.V) * nrhs >= 500000;
+  double tie = 1.0;
+  if (prec == WD_FP32 && fused && two_workgroups(n)) tie = 1.04;
+  if (prec == WD_FP32 && !fused && n == kMarchMaxThreads && large) tie = 0.96;
   // FP16 storage: one slice per workgroup (its own kernel), unless the fields and
   // links outgrow the 256 MB cache that serves the t neighbours then (about 2^20
   // sites; us, one slice / best longer march: 24^3 x 48 37.5 / 41.2, 32^4 59.9 /
@@ -724,7 +731,7 @@ MarchParams march_params(const Geo& geo, int prec, int nrhs, bool fused = false,
         rounds = std::max(1.0, columns * nt / (static_cast<double>(kNumCu) * per_cu) + mc.tail);
       }
       const double cost = rounds * (tb + (rb == 1 ? mc.prologue : mc.prologue2)) * (rb == 1 ? 1.0 : mc.rb2);
-      if (p.tb == 0 || cost < best || (cost <= best * tie && rb == p.rb)) {
+      if (p.tb == 0 || cost < best * std::min(tie, 1.0) || (cost <= best * tie && rb == p.rb)) {
         best = p.tb == 0 ? cost : std::min(best, cost);
         p.tb = tb;
         p.rb = rb;

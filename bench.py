@@ -49,14 +49,14 @@ def compulsory_bytes(prec: str, c12: bool) -> int:
 TRAFFIC = {
     # FETCH_SIZE x 2.000 + WRITE_SIZE x 1.000 (copy-calibrated KiB per dispatch), measured for
     # the kernel code hashed below, per launch "tb,gw,group,rb" the bytes belong to
-    "wilson_dslash_32x32x32x64_fp64": {"source_sha": "0c1042dda75ccce5", "launches": {
-        "32,1,32,1": 2212778080}},  # 883,850 / 393,216
-    "wilson_dslash_32x32x32x64_fp64_c12": {"source_sha": "0c1042dda75ccce5", "launches": {
-        "32,1,32,1": 1782736448}},  # 673,846 / 393,261
-    "wilson_dslash_32x32x32x64_fp32": {"source_sha": "0c1042dda75ccce5", "launches": {
-        "16,1,64,1": 1223784032}},  # 499,247 / 196,608
-    "wilson_dslash_32x32x32x64_fp16": {"source_sha": "0c1042dda75ccce5", "launches": {
-        "4,1,256,1": 644377696}},   # 261,390 / 106,496
+    "wilson_dslash_32x32x32x64_fp64": {"source_sha": "552c564f72c84e31", "launches": {
+        "32,1,32,1": 2208722528}},  # 881,870 / 393,216
+    "wilson_dslash_32x32x32x64_fp64_c12": {"source_sha": "552c564f72c84e31", "launches": {
+        "32,1,32,1": 1780879840}},  # 672,944 / 393,253
+    "wilson_dslash_32x32x32x64_fp32": {"source_sha": "552c564f72c84e31", "launches": {
+        "16,1,64,1": 1224191104}},  # 499,446 / 196,608
+    "wilson_dslash_32x32x32x64_fp16": {"source_sha": "552c564f72c84e31", "launches": {
+        "4,1,256,1": 644567968}},   # 261,482 / 106,496
 }
 KERNEL_SOURCES = ["paper_1901_07294_amd/csrc/dslash.hip", "paper_1901_07294_amd/csrc/split.h",
                   "paper_1901_07294_amd/csrc/stencil.h",

@@ -100,7 +100,7 @@ __global__ __launch_bounds__(kSiteBlock) __attribute__((amdgpu_waves_per_eu(4, 4
     const h8* __restrict__ in_all, h8* __restrict__ out_all, const h2* __restrict__ links, Diag<float> diags,
     long stride, int gamma5, SplitParams p) {
   int rhs;
-  const int tile = split_tile(p, &rhs);
+  const int tile = split_tile<true>(p, &rhs);
   const int s = tile * kSiteBlock + static_cast<int>(threadIdx.x);
   if (tile >= p.ntiles || s >= p.V) return;
   const long V = p.V;

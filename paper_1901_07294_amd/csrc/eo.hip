@@ -56,7 +56,7 @@ __global__ __launch_bounds__(kEoBlock) void eo_hop_kernel(
   using GS = typename Packed<T>::S;
   __shared__ double aw[kEoBlock / 64];
   int rhs;
-  const int tile = split_tile(p, &rhs);
+  const int tile = split_tile<CGM == kCgNone>(p, &rhs);
   if (tile >= p.ntiles) return;
   const long k = cf.idx[rhs];
   const int h0 = tile * kEoBlock + static_cast<int>(threadIdx.x);

@@ -166,9 +166,17 @@ __device__ __forceinline__ int split_neighbour(const SplitParams& p, int mu, int
 // from HBM once: with the right-hand sides in the grid's second dimension four
 // FP64 fields on an even-odd 24^4 took 443 us per application, now 284. The
 // shares are of workgroups, not of tiles: 41 tiles of six fields are 31
-// workgroups for each XCD's 32 CUs, where six tiles each were 36.
+// workgroups for each XCD's 32 CUs, where six tiles each were 36. One field skips the
+// divisions, which stand before the first load (FP64 27 x 4 x 14 x 14 7.5 -> 7.1 us, the
+// Schur operator on 12^4 12.9 -> 12.2).
+// The kernels with CG work, whose first loads are the partial sums, lost 1 % by it (ONE).
+template <bool ONE>
 __device__ __forceinline__ int split_tile(const SplitParams& p, int* rhs) {
   const int b = blockIdx.x % kNumXcd * p.per + blockIdx.x / kNumXcd;
+  if (ONE && p.nrhs == 1) {
+    *rhs = 0;
+    return b;
+  }
   *rhs = b % p.nrhs;
   return b / p.nrhs;
 }
@@ -234,7 +242,7 @@ __global__ __launch_bounds__(kSplitThreads) void split_hop_kernel(
   __shared__ double aw[kSplitThreads / 64];
 
   int rhs;
-  const int tile = split_tile(p, &rhs);
+  const int tile = split_tile<CGM == kCgNone>(p, &rhs);
   if (tile >= p.ntiles) return;
   const long k = cf.idx[rhs];
   const auto in = field_in<BUF>(in_all + k * stride, p.spinor_bytes);

@@ -49,14 +49,14 @@ def compulsory_bytes(prec: str, c12: bool) -> int:
 TRAFFIC = {
     # FETCH_SIZE x 2.000 + WRITE_SIZE x 1.000 (copy-calibrated KiB per dispatch), measured for
     # the kernel code hashed below, per launch "tb,gw,group,rb" the bytes belong to
-    "wilson_dslash_32x32x32x64_fp64": {"source_sha": "552c564f72c84e31", "launches": {
-        "32,1,32,1": 2208722528}},  # 881,870 / 393,216
-    "wilson_dslash_32x32x32x64_fp64_c12": {"source_sha": "552c564f72c84e31", "launches": {
-        "32,1,32,1": 1780879840}},  # 672,944 / 393,253
-    "wilson_dslash_32x32x32x64_fp32": {"source_sha": "552c564f72c84e31", "launches": {
-        "16,1,64,1": 1224191104}},  # 499,446 / 196,608
-    "wilson_dslash_32x32x32x64_fp16": {"source_sha": "552c564f72c84e31", "launches": {
-        "4,1,256,1": 644567968}},   # 261,482 / 106,496
+    "wilson_dslash_32x32x32x64_fp64": {"source_sha": "69e84e24a3962ce4", "launches": {
+        "32,1,32,1": 2209820512}},  # 882,406 / 393,216
+    "wilson_dslash_32x32x32x64_fp64_c12": {"source_sha": "69e84e24a3962ce4", "launches": {
+        "32,1,32,1": 1783660800}},  # 674,295 / 393,266
+    "wilson_dslash_32x32x32x64_fp32": {"source_sha": "69e84e24a3962ce4", "launches": {
+        "16,1,64,1": 1225095520}},  # 499,887 / 196,608
+    "wilson_dslash_32x32x32x64_fp16": {"source_sha": "69e84e24a3962ce4", "launches": {
+        "4,1,256,1": 644842464}},   # 261,616 / 106,496
 }
 KERNEL_SOURCES = ["paper_1901_07294_amd/csrc/dslash.hip", "paper_1901_07294_amd/csrc/split.h",
                   "paper_1901_07294_amd/csrc/stencil.h",

@@ -49,14 +49,14 @@ def compulsory_bytes(prec: str, c12: bool) -> int:
 TRAFFIC = {
     # FETCH_SIZE x 2.000 + WRITE_SIZE x 1.000 (copy-calibrated KiB per dispatch), measured for
     # the kernel code hashed below, per launch "tb,gw,group,rb" the bytes belong to
-    "wilson_dslash_32x32x32x64_fp64": {"source_sha": "69e84e24a3962ce4", "launches": {
-        "32,1,32,1": 2209820512}},  # 882,406 / 393,216
-    "wilson_dslash_32x32x32x64_fp64_c12": {"source_sha": "69e84e24a3962ce4", "launches": {
-        "32,1,32,1": 1783660800}},  # 674,295 / 393,266
-    "wilson_dslash_32x32x32x64_fp32": {"source_sha": "69e84e24a3962ce4", "launches": {
-        "16,1,64,1": 1225095520}},  # 499,887 / 196,608
-    "wilson_dslash_32x32x32x64_fp16": {"source_sha": "69e84e24a3962ce4", "launches": {
-        "4,1,256,1": 644842464}},   # 261,616 / 106,496
+    "wilson_dslash_32x32x32x64_fp64": {"source_sha": "6b84618ea204f636", "launches": {
+        "32,1,32,1": 2212633536}},  # 883,779 / 393,216
+    "wilson_dslash_32x32x32x64_fp64_c12": {"source_sha": "6b84618ea204f636", "launches": {
+        "32,1,32,1": 1781744256}},  # 673,356 / 393,273
+    "wilson_dslash_32x32x32x64_fp32": {"source_sha": "6b84618ea204f636", "launches": {
+        "16,1,64,1": 1224353504}},  # 499,525 / 196,608
+    "wilson_dslash_32x32x32x64_fp16": {"source_sha": "6b84618ea204f636", "launches": {
+        "4,1,256,1": 644828288}},   # 261,610 / 106,496
 }
 KERNEL_SOURCES = ["paper_1901_07294_amd/csrc/dslash.hip", "paper_1901_07294_amd/csrc/split.h",
                   "paper_1901_07294_amd/csrc/stencil.h",
